@@ -43,255 +43,224 @@ __device__ __forceinline__ Lds carve(uint8_t *smem, const Geom &g)
 }
 
 // ---------------------------------------------------------------- map generation
-// Cells within BFS distance r of `src` (4-neighbour steps over the passable
-// bitmap), for up to three radii in one sweep: lane w < NW gets word w of
-// each set.  r < 0 means unlimited (the connected component).  Layer by
-// layer bitmap dilation (like the fog, with 4 instead of 8 neighbours) until
-// the last requested radius or a fixpoint.  Every lane must call it.
-struct Reach3 { uint64_t a, b, c; };
+// The generator works on row bitmaps: lane r holds row r of the board as 32
+// bits (bit = column), so the 4-neighbour step is two shifts and two wave
+// shifts, a Manhattan ball is one mask per row, and a uniform pick is a
+// prefix sum over the rows' populations and one ballot.  It is bound by
+// vector issue and, in small batches, by its serial chain.  A Philox4x64
+// block costs a wave about 2,000 clocks and gives every lane 8 draws, so
+// the draws after the cells' come from the block round that drew the last
+// cells, one per lane, rather than from a block each.  Measured with the
+// observation: 65,536 maps of 24x24 1,229 -> 178 us, 512 official 23x23
+// maps 55 -> 18 us (before: cell bitmaps of 64-bit words in LDS, a Philox
+// block per draw, the plain cells balloted again for every city).
 
-__device__ Reach3 bfs_reach(const uint64_t *pass, int src, int ra, int rb, int rc, const Geom &g)
+// Bits [lane W, lane W + W) of a cell bitmap in LDS: row `lane` of the board
+// (0 past the last row).  Reads at most one dword past the bitmap's last.
+__device__ __forceinline__ uint32_t row_bits(const uint32_t *bm, uint32_t rowm, const Geom &g)
 {
-    const int lane = lane_id(), NW = g.NW, W = g.W;
-    const ColMasks cm = col_masks(lane < NW ? lane : 0, g);
-    const uint64_t pw = lane < NW ? pass[lane] : 0ull;
-    uint64_t cw = (lane == (src >> 6)) ? (1ull << (src & 63)) : 0ull;
-    Reach3 out{cw, cw, cw};
-    const int rmax = (ra < 0 || rb < 0 || rc < 0) ? INT32_MAX : max(ra, max(rb, rc));
-    for (int r = 1; r <= rmax; ++r) {
-        const uint64_t prev = shfl64(cw, lane - 1), next = shfl64(cw, lane + 1);
-        const uint64_t pv = lane > 0 ? prev : 0ull, nx = lane < NW - 1 ? next : 0ull;
-        uint64_t n = cw;
-        n |= ((cw << 1) | (pv >> 63)) & ~cm.col0;
-        n |= ((cw >> 1) | (nx << 63)) & ~cm.colL;
-        n |= (cw << W) | (pv >> (64 - W));
-        n |= (cw >> W) | (nx << (64 - W));
-        n &= pw;
+    const int o = (rowm ? lane_id() : 0) * g.W;
+    const uint64_t v = (uint64_t)bm[o >> 5] | ((uint64_t)bm[(o >> 5) + 1] << 32);
+    return (uint32_t)(v >> (o & 31)) & rowm;
+}
+
+// One cell and its place: row and column (wave-uniform).
+struct RowCol { int r, c; };
+
+// The cell at position idx (row-major order) of a row bitmap whose rows'
+// inclusive population prefix is `incl`; idx < population.
+__device__ __forceinline__ RowCol row_select(uint32_t row, uint32_t incl, uint32_t idx)
+{
+    const uint32_t excl = incl - (uint32_t)__popc(row);
+    const int r = __builtin_ctzll(ballot(excl <= idx && idx < incl));
+    const uint32_t word = (uint32_t)readlane((int)row, r), t = idx - (uint32_t)readlane((int)excl, r);
+    const bool hit = lane_id() < 32 && ((word >> (lane_id() & 31)) & 1u) && __builtin_amdgcn_mbcnt_lo(word, 0u) == t;
+    return {r, __builtin_ctzll(ballot(hit))};
+}
+
+// Cells within BFS distance r of a cell (4-neighbour steps over `pass`).
+__device__ uint32_t row_reach(uint32_t pass, RowCol src, int radius)
+{
+    uint32_t cw = lane_id() == src.r ? 1u << src.c : 0u;
+    for (int r = 1; r <= radius; ++r) {
+        const uint32_t n = (cw | (cw << 1) | (cw >> 1) | wave_shr1(cw, 0u) | wave_shl1(cw, 0u)) & pass;
         const bool changed = ballot(n != cw) != 0ull;
         cw = n;
-        if (ra < 0 || r <= ra) out.a = cw;
-        if (rb < 0 || r <= rb) out.b = cw;
-        if (rc < 0 || r <= rc) out.c = cw;
         if (!changed) break;
     }
-    return out;
+    return cw;
 }
 
-// The official rules after G1/G2 (reading R18): each further general among
-// the cells whose BFS distance to every earlier general lies in
-// [dmin, dmax], the castle count, a castle within the radius of every
-// general that has none, the rest anywhere.  `j` is the next draw index.
-// Returns false when this attempt has to be abandoned.
-__device__ bool mapgen_official(const Lds &L, const Geom &g, const GenParamsDev &prm, uint64_t seed,
-                                uint64_t env_id, uint32_t episode, int attempt, uint32_t &j, int *gp)
+// The 4-connected component of a cell: one row up and down per round, and
+// each row's runs filled at once (adding the seeds to the passable bits
+// carries through a run to its end; the other direction on reversed rows).
+__device__ uint32_t row_component(uint32_t pass, RowCol src)
 {
-    const int lane = lane_id(), NW = g.NW, HW = g.HW;
-    const uint64_t *pass = L.gbm;
-    uint64_t *cand = L.gbm + 32;
-    const int lo_r = prm.dmin - 1;                       // cells within dmin-1 are too close
-    const int hi_r = prm.dmax > 0 ? prm.dmax : -1;
-    uint64_t acc = lane < NW ? pass[lane] : 0ull;        // word `lane` of the candidate set
-    uint64_t gens = 0ull;                                // word `lane` of the general cells
-    for (int i = 0;; ++i) {
-        const int gi = gp[i];
-        if (lane == (gi >> 6)) gens |= 1ull << (gi & 63);
-        if (i == g.P - 1) break;
-        const Reach3 r = bfs_reach(pass, gi, lo_r < 0 ? 0 : lo_r, hi_r, 0, g);
-        acc &= r.b & (lo_r < 0 ? ~0ull : ~r.a);
-        acc &= ~gens;
-        if (lane < NW) cand[lane] = acc;
-        const uint32_t n = (uint32_t)readfirst((int)wave_sum_u32(lane < NW ? (uint32_t)__popcll(acc) : 0u));
-        wave_sync();
-        if (n == 0) return false;
-        const int gn = bm_select(cand, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), n));
-        if (lane == 0) { gp[i + 1] = gn; L.type[gn] = GENERAL; }
-        wave_sync();
+    const uint32_t rp = __brev(pass);
+    uint32_t cw = lane_id() == src.r ? 1u << src.c : 0u;
+    for (;;) {
+        uint32_t n = (cw | wave_shr1(cw, 0u) | wave_shl1(cw, 0u)) & pass;
+        n |= pass & ~(pass + n);
+        uint32_t b = __brev(n);
+        b |= rp & ~(rp + b);
+        n = __brev(b);
+        if (ballot(n != cw) == 0ull) return n;
+        cw = n;
     }
-    const int ncas = prm.cmin + (int)pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++),
-                                          (uint32_t)(prm.cmax - prm.cmin + 1));
-    uint64_t cas = 0ull;                                 // word `lane` of the castle cells
-    int placed = 0;
-    for (int i = 0; i < g.P; ++i) {
-        const Reach3 r = bfs_reach(pass, gp[i], prm.radius, 0, 0, g);
-        if (ballot((r.a & cas) != 0ull) != 0ull) continue;
-        const uint64_t c_w = lane < NW ? (r.a & pass[lane] & ~gens & ~cas) : 0ull;
-        if (lane < NW) cand[lane] = c_w;
-        const uint32_t n = (uint32_t)readfirst((int)wave_sum_u32((uint32_t)__popcll(c_w)));
-        wave_sync();
-        if (n == 0) return false;
-        const int c = bm_select(cand, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), n));
-        const int32_t a = prm.amin + (int32_t)pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++),
-                                                   (uint32_t)(prm.amax - prm.amin + 1));
-        if (lane == 0) { L.type[c] = CASTLE; L.army[c] = a; }
-        if (lane == (c >> 6)) cas |= 1ull << (c & 63);
-        ++placed;
-        wave_sync();
-    }
-    for (int t = placed; t < ncas; ++t) {
-        uint32_t n = 0;
-        for (int w = 0; w < NW; ++w) {
-            const int c = w * 64 + lane;
-            const uint64_t m = ballot(c < HW && L.type[c] == PLAIN);
-            if (lane == 0) cand[w] = m;
-            n += (uint32_t)__popcll(m);
-        }
-        wave_sync();
-        if (n == 0) break;
-        const int c = bm_select(cand, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), n));
-        const int32_t a = prm.amin + (int32_t)pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++),
-                                                   (uint32_t)(prm.amax - prm.amin + 1));
-        if (lane == 0) { L.type[c] = CASTLE; L.army[c] = a; }
-        wave_sync();
-    }
-    return true;
 }
 
-// Section IV-A generator family (reading R14; the official rules, R18).  Executed by the whole wave
-// with uniform control flow; every random choice is a Philox draw indexed
-// exactly as the generator's draw order defines.  Leaves the grid in LDS and
-// the scalars in `s`.
+// Section IV-A generator family (readings R14, R18).  Executed by the whole
+// wave with uniform control flow; every random choice is a Philox draw
+// indexed exactly as the generator's draw order defines.  Leaves the grid in
+// LDS and the scalars in `s`.
 __device__ void mapgen_wave(const Lds &L, const Geom &g, const GenParamsDev &prm, uint64_t seed, uint64_t env_id,
                             uint32_t episode, EnvScalars &s)
 {
     const int lane = lane_id();
-    const int HW = g.HW, W = g.W, NW = g.NW;
-    uint64_t *pass = L.gbm, *comp = L.gbm + 16, *cand = L.gbm + 32;
-    int *gp = reinterpret_cast<int *>(L.gbm + 48);   // general cells, written by lane 0
+    const int HW = g.HW, W = g.W, H = g.H;
+    const uint32_t rowm = lane < H ? (W == 32 ? ~0u : (1u << W) - 1u) : 0u;     // the columns of row `lane`
+    uint8_t *mt8 = reinterpret_cast<uint8_t *>(L.gbm);                           // mountain bitmap, a byte per block
+    int gpv = 0;                                                                 // lane i: cell of general i
     bool placed = false;
+
+    // LDS rows of a map without owners: types from the mountain bitmap
+    auto blank = [&](bool mountains) {
+        for (int q = lane; q * 4 < g.S; q += kWave) {
+            const uint32_t m4 = mountains ? ((uint32_t)mt8[q >> 1] >> ((q & 1) * 4)) & 0xFu : 0u;
+            reinterpret_cast<uint32_t *>(L.type)[q] = spread4(m4) * (uint32_t)MOUNTAIN;
+            reinterpret_cast<uint32_t *>(L.owner)[q] = 0xFFFFFFFFu;
+            reinterpret_cast<uint4 *>(L.army)[q] = make_uint4(0u, 0u, 0u, 0u);
+        }
+        wave_sync();
+    };
 
     for (int attempt = 0; attempt < 128 && !placed; ++attempt) {
         const uint32_t T = attempt < 64 ? prm.thresh : 0u;
         // G1: one draw per cell; a Philox block gives the draws of 8 cells.
-        for (int b = lane; b * 8 < g.S; b += kWave) {
+        uint32_t v[8];
+        int base = 0;                                  // block of lane 0 in the last round
+        for (;; base += kWave) {
+            const int b = base + lane;
             uint64_t x0 = env_id, x1 = episode, x2 = (uint64_t)attempt, x3 = (uint64_t)b;
             philox4x64_10(x0, x1, x2, x3, seed, DOM_MAPGEN);
-            const uint64_t w4[4] = {x0, x1, x2, x3};
+            v[0] = (uint32_t)x0; v[1] = (uint32_t)(x0 >> 32); v[2] = (uint32_t)x1; v[3] = (uint32_t)(x1 >> 32);
+            v[4] = (uint32_t)x2; v[5] = (uint32_t)(x2 >> 32); v[6] = (uint32_t)x3; v[7] = (uint32_t)(x3 >> 32);
+            uint32_t m8 = 0;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int c = b * 8 + t;
-                const uint32_t r = (t & 1) ? (uint32_t)(w4[t >> 1] >> 32) : (uint32_t)w4[t >> 1];
-                if (c < g.S) {
-                    L.type[c] = (c < HW && r < T) ? MOUNTAIN : PLAIN;
-                    L.owner[c] = -1;
-                    L.army[c] = 0;
-                }
-            }
+            for (int t = 0; t < 8; ++t) m8 |= (v[t] < T ? 1u : 0u) << t;
+            const int left = HW - b * 8;
+            if (left < 8) m8 &= left > 0 ? (1u << left) - 1u : 0u;
+            if (b * 8 < g.S) mt8[b] = (uint8_t)m8;
+            if ((base + kWave) * 8 >= HW) break;
         }
-        wave_sync();
-        // passable bitmap and its population
-        uint32_t K = 0;
-        for (int w = 0; w < NW; ++w) {
-            const int c = w * 64 + lane;
-            const uint64_t m = ballot(c < HW && L.type[c] != MOUNTAIN);
-            if (lane == 0) pass[w] = m;
-            K += (uint32_t)__popcll(m);
+        // The draws after the cells': draw HW + t on lane t.  The last
+        // round's blocks hold the next ones (up to 512).  A longer sequence
+        // is drawn 64 at a time, each lane the block of its own draw: before
+        // the cities of a board that leaves fewer than the 32 draws that
+        // come before them, and between the cities.
+        uint32_t D = 0, j = 0, dn = (uint32_t)min(kWave, (base + kWave) * 8 - HW);   // draws j .. dn - 1 are on hand
+        uint32_t d0 = (uint32_t)HW;                    // first draw of the window
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t x = shfl32(v[t], ((HW + lane) >> 3) - base);
+            if (((HW + lane) & 7) == t) D = x;
         }
+        auto refill = [&]() {
+            d0 += j;
+            j = 0;
+            dn = kWave;
+            D = draw32(seed, DOM_MAPGEN, env_id, episode, (uint64_t)attempt, d0 + (uint32_t)lane);
+        };
+        auto draw = [&]() -> uint32_t { return (uint32_t)readlane((int)D, (int)(j++)); };
+        if (dn < 32u) refill();
         wave_sync();
-        if (K == 0) continue;
-        uint32_t j = (uint32_t)HW;
+        const uint32_t pass = ~row_bits(reinterpret_cast<const uint32_t *>(mt8), rowm, g) & rowm;
+        uint32_t incl = wave_incl_scan((uint32_t)__popc(pass));
+        uint32_t n = (uint32_t)readlane((int)incl, kWave - 1);
+        if (n == 0) continue;
         // G2: first general over the non-mountain cells in row-major order
-        const int g0 = bm_select(pass, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), K));
-        if (lane == 0) { gp[0] = g0; L.type[g0] = GENERAL; }
-        if (prm.generator == 1) {
-            wave_sync();
-            placed = mapgen_official(L, g, prm, seed, env_id, episode, attempt, j, gp);
-            continue;
-        }
-        // G3: 4-connected component of gp[0] (bitmap flood fill to a fixpoint)
-        {
-            const ColMasks cm = col_masks(lane < NW ? lane : 0, g);
-            const uint64_t pw = lane < NW ? pass[lane] : 0ull;
-            uint64_t cw = (lane == (g0 >> 6)) ? (1ull << (g0 & 63)) : 0ull;
-            for (;;) {
-                const uint64_t prev = shfl64(cw, lane - 1), next = shfl64(cw, lane + 1);
-                const uint64_t pv = lane > 0 ? prev : 0ull, nx = lane < NW - 1 ? next : 0ull;
-                uint64_t n = cw;
-                n |= ((cw << 1) | (pv >> 63)) & ~cm.col0;
-                n |= ((cw >> 1) | (nx << 63)) & ~cm.colL;
-                n |= (cw << W) | (pv >> (64 - W));
-                n |= (cw >> W) | (nx << (64 - W));
-                n &= pw;
-                const bool changed = ballot(n != cw) != 0ull;
-                cw = n;
-                if (!changed) break;
-            }
-            if (lane < NW) comp[lane] = cw;
-        }
-        wave_sync();
-        // G4: each further general in the component, far enough from all earlier ones
+        RowCol at = row_select(pass, incl, pick(draw(), n));
+        if (lane == 0) gpv = at.r * W + at.c;
+        uint32_t gens = lane == at.r ? 1u << at.c : 0u;
+        // G3: its 4-connected component; further generals stay inside it
+        // (with a cap on the BFS distance the reach takes its place)
+        const bool official = prm.generator == 1;
+        uint32_t room = official && prm.dmax > 0 ? pass : row_component(pass, at);
+        // G4: each further general far enough from all earlier ones: in
+        // Manhattan distance, or (R18) in BFS steps, at most dmax if set
         bool ok = true;
         for (int i = 1; i < g.P; ++i) {
-            uint32_t n = 0;
-            for (int w = 0; w < NW; ++w) {
-                const int c = w * 64 + lane;
-                bool in = c < HW && ((comp[w] >> lane) & 1ull) && L.type[c] != GENERAL;
-                if (in) {
-                    const int r = div_w(c, g), col = c - r * W;
-                    for (int k = 0; k < i; ++k) {
-                        const int gr = div_w(gp[k], g), gc = gp[k] - gr * W;
-                        const int d = abs(r - gr) + abs(col - gc);
-                        if (d < prm.dmin) in = false;
-                    }
-                }
-                const uint64_t m = ballot(in);
-                if (lane == 0) cand[w] = m;
-                n += (uint32_t)__popcll(m);
+            if (official) {
+                if (prm.dmin > 0) room &= ~row_reach(pass, at, prm.dmin - 1);
+                if (prm.dmax > 0) room &= row_reach(pass, at, prm.dmax);
+            } else {
+                const int k = prm.dmin - 1 - abs(lane - at.r);       // columns at.c - k .. at.c + k are too near
+                if (k >= 0) room &= ~(((2u << min(at.c + k, 31)) - 1u) & ~((1u << max(at.c - k, 0)) - 1u));
             }
-            wave_sync();
+            room &= ~gens;
+            incl = wave_incl_scan((uint32_t)__popc(room));
+            n = (uint32_t)readlane((int)incl, kWave - 1);
             if (n == 0) { ok = false; break; }
-            const int gi = bm_select(cand, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), n));
-            if (lane == 0) { gp[i] = gi; L.type[gi] = GENERAL; }
-            wave_sync();
+            at = row_select(room, incl, pick(draw(), n));
+            if (lane == i) gpv = at.r * W + at.c;
+            if (lane == at.r) gens |= 1u << at.c;
         }
         if (!ok) continue;
-        // G5: cities on remaining plain cells anywhere
-        const int ncity = prm.cmin + (int)pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++),
-                                               (uint32_t)(prm.cmax - prm.cmin + 1));
-        for (int t = 0; t < ncity; ++t) {
-            uint32_t n = 0;
-            for (int w = 0; w < NW; ++w) {
-                const int c = w * 64 + lane;
-                const uint64_t m = ballot(c < HW && L.type[c] == PLAIN);
-                if (lane == 0) cand[w] = m;
-                n += (uint32_t)__popcll(m);
-            }
-            wave_sync();
-            if (n == 0) break;
-            const int c = bm_select(cand, NW, pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++), n));
-            const int32_t a = prm.amin + (int32_t)pick(draw32(seed, DOM_MAPGEN, env_id, episode, attempt, j++),
-                                                       (uint32_t)(prm.amax - prm.amin + 1));
+        // G5: cities; under the official rules one within the radius of
+        // every general first, then the rest on plain cells anywhere
+        blank(true);
+        uint32_t plain = pass & ~gens, cas = 0u;
+        const int ncity = prm.cmin + (int)pick(draw(), (uint32_t)(prm.cmax - prm.cmin + 1));
+        auto city = [&](uint32_t among) -> bool {
+            incl = wave_incl_scan((uint32_t)__popc(among));
+            n = (uint32_t)readlane((int)incl, kWave - 1);
+            if (n == 0) return false;
+            at = row_select(among, incl, pick(draw(), n));
+            const int32_t a = prm.amin + (int32_t)pick(draw(), (uint32_t)(prm.amax - prm.amin + 1));
+            const int c = at.r * W + at.c;
             if (lane == 0) { L.type[c] = CASTLE; L.army[c] = a; }
-            wave_sync();
+            if (lane == at.r) { cas |= 1u << at.c; plain &= ~(1u << at.c); }
+            return true;
+        };
+        int t = 0;
+        if (official) {
+            for (int i = 0; i < g.P && ok; ++i) {
+                const int c = readlane(gpv, i), r = div_w(c, g);
+                const uint32_t near = row_reach(pass, {r, c - r * W}, prm.radius);
+                if (ballot((near & cas) != 0u) != 0ull) continue;
+                ok = city(near & plain);
+                ++t;
+            }
+            if (!ok) continue;
+        }
+        for (; t < ncity; ++t) {
+            if (j + 2u > dn) refill();
+            if (!city(plain)) break;
         }
         placed = true;
     }
     if (!placed) {
         // deterministic last resort: no mountains, no cities, fixed border cells
-        for (int c = lane; c < g.S; c += kWave) { L.type[c] = PLAIN; L.owner[c] = -1; L.army[c] = 0; }
-        if (lane == 0) {
-            for (int i = 0; i < g.P; ++i) {
-                const int r = (i == 0 || i == 2 || i == 4) ? 0 : (i == 1 || i == 3 || i == 5) ? g.H - 1 : g.H / 2;
-                const int c = (i == 0 || i == 3 || i == 6) ? 0 : (i == 1 || i == 2 || i == 7) ? W - 1 : W / 2;
-                gp[i] = r * W + c;
-            }
-        }
+        blank(false);
+        const int r = (lane == 0 || lane == 2 || lane == 4) ? 0 : (lane == 1 || lane == 3 || lane == 5) ? H - 1 : H / 2;
+        const int c = (lane == 0 || lane == 3 || lane == 6) ? 0 : (lane == 1 || lane == 2 || lane == 7) ? W - 1 : W / 2;
+        gpv = r * W + c;
     }
     wave_sync();
     // G6: generals (plus pre-grown armies on the overflow-stress workload)
-    if (lane == 0) {
-        for (int i = 0; i < g.P; ++i) {
-            const int c = gp[i];
-            L.type[c] = GENERAL;
-            L.owner[c] = (int8_t)i;
-            int32_t a = 1;
-            if (prm.pregrow && episode == 0 && (env_id & 3) == 0)
-                a = 100000 + (int32_t)pick(draw32(seed, DOM_PREGROW, env_id, 0, 0, (uint32_t)i), 900001u);
-            L.army[c] = a;
+    int32_t a = 1;
+    if (prm.pregrow && episode == 0 && (env_id & 3) == 0)
+        a = 100000 + (int32_t)pick(draw32(seed, DOM_PREGROW, env_id, 0, 0, (uint32_t)(lane & 7)), 900001u);
+    for (int i = 0; i < g.P; ++i) {                    // in order: the last resort's cells may coincide
+        if (lane == i) {
+            L.type[gpv] = GENERAL;
+            L.owner[gpv] = (int8_t)i;
+            L.army[gpv] = a;
         }
     }
     wave_sync();
 #pragma unroll
-    for (int i = 0; i < kMaxP; ++i) s.gpos[i] = (int16_t)(i < g.P ? gp[i] : -1);
+    for (int i = 0; i < kMaxP; ++i) s.gpos[i] = (int16_t)(i < g.P ? readlane(gpv, i) : -1);
     s.turn = 0;
     s.episode = episode;
     s.alive = (uint8_t)((1u << g.P) - 1u);
