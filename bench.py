@@ -37,7 +37,8 @@ import workloads  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ["paper_2606_23348_amd/csrc/kernels.hip", "paper_2606_23348_amd/csrc/features.hip",
-                  "paper_2606_23348_amd/csrc/device.hpp", "paper_2606_23348_amd/csrc/internal.hpp"]
+                  "paper_2606_23348_amd/csrc/board.hpp", "paper_2606_23348_amd/csrc/device.hpp",
+                  "paper_2606_23348_amd/csrc/internal.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 EXTRAS = ("sustained", "step_alone", "features", "copy", "c1", "c3", "rollout", "served", "pool", "served_mix")
 
@@ -261,7 +262,7 @@ def run_rollout(gen, torch, n_envs: int = 512, n_steps: int = 512) -> dict:
     torch.cuda.empty_cache()
     return {"workload": f"rollout 1v1 {H}x{W} official rules, {n_envs} envs x {n_steps} steps "
                         "(features + tokens + random actor + step)",
-            "ms_per_rollout": s_ * 1e3, "frames_per_s": n_envs * n_steps / s_, "launches": 2 * n_steps + 1}
+            "ms_per_rollout": s_ * 1e3, "frames_per_s": n_envs * n_steps / s_, "launches": 1}
 
 
 def pool_rw_per_frame(specs) -> tuple:

@@ -268,8 +268,8 @@ int gen_features(const gen_state *st, void *d_mem, uint64_t mem_bytes, float *d_
  *   actor draws, step index step0+t -> d_actions [t][E][P]
  *   one step                        -> d_rewards [t][E][P], d_dones [t][E]
  * exactly as gen_features, gen_sample_actions and gen_step called in that
- * order (no 8-channel observation is written).  2 launches per step on
- * `stream` (capture the stream into a HIP graph to replay whole rollouts).
+ * order (no 8-channel observation is written).  One launch on `stream` for
+ * the whole rollout (may be captured into a HIP graph).
  * The batch and d_mem advance by n_steps steps. */
 int gen_rollout(const gen_state *st, void *d_mem, uint64_t mem_bytes, int32_t n_steps, uint64_t actor_seed,
                 uint64_t step0, float *d_feat, float *d_tokens, int32_t *d_actions, int32_t *d_rewards, uint8_t *d_dones,

@@ -534,47 +534,28 @@ int gen_rollout(const gen_state *st, void *d_mem, uint64_t mem_bytes, int32_t n_
     hipError_t e = gen::feature_tables_ready();
     if (e != hipSuccess) return hip_fail(e, "feature table upload");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const size_t E = (size_t)st->n_envs, P = (size_t)st->n_players, HW = (size_t)st->H * st->W;
-    const size_t f_stride = E * P * GEN_FEAT_CHANNELS * HW, t_stride = E * P * 2 * GEN_TOKEN_WINDOW;
-    const gen::EnvArgs base = env_args(*st);
-
-    gen::SampleArgs sa{};
-    sa.g = base.g;
-    sa.env_base = st->env_base;
-    sa.actor_seed = actor_seed;
-    sa.step_idx = step0;
-    sa.sc = base.sc;
-    sa.owner = base.owner;
-    sa.type = base.type;
-    sa.army = base.army;
-    sa.actions = d_actions;
-    e = gen::launch_sample(sa, st->n_envs, s);
-    if (e != hipSuccess) return hip_fail(e, "rollout sample launch");
-    for (int32_t t = 0; t < n_steps; ++t) {
-        gen::FeatArgs fa{};
-        fa.g = base.g;
-        fa.blk = fb;
-        fa.sc = base.sc;
-        fa.owner = base.owner;
-        fa.type = base.type;
-        fa.army = base.army;
-        fa.mem = static_cast<uint8_t *>(d_mem);
-        fa.feat = d_feat + (size_t)t * f_stride;
-        fa.tokens = d_tokens ? d_tokens + (size_t)t * t_stride : nullptr;
-        e = gen::launch_features(fa, st->n_envs, s);
-        if (e != hipSuccess) return hip_fail(e, "rollout features launch");
-        gen::EnvArgs ea = base;
-        ea.actions = d_actions + (size_t)t * E * P;
-        ea.rewards = d_rewards + (size_t)t * E * P;
-        ea.dones = d_dones + (size_t)t * E;
-        if (t + 1 < n_steps) {           // the next step's actions, sampled in the same launch
-            ea.next_actions = d_actions + (size_t)(t + 1) * E * P;
-            ea.actor_seed = actor_seed;
-            ea.step_idx = step0 + (uint64_t)t + 1;
-        }
-        e = gen::launch_step(ea, st->n_envs, s);
-        if (e != hipSuccess) return hip_fail(e, "rollout step launch");
-    }
+    const gen::EnvArgs ea = env_args(*st);
+    gen::RolloutArgs a{};
+    a.g = ea.g;
+    a.blk = fb;
+    a.prm = ea.prm;
+    a.seed = ea.seed;
+    a.env_base = ea.env_base;
+    a.actor_seed = actor_seed;
+    a.step0 = step0;
+    a.n_steps = n_steps;
+    a.sc = ea.sc;
+    a.owner = ea.owner;
+    a.type = ea.type;
+    a.army = ea.army;
+    a.mem = static_cast<uint8_t *>(d_mem);
+    a.feat = d_feat;
+    a.tokens = d_tokens;
+    a.actions = d_actions;
+    a.rewards = d_rewards;
+    a.dones = d_dones;
+    e = gen::launch_rollout(a, st->n_envs, s);
+    if (e != hipSuccess) return hip_fail(e, "rollout launch");
     return ok();
 }
 

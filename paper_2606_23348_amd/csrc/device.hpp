@@ -121,7 +121,18 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+// GEN_LANE_PER_USE (kernels that loop over turns or channels): every use
+// derives its lane index anew; what depends on it is then not hoisted out of
+// the loops, where it held up to 50 vector registers (the feature planes 113
+// -> 62, 4 -> 8 waves per SIMD).
+__device__ __forceinline__ int lane_id()
+{
+    int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+#ifdef GEN_LANE_PER_USE
+    asm volatile("" : "+v"(l));
+#endif
+    return l;
+}
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
@@ -339,6 +350,7 @@ __device__ __forceinline__ ColMasks col_masks(int w, const Geom &g)
 // Only for whole, sector-aligned runs: where two stores share a 32-byte
 // sector (unaligned observation planes) plain stores are faster.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void st_nt(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }

@@ -1,49 +1,34 @@
 // features.hip -- the paper's full feature tensor (Appendix A, table of
 // observation channels; reading R17 of this library): 38 float32 maps per
-// player and env, computed by one workgroup of 2, 4 or 8 wave64s per env
-// from the env's state and a per-env memory in HBM (persistent masks, the
-// last enemy sighting per cell, a ring of the last 8 frames).  Small batches
-// (a training rollout's 512 envs) cannot fill the GPU with one wave per env,
-// so their cells are spread over more waves.
+// player and env, and whole rollouts that record them, by one workgroup per
+// env.
 //
-// Memory traffic dominates (the output alone is 152 bytes per cell and
-// player), so the kernel keeps every store coalesced: lane i of a round
-// handles cell 64r + i, and each of the 38 channel stores of a player is one
-// contiguous 256-byte wave store, nontemporal.  The state sits in LDS only
-// for the ballots and the team-vision dilation.  A cell's 7 earlier frames
-// are loaded from the ring before its 24 instantaneous channels are written,
-// so their latency hides behind those stores; the delta stacks then walk the
-// frames for all players with two running values per player.
+// The output alone is 152 bytes per cell and player, so the kernels are
+// built around its stores.  The env's state and its memory in HBM (persistent
+// masks, the last enemy sighting per cell, a ring of the last 8 frames) are
+// read once into LDS with 16-byte loads, the memory is updated there, and
+// then each wave writes whole planes: one (player, channel) at a time, so
+// the channel is wave-uniform, four consecutive cells per lane, 16-byte
+// nontemporal stores in runs on 128-byte boundaries whatever the board's
+// size, the waves of a workgroup side by side.  Before, a lane per cell wrote
+// all channels with 4-byte stores; where planes are no multiple of 128 bytes
+// every line then was written in parts.  Features and step, us: FFA-8 25x25,
+// 1,024 envs, 347 -> 206 (24x24 178 -> 167); 1v1 25x25, 8,192 envs, 665 ->
+// 445; 24x24, 460 -> 385; 10x10, 163 -> 113; 24x24 with tokens, 65,536 envs,
+// 3,400 -> 3,100, where constant planes take 2,600: the stores bound it.
+// Measured and not kept: runs of 2 to 4 planes per wave with the values at
+// their seams carried over (10 to 25% slower: the waves write further apart).
+#define GEN_LANE_PER_USE        // see lane_id()
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
+#include "board.hpp"
+#include "device.hpp"
 #include "internal.hpp"
 
 namespace gen {
-
-namespace {
-
-constexpr int kFeatC = 38;
-constexpr int kHist = 7;
-
-enum : uint32_t { B_SEEN = 1, B_ENEMY = 2, B_GENERAL = 4, B_CASTLE = 8, B_MOUNTAIN = 16 };
-
-// Owned by a player outside p's team (team = p, and p ^ 2 in 2v2).
-__device__ __forceinline__ bool enemy_of(int owner, int p, int mode)
-{
-    return owner >= 0 && owner != p && !(mode == MODE_2V2 && owner == (p ^ 2));
-}
-
-// Every per-env access goes through a raw buffer descriptor of the env's own
-// block (base in scalar registers, bounds = the block), so a channel or
-// memory-section offset is a scalar operand rather than a 64-bit address
-// per lane, and an access past the block is dropped by the hardware.
-constexpr int kNT = kAuxNT;                // cache policy of the stores: nontemporal
-
-__device__ __forceinline__ Rsrc rsrc(void *base, uint32_t bytes) { return buffer_rsrc(base, bytes); }
-
-}  // namespace
 
 // log(1 + dt) / 5 (channel 21) for dt in [0, kAgeTable): filled once per
 // device by host code from the host C library's double log1p, divided by 5
@@ -53,305 +38,821 @@ __device__ float g_age_table[kAgeTable];
 
 namespace {
 
-__device__ __forceinline__ float age_of(int32_t dt)
+constexpr int kFeatC = 38;
+constexpr int kHist = 7;
+constexpr int kEdge = 0;          // cache policy of the part stores at a plane's ends: plain, so the cache merges them
+constexpr uint32_t kOnes = 0x01010101u;          // one per cell byte
+constexpr int kFeatWaves = 8, kFeatMostWaves = 16;
+
+// Bits of a player's byte per cell.  The first five are the memory (channels
+// 4 to 8); the others only stand in LDS, for the turn's planes: visible now;
+// channel 9 where visible, channel 13 in the fog; visible and neutral.
+enum : int { B_SEEN = 0, B_ENEMY, B_GENERAL, B_CASTLE, B_MOUNTAIN, B_NOW, B_PLACE, B_NEUTRAL };
+constexpr uint32_t kMemoryBits = 0x1F1F1F1Fu;
+
+// Barrier of the workgroup that orders LDS only: a full __syncthreads would
+// also wait for the wave's outstanding stores to HBM, which no other wave
+// reads.
+__device__ __forceinline__ void lds_barrier()
 {
-    if ((uint32_t)dt < (uint32_t)kAgeTable) return g_age_table[dt];
-    return (float)(log1p((double)dt) / 5.0);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// ---------------------------------------------------------------- LDS of one env
+// `mem` mirrors the env's memory block from its `bits` section to the end of
+// the frame ring (FeatBlock: bits | last | lturn | fowner | fvis | farmy), so
+// block and mirror are copied as one run.  The frame of turn t sits in ring
+// slot t mod 8.  The planes read a frame as its armies and two masks per
+// cell: own (bit p: owned by player p) and foe (bit p: seen by p on an
+// enemy's cell), both 0 in a slot that holds no frame of the last 8 turns.
+struct FeatLds {
+    uint8_t *mem;            // 9 P S + 48 S bytes
+    uint8_t *bits;           // [P][S]
+    int32_t *last, *lturn;   // [P][S]
+    int8_t *fowner;          // [8][S]
+    uint8_t *fvis;           // [8][S]
+    int32_t *farmy;          // [8][S]
+    uint8_t *own, *foe;      // [8][S] masks (k_features: in the place of fowner and fvis)
+    int8_t *owner;           // [S] the board of this turn
+    uint8_t *type;           // [S]
+    int32_t *army;           // [S] (k_features: the ring slot of this turn)
+    uint64_t *obm, *vis;     // [P][16]
+    unsigned long long *armt;    // [8] army totals
+    int32_t *land;           // [8]
+    float *flat;             // [8][6] channels 14 to 19 by player
+    float *cx, *cy;          // [32] channels 22 and 23 by column, row
+};
+
+__host__ __device__ inline uint32_t feat_lds_bytes(int S, int P)
+{
+    return (uint32_t)(16 + 9 * P * S + 48 * S + 2 * S + 2 * P * 128 + 64 + 32 + 192 + 256);
+}
+
+__device__ __forceinline__ FeatLds feat_carve(uint8_t *smem, int S, int P)
+{
+    FeatLds F;
+    F.mem = smem + 16;                                 // an unaligned quad at a row's start stays inside
+    F.bits = F.mem;
+    F.last = reinterpret_cast<int32_t *>(F.mem + P * S);
+    F.lturn = F.last + P * S;
+    F.fowner = reinterpret_cast<int8_t *>(F.lturn + P * S);
+    F.fvis = reinterpret_cast<uint8_t *>(F.fowner + 8 * S);
+    F.farmy = reinterpret_cast<int32_t *>(F.fvis + 8 * S);
+    F.own = reinterpret_cast<uint8_t *>(F.fowner);
+    F.foe = F.fvis;
+    F.army = F.farmy;
+    F.owner = reinterpret_cast<int8_t *>(F.farmy + 8 * S);
+    F.type = reinterpret_cast<uint8_t *>(F.owner + S);
+    F.obm = reinterpret_cast<uint64_t *>(F.type + S);
+    F.vis = F.obm + P * 16;
+    F.armt = reinterpret_cast<unsigned long long *>(F.vis + P * 16);
+    F.land = reinterpret_cast<int32_t *>(F.armt + 8);
+    F.flat = reinterpret_cast<float *>(F.land + 8);
+    F.cx = F.flat + 48;
+    F.cy = F.cx + 32;
+    return F;
+}
+
+// The workgroup's copy of n 16-byte chunks, four loads in flight per thread.
+__device__ __forceinline__ void copy16(void *dst, const void *src, int n, int tid, int nt)
+{
+    const u32x4 *sp = static_cast<const u32x4 *>(src);
+    u32x4 *dp = static_cast<u32x4 *>(dst);
+    for (int i = tid; i < n; i += 4 * nt) {
+        const int i1 = i + nt, i2 = i1 + nt, i3 = i2 + nt;
+        const u32x4 v0 = sp[i], v1 = sp[min(i1, n - 1)], v2 = sp[min(i2, n - 1)], v3 = sp[min(i3, n - 1)];
+        dp[i] = v0;
+        if (i1 < n) dp[i1] = v1;
+        if (i2 < n) dp[i2] = v2;
+        if (i3 < n) dp[i3] = v3;
+    }
+}
+
+// ---------------------------------------------------------------- one turn's frame
+struct FrameCtx {
+    Geom g;
+    int t = 0, slot = 0;     // turn, its ring slot
+    bool fresh = true;       // the block holds another episode (or nothing): an empty memory
+};
+
+// Bit j: ring slot j holds the frame of one of the 7 turns before t
+// (stamp[j]: turn of the frame in slot j, -1 none).
+__device__ __forceinline__ uint32_t slots_held(const int32_t (&stamp)[8], int t)
+{
+    uint32_t h = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int32_t d = t - stamp[j];
+        if (stamp[j] >= 0 && (stamp[j] & 7) == j && d >= 1 && d <= kHist) h |= 1u << j;
+    }
+    return h;
+}
+
+// The two masks of a quad (see FeatLds) from its owner and visibility bytes.
+// An owner byte is a player (0..7) or 0xFF; the shift takes its low 5 bits.
+__device__ __forceinline__ uint32_t own_mask(uint32_t o4)
+{
+    return ((1u << (o4 & 31u)) & 0xFFu) | (((1u << ((o4 >> 8) & 31u)) & 0xFFu) << 8) |
+           (((1u << ((o4 >> 16) & 31u)) & 0xFFu) << 16) | ((1u << ((o4 >> 24) & 31u)) << 24);
+}
+
+__device__ __forceinline__ uint32_t foe_mask(uint32_t o4, uint32_t own, uint32_t vis, int mode)
+{
+    const uint32_t owned = (~(o4 >> 7) & kOnes) * 0xFFu;
+    const uint32_t team = mode == MODE_2V2 ? own | ((own << 2) & 0x0C0C0C0Cu) | ((own >> 2) & 0x03030303u) : own;
+    return vis & owned & ~team;
+}
+
+// The masks of the ring's earlier frames (0 for a slot that holds none).
+__device__ __forceinline__ void ring_masks(const FeatLds &F, const FrameCtx &f, uint32_t held, int tid, int nt)
+{
+    const int nq = f.g.S >> 2;
+    const uint32_t magic = ((1u << 20) + (uint32_t)nq - 1) / (uint32_t)nq;
+    for (int n = tid; n < 8 * nq; n += nt) {
+        const int j = (int)(((uint32_t)n * magic) >> 20);
+        const uint32_t o4 = reinterpret_cast<const uint32_t *>(F.fowner)[n], v4 = reinterpret_cast<const uint32_t *>(F.fvis)[n];
+        const bool have = (held >> j) & 1u;
+        const uint32_t own = have ? own_mask(o4) : 0u;
+        const uint32_t foe = have ? foe_mask(o4, own, v4, f.g.mode) : 0u;
+        reinterpret_cast<uint32_t *>(F.own)[n] = own;
+        reinterpret_cast<uint32_t *>(F.foe)[n] = foe;
+    }
+}
+
+// Owned-cell bitmaps and the players' land and army totals, the 64-cell
+// words shared out over the waves (armt and land zeroed before).  One LDS
+// addition per owned cell: 64 of them to few addresses cost less than a wave
+// sum per player.
+__device__ __forceinline__ void frame_totals(const FeatLds &F, const Geom &g, int wv, int nwv)
+{
+    const int lane = lane_id();
+    for (int w = wv; w < g.NW; w += nwv) {
+        const int c = w * 64 + lane;
+        const int o = c < g.HW ? (int)F.owner[c] : -1;
+        uint64_t mine = 0ull;                          // word w of player `lane`
+        for (int p = 0; p < g.P; ++p) {
+            const uint64_t m = ballot(o == readfirst(p));
+            if (lane == p) mine = m;
+        }
+        if (lane < g.P) {
+            F.obm[lane * 16 + w] = mine;
+            atomicAdd(&F.land[lane], __popcll(mine));
+        }
+        if (o >= 0) atomicAdd(&F.armt[o], (unsigned long long)F.army[c]);
+    }
+}
+
+// Memory update of a (player, quad of cells) per thread and that player's
+// masks of this turn; the row after the last player puts the quad's frame
+// into its ring slot.  MIRROR: the memory stays in LDS (the caller writes it
+// back later, so the raw frame is kept beside its masks), else it goes to
+// HBM at once.
+template <bool MIRROR>
+__device__ __forceinline__ void frame_update(const FeatLds &F, const FrameCtx &f, const Rsrc &rm, const FeatBlock &fb,
+                                             int tid, int nt)
+{
+    const Geom &g = f.g;
+    const int nq = g.S >> 2;
+    const uint32_t magic = ((1u << 20) + (uint32_t)nq - 1) / (uint32_t)nq;    // n / nq, exact for n < 9 * 256
+    for (int n = tid; n < nq * (g.P + 1); n += nt) {
+        const int p = (int)(((uint32_t)n * magic) >> 20), q = n - p * nq;
+        const int w = q >> 4, sh = (q & 15) * 4;
+        const uint32_t o4 = reinterpret_cast<const uint32_t *>(F.owner)[q];
+        const int4 a = reinterpret_cast<const int4 *>(F.army)[q];
+        if (p == g.P) {
+            uint32_t vb = 0;
+            for (int k = 0; k < g.P; ++k) vb |= spread4((uint32_t)(F.vis[k * 16 + w] >> sh) & 0xFu) << k;
+            const uint32_t own = own_mask(o4);
+            const int at = f.slot * nq + q;
+            if (MIRROR) {
+                reinterpret_cast<uint32_t *>(F.fowner)[at] = o4;
+                reinterpret_cast<uint32_t *>(F.fvis)[at] = vb;
+            } else {
+                const u32x4 x = {(uint32_t)a.x, (uint32_t)a.y, (uint32_t)a.z, (uint32_t)a.w};
+                __builtin_amdgcn_raw_buffer_store_b32(o4, rm, 4 * q, (int)fb.fowner + f.slot * g.S, kAuxNT);
+                __builtin_amdgcn_raw_buffer_store_b32(vb, rm, 4 * q, (int)fb.fvis + f.slot * g.S, kAuxNT);
+                __builtin_amdgcn_raw_buffer_store_b128(x, rm, 16 * q, (int)fb.farmy + 4 * f.slot * g.S, kAuxNT);
+            }
+            reinterpret_cast<uint32_t *>(F.own)[at] = own;
+            reinterpret_cast<uint32_t *>(F.foe)[at] = foe_mask(o4, own, vb, g.mode);
+            reinterpret_cast<int4 *>(F.farmy)[at] = a;
+            continue;
+        }
+        const uint32_t t4 = reinterpret_cast<const uint32_t *>(F.type)[q];
+        const uint32_t v = spread4((uint32_t)(F.vis[p * 16 + w] >> sh) & 0xFu);
+        const uint32_t mate = g.mode == MODE_2V2 ? (uint32_t)(p ^ 2) : (uint32_t)p;
+        const uint32_t none = (o4 >> 7) & kOnes, mine = bytes_eq(o4, (uint32_t)p);
+        const uint32_t ve = v & ~none & ~mine & ~bytes_eq(o4, mate);
+        const uint32_t mtn = t4 & ~(t4 >> 1), cas = (t4 >> 1) & ~t4, gnl = t4 & (t4 >> 1);
+        uint32_t *pb = reinterpret_cast<uint32_t *>(F.bits + p * g.S) + q;
+        int4 *pl = reinterpret_cast<int4 *>(F.last + p * g.S) + q, *pt = reinterpret_cast<int4 *>(F.lturn + p * g.S) + q;
+        uint32_t bits = f.fresh ? 0u : *pb & kMemoryBits;
+        int4 last = f.fresh ? make_int4(0, 0, 0, 0) : *pl, lt = f.fresh ? make_int4(0, 0, 0, 0) : *pt;
+        bits |= (v << B_SEEN) | (ve << B_ENEMY) | ((v & gnl) << B_GENERAL) | ((v & cas) << B_CASTLE) | ((v & mtn) << B_MOUNTAIN);
+        if (v & 0x00000001u) last.x = (ve & 0x00000001u) ? a.x : 0;
+        if (v & 0x00000100u) last.y = (ve & 0x00000100u) ? a.y : 0;
+        if (v & 0x00010000u) last.z = (ve & 0x00010000u) ? a.z : 0;
+        if (v & 0x01000000u) last.w = (ve & 0x01000000u) ? a.w : 0;
+        if (ve & 0x00000001u) lt.x = f.t;
+        if (ve & 0x00000100u) lt.y = f.t;
+        if (ve & 0x00010000u) lt.z = f.t;
+        if (ve & 0x01000000u) lt.w = f.t;
+        const uint32_t fog = v ^ kOnes;
+        *pb = bits | (v << B_NOW) | ((v & none) << B_NEUTRAL) |
+              (((v & none & ~mtn) | (fog & (mtn | cas | (bits >> B_GENERAL)))) << B_PLACE);
+        *pl = last;
+        *pt = lt;
+        if (!MIRROR) {
+            const u32x4 xl = {(uint32_t)last.x, (uint32_t)last.y, (uint32_t)last.z, (uint32_t)last.w};
+            const u32x4 xt = {(uint32_t)lt.x, (uint32_t)lt.y, (uint32_t)lt.z, (uint32_t)lt.w};
+            __builtin_amdgcn_raw_buffer_store_b32(bits, rm, 4 * q, (int)fb.bits + p * g.S, kAuxNT);
+            __builtin_amdgcn_raw_buffer_store_b128(xl, rm, 16 * q, (int)fb.last + 4 * p * g.S, kAuxNT);
+            __builtin_amdgcn_raw_buffer_store_b128(xt, rm, 16 * q, (int)fb.lturn + 4 * p * g.S, kAuxNT);
+        }
+    }
+}
+
+// Four cells' bytes and int32 values in LDS, from any cell (ANY) or a multiple of 4.
+template <bool ANY>
+__device__ __forceinline__ uint32_t ld4(const void *p)
+{
+    if (!ANY) return *static_cast<const uint32_t *>(p);
+    uint32_t v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+
+template <bool ANY>
+__device__ __forceinline__ int4 ld16(const int32_t *p)
+{
+    if (!ANY) return *reinterpret_cast<const int4 *>(p);
+    return make_int4(p[0], p[1], p[2], p[3]);
+}
+
+// v where bit `at` of m is set, else 0.
+__device__ __forceinline__ int keep(int v, uint32_t m, int at) { return v & __builtin_amdgcn_sbfe((int)m, at, 1); }
+
+__device__ __forceinline__ int4 keep4(int4 a, uint32_t m, int bit)
+{
+    return make_int4(keep(a.x, m, bit), keep(a.y, m, bit + 8), keep(a.z, m, bit + 16), keep(a.w, m, bit + 24));
+}
+
+__device__ __forceinline__ float4 bytes_to_f(uint32_t m)
+{
+    return make_float4((float)(m & 0xFFu), (float)((m >> 8) & 0xFFu), (float)((m >> 16) & 0xFFu), (float)(m >> 24));
+}
+
+// Channel ch (wave-uniform) of player p at the quads of cells c[0], c[1], ...
+// (any cell with ANY, else multiples of 4): the channel is decided once for all R quads of a lane,
+// whose LDS reads are then in flight together.
+template <bool ANY, int R>
+__device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int p, int ch, const int (&c)[R], float4 (&x)[R])
+{
+    const Geom &g = f.g;
+    const int S = g.S;
+    auto each = [&](auto &&value) {
+#pragma unroll
+        for (int k = 0; k < R; ++k) x[k] = value(c[k]);
+    };
+    if (ch >= 24) {
+        // army of the frame of turn t - k minus that of t - k - 1 on the
+        // player's (resp. visible enemies') cells; an absent frame is empty
+        const int k = ch - (ch >= 24 + kHist ? 24 + kHist : 24);
+        const uint8_t *mask = ch >= 24 + kHist ? F.foe : F.own;
+        const int o0 = ((f.t - k) & 7) * S, o1 = ((f.t - k - 1) & 7) * S;
+        each([&](int q) {
+            const int4 u = keep4(ld16<ANY>(F.farmy + o0 + q), ld4<ANY>(mask + o0 + q), p), v = keep4(ld16<ANY>(F.farmy + o1 + q), ld4<ANY>(mask + o1 + q), p);
+            return make_float4((float)(u.x - v.x), (float)(u.y - v.y), (float)(u.z - v.z), (float)(u.w - v.w));
+        });
+        return;
+    }
+    const uint8_t *bits = F.bits + p * S;
+    const int now = f.slot * S;
+    switch (ch) {
+    case 0: case 1: case 2: case 3: {
+        const uint8_t *mask = ch == 1 ? F.own + now : ch == 2 ? F.foe + now : bits;
+        const int bit = ch == 0 ? (int)B_NOW : ch == 3 ? (int)B_NEUTRAL : p;
+        each([&](int q) {
+            const int4 v = keep4(ld16<ANY>(F.farmy + now + q), ld4<ANY>(mask + q), bit);
+            return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
+        });
+        break;
+    }
+    case 4: case 5: case 6: case 7: case 8:
+        each([&](int q) { return bytes_to_f((ld4<ANY>(bits + q) >> (ch - 4)) & kOnes); });
+        break;
+    case 10: case 11: {
+        const uint8_t *mask = ch == 10 ? F.own + now : F.foe + now;
+        each([&](int q) { return bytes_to_f((ld4<ANY>(mask + q) >> p) & kOnes); });
+        break;
+    }
+    case 9: case 12: case 13: {
+        const uint32_t in = ch == 9 ? 0u : kOnes, all = ch == 12 ? kOnes : 0u;     // not visible; every such cell
+        each([&](int q) {
+            const uint32_t b = ld4<ANY>(bits + q);
+            return bytes_to_f(((b >> B_NOW) ^ in) & ((b >> B_PLACE) | all) & kOnes);
+        });
+        break;
+    }
+    case 14: case 15: case 16: case 17: case 18: case 19: {
+        const float v = F.flat[p * 6 + ch - 14];
+        each([&](int) { return make_float4(v, v, v, v); });
+        break;
+    }
+    case 20:
+        each([&](int q) {
+            const int4 v = ld16<ANY>(F.last + p * S + q);
+            return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
+        });
+        break;
+    case 21: {
+        // age of the sightings before, not visible now; gaps beyond the
+        // table are computed in a loop of their own (one copy of log1p)
+        bool far = false;
+        each([&](int q) {
+            const uint32_t b = ld4<ANY>(bits + q), m = ~(b >> B_NOW) & (b >> B_ENEMY);
+            const int4 lt = ld16<ANY>(F.lturn + p * S + q);
+            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            auto age = [&](uint32_t bit, int32_t then, float &to) {
+                if (!(m & bit)) return;
+                const uint32_t dt = (uint32_t)(f.t - then);
+                to = g_age_table[min(dt, (uint32_t)kAgeTable - 1u)];
+                far = far || dt >= (uint32_t)kAgeTable;
+            };
+            age(0x00000001u, lt.x, v.x);
+            age(0x00000100u, lt.y, v.y);
+            age(0x00010000u, lt.z, v.z);
+            age(0x01000000u, lt.w, v.w);
+            return v;
+        });
+        // wait for the table here: left to the store below, which every
+        // channel shares, the wait would hold each plane's store until all
+        // stores before it have reached memory (they count together)
+#pragma unroll
+        for (int k = 0; k < R; ++k) asm volatile("" : "+v"(x[k].x), "+v"(x[k].y), "+v"(x[k].z), "+v"(x[k].w));
+        if (ballot(far) != 0ull) {
+#pragma nounroll
+            for (int n = 0; n < 4 * R; ++n) {
+                int q = 0;
+#pragma unroll
+                for (int k = 0; k < R; ++k) q = n >> 2 == k ? max(c[k] + (n & 3), 0) : q;
+                const uint32_t b = bits[q];
+                const uint32_t dt = (uint32_t)(f.t - F.lturn[p * S + q]);
+                if (((b >> B_NOW) & 1u) || !((b >> B_ENEMY) & 1u) || dt < (uint32_t)kAgeTable) continue;
+                const float v = (float)(log1p((double)(int32_t)dt) / 5.0);
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    if (n == 4 * k) x[k].x = v;
+                    if (n == 4 * k + 1) x[k].y = v;
+                    if (n == 4 * k + 2) x[k].z = v;
+                    if (n == 4 * k + 3) x[k].w = v;
+                }
+            }
+        }
+        break;
+    }
+    default: {
+        const float *v = ch == 22 ? F.cx : F.cy;
+        each([&](int q) {
+            int r[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int row = div_w(max(q + k, 0), g);
+                r[k] = (ch == 22 ? q + k - g.W * row : row) & 31;
+            }
+            return make_float4(v[r[0]], v[r[1]], v[r[2]], v[r[3]]);
+        });
+    }
+    }
+}
+
+// Shift a wave's run of quads (quad 64 k + lane in x[k]) up by r values: each
+// quad takes the last r values of the one before it, one DPP move each.
+template <int r, int R>
+__device__ __forceinline__ void shift_run(float4 (&x)[R])
+{
+#pragma unroll
+    for (int k = R - 1; k >= 0; --k) {
+        auto prev = [&](float v, float before) {
+            const int first = k > 0 ? readlane(__float_as_int(before), kWave - 1) : 0;
+            return __uint_as_float(wave_shr1(__float_as_uint(v), (uint32_t)first));
+        };
+        const float4 u = x[k], l = x[k > 0 ? k - 1 : 0];
+        const float w = prev(u.w, l.w);
+        if (r == 1) {
+            x[k] = make_float4(w, u.x, u.y, u.z);
+        } else {
+            const float z = prev(u.z, l.z);
+            x[k] = r == 2 ? make_float4(z, w, u.x, u.y) : make_float4(prev(u.y, l.y), z, w, u.x);
+        }
+    }
+}
+
+// Plane (p, ch) of one player (of 64 / G players, G lanes each: boards whose
+// planes leave most of a wave idle), by one wave, in 16-byte stores on
+// 16-byte boundaries, each round's run of 1 KB on a 128-byte one: lane i
+// stores the quad of cells from 4 i - sh on, sh the floats between that
+// boundary and the plane.  Where planes start inside 16 bytes (SHIFT) a lane
+// reads the quad at the multiple of 4 above that and the wave shifts (reading
+// LDS off its boundaries: 23x23 rollout 1,295 -> 1,400 us; small boards,
+// G < 64, do, their players' shifts differ), and the quads across a plane's
+// ends are written in part.  ro: the env's block from the 128-byte boundary
+// at or before its first float, d floats into it.
+// R: rounds of 64 quads that cover a plane (G < 64: one).
+template <bool SHIFT, int G, int R>
+__device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, int p0, int ch, const Rsrc &ro, int d)
+{
+    const Geom &g = f.g;
+    const int HW = g.HW, lane = lane_id(), gl = lane & (G - 1);
+    int p = G == kWave ? p0 : p0 + lane / G;
+    const bool real = G == kWave || p < g.P;
+    p = G == kWave ? p : min(p, g.P - 1);
+    const int fo = d + (p * kFeatC + ch) * HW;         // the plane's first float
+    const int sh = fo & (G == kWave ? 31 : 3);
+    const int base = 4 * (fo - sh);
+    const int vo = G == kWave ? 0 : base, so = G == kWave ? base : 0;
+    int c[R];
+    float4 x[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        c[k] = G == kWave ? min(max(4 * (kWave * k + gl) - (sh & ~3), 0), g.S - 4)
+                          : min(max(4 * gl - sh, SHIFT ? -3 : 0), SHIFT ? HW - 1 : HW - 4);
+    channel<SHIFT && G != kWave, R>(F, f, p, ch, c, x);
+    if (SHIFT && G == kWave) {
+        if ((sh & 3) == 1) shift_run<1>(x);
+        else if ((sh & 3) == 2) shift_run<2>(x);
+        else if ((sh & 3) == 3) shift_run<3>(x);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int c0 = 4 * (kWave * k + gl) - sh, at = vo + 16 * (kWave * k + gl);
+        const u32x4 v = {__float_as_uint(x[k].x), __float_as_uint(x[k].y), __float_as_uint(x[k].z), __float_as_uint(x[k].w)};
+        if (real && c0 >= 0 && c0 + 4 <= HW) __builtin_amdgcn_raw_buffer_store_b128(v, ro, at, so, kAuxNT);
+        if (!SHIFT) continue;
+        if (G == kWave) {                              // how much of an end's quad is the same for the wave
+            const int head = sh & 3, tail = (HW + sh) & 3;
+            if (k == 0 && head != 0) {
+                if (c0 < 0 && c0 > -4) {
+                    if (head == 1) __builtin_amdgcn_raw_buffer_store_b96(u32x3{v.y, v.z, v.w}, ro, at + 4, so, kEdge);
+                    else if (head == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.z, v.w}, ro, at + 8, so, kEdge);
+                    else __builtin_amdgcn_raw_buffer_store_b32(v.w, ro, at + 12, so, kEdge);
+                }
+            }
+            if (tail != 0 && k == (HW + sh) >> 8) {
+                if (c0 < HW && c0 + 4 > HW) {
+                    if (tail == 1) __builtin_amdgcn_raw_buffer_store_b32(v.x, ro, at, so, kEdge);
+                    else if (tail == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, ro, at, so, kEdge);
+                    else __builtin_amdgcn_raw_buffer_store_b96(u32x3{v.x, v.y, v.z}, ro, at, so, kEdge);
+                }
+            }
+        } else if (real && ((c0 < 0 && c0 > -4) || (c0 < HW && c0 + 4 > HW))) {
+            if (c0 >= 0) __builtin_amdgcn_raw_buffer_store_b32(v.x, ro, at, so, kEdge);
+            if (c0 + 1 >= 0 && c0 + 1 < HW) __builtin_amdgcn_raw_buffer_store_b32(v.y, ro, at + 4, so, kEdge);
+            if (c0 + 2 >= 0 && c0 + 2 < HW) __builtin_amdgcn_raw_buffer_store_b32(v.z, ro, at + 8, so, kEdge);
+            if (c0 + 3 < HW) __builtin_amdgcn_raw_buffer_store_b32(v.w, ro, at + 12, so, kEdge);
+        }
+    }
+}
+
+// The env's planes as tasks for one wave each, in the order of the tensor:
+// the waves of a workgroup then write next to each other.
+template <int G>
+__device__ __forceinline__ int plane_tasks(int P) { return (P + kWave / G - 1) / (kWave / G) * kFeatC; }
+
+template <bool SHIFT, int G, int R>
+__device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, int k, float *fe)
+{
+    const int d = (int)(((uintptr_t)fe >> 2) & 31);
+    const Rsrc ro = buffer_rsrc(fe - d, 4u * (uint32_t)(d + f.g.P * kFeatC * f.g.HW));
+    const int grp = k / kFeatC;
+    plane_out<SHIFT, G, R>(F, f, grp * (kWave / G), k - grp * kFeatC, ro, d);
+}
+
+// Token windows: 64 of the 512 turns of one player's two rows (the enemies'
+// army and land) per task.  The loads of a wave's first two tasks are issued
+// before the turn's memory update and their values stored after it, so the
+// ring's latency is hidden (as a last task of a few waves the windows cost
+// 1.1 ms of the 3.9 of 65,536 envs of 24x24).
+struct TokenLoad {
+    int32_t stamp, land;
+    u32x2 army;
+};
+
+__device__ __forceinline__ int token_tasks(int P) { return P * (kTokenWindow / kWave); }
+
+__device__ __forceinline__ TokenLoad token_load(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
+{
+    const int p = k >> 3, j = (k & 7) * kWave + lane_id();
+    const int sl = (f.t - (kTokenWindow - 1) + j) & (kTokenWindow - 1);
+    TokenLoad v;
+    v.stamp = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tstamp, 0);
+    v.army = __builtin_amdgcn_raw_buffer_load_b64(rm, 8 * sl, (int)fb.tarmy + 8 * p * kTokenWindow, 0);
+    v.land = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tland + 4 * p * kTokenWindow, 0);
+    return v;
+}
+
+__device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f, const TokenLoad &v, int k, float *te)
+{
+    const int p = k >> 3, j = (k & 7) * kWave + lane_id();
+    const int32_t tau = f.t - (kTokenWindow - 1) + j;
+    const Rsrc rt = buffer_rsrc(te + (size_t)p * 2 * kTokenWindow, 8u * kTokenWindow);
+    const bool now = j == kTokenWindow - 1;                  // this turn: channels 19 and 18
+    const bool have = !f.fresh && tau >= 0 && v.stamp == tau;
+    const float army = now ? F.flat[p * 6 + 5] : have ? (float)(int64_t)(((uint64_t)v.army.y << 32) | v.army.x) : 0.0f;
+    const float land = now ? F.flat[p * 6 + 4] : have ? (float)v.land : 0.0f;
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(army), rt, 4 * j, 0, kAuxNT);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(land), rt, 4 * j, 4 * kTokenWindow, kAuxNT);
+}
+
+// Channels 14 to 19 of each player, and this turn's entry of the scoreboard
+// ring (Section V-A: the two temporal tokens), by one wave; a fresh block's
+// ring is emptied.
+__device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm)
+{
+    const int lane = lane_id(), ts = f.t & (kTokenWindow - 1);
+    for (int j = lane; j < kTokenWindow; j += kWave)
+        if (f.fresh || j == ts)
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(j == ts ? f.t : -1), rm, 4 * j, (int)fb.tstamp, 0);
+    if (lane < f.g.P) {
+        int32_t ol = 0;
+        int64_t oa = 0;
+        for (int q = 0; q < f.g.P; ++q) {              // the enemies' totals
+            if (q == lane || (f.g.mode == MODE_2V2 && q == (lane ^ 2))) continue;
+            ol += F.land[q];
+            oa += (int64_t)F.armt[q];
+        }
+        float *to = F.flat + 6 * lane;
+        to[0] = (float)f.t;
+        to[1] = (float)((double)(f.t % 50) / 50.0);
+        to[2] = (float)F.land[lane];
+        to[3] = (float)(int64_t)F.armt[lane];
+        to[4] = (float)ol;
+        to[5] = (float)oa;
+        const int off = lane * kTokenWindow + ts;
+        const u32x2 v = {(uint32_t)(uint64_t)oa, (uint32_t)((uint64_t)oa >> 32)};
+        __builtin_amdgcn_raw_buffer_store_b64(v, rm, 8 * off, (int)fb.tarmy, 0);
+        __builtin_amdgcn_raw_buffer_store_b32((uint32_t)ol, rm, 4 * off, (int)fb.tland, 0);
+    }
 }
 
 }  // namespace
 
-// NT: the feature planes are whole 32-byte sectors (H*W a multiple of 8),
-// so their stores can be nontemporal; otherwise two stores share the sector
-// at each plane boundary and plain stores let the cache merge them.
-template <bool NT>
-__global__ __launch_bounds__(512) void k_features(FeatArgs a)
+template <bool SHIFT, int G, int R>
+__global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 {
-    constexpr int kOut = NT ? kNT : 0;        // cache policy of the feature and token stores
     extern __shared__ __align__(16) uint8_t smem[];
     const int e = (int)xcd_env(blockIdx.x, gridDim.x), lane = lane_id();   // see xcd_env
-    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;   // nt = 64 x (waves per env)
-    const bool wave0 = readfirst(tid >> 6) == 0;
-    const Geom g = a.g;
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    const int wv = readfirst(tid >> 6), nwv = nt >> 6;
     const FeatBlock fb = a.blk;
-    const int S = g.S, HW = g.HW, P = g.P;
-
-    // LDS: owner [S] | type [S] | army int32 [S] | obm [P][16] | vis [P][16] |
-    //      enemy army total [P] int64 | enemy land [P] int32 |
-    //      army total [P] int64 | land [P] int32
-    int8_t *Lo = reinterpret_cast<int8_t *>(smem);
-    uint8_t *Lt = smem + S;
-    int32_t *La = reinterpret_cast<int32_t *>(smem + 2 * S);
-    uint64_t *obm = reinterpret_cast<uint64_t *>(smem + 6 * S);
-    uint64_t *vis = obm + P * 16;
-    int64_t *opp_army_l = reinterpret_cast<int64_t *>(vis + P * 16);
-    int32_t *opp_land_l = reinterpret_cast<int32_t *>(opp_army_l + P);
-    int64_t *armt_l = reinterpret_cast<int64_t *>(smem + 6 * S + 2 * P * 16 * 8 + 16 * P);
-    int32_t *land_l = reinterpret_cast<int32_t *>(armt_l + P);
-
-    const EnvScalars s = a.sc[e];
-    {
-        const size_t cell0 = (size_t)e * S;
-        const uint4 *go = reinterpret_cast<const uint4 *>(a.owner + cell0);
-        const uint4 *gt = reinterpret_cast<const uint4 *>(a.type + cell0);
-        const uint4 *ga = reinterpret_cast<const uint4 *>(a.army + cell0);
-        const int n16 = S >> 4;
-        for (int i = tid; i < n16; i += nt) {
-            reinterpret_cast<uint4 *>(Lo)[i] = go[i];
-            reinterpret_cast<uint4 *>(Lt)[i] = gt[i];
-        }
-        for (int i = tid; i < 4 * n16; i += nt) reinterpret_cast<uint4 *>(La)[i] = ga[i];
-    }
-    // the memory header is read by every wave before the first barrier (the
-    // last barrier orders its rewrite after all of them)
+    FrameCtx f;
+    f.g = a.g;
+    const Geom &g = f.g;
+    const int S = g.S, P = g.P;
+    FeatLds F = feat_carve(smem, S, P);
     uint8_t *blk = a.mem + (size_t)e * fb.bytes;
+
+    const int n16 = S >> 4;
+    const size_t cell0 = (size_t)e * S;
+    const EnvScalars s = a.sc[e];
     uint32_t *hdr = reinterpret_cast<uint32_t *>(blk);
-    const int32_t t = s.turn;
-    const int slot = t & 7;
-    const bool fresh = readfirst((int)hdr[0]) != (int)kFeatMagic || (uint32_t)readfirst((int)hdr[1]) != s.episode;
+    f.t = s.turn;
+    f.slot = f.t & 7;
+    F.army = F.farmy + f.slot * S;
+    copy16(F.owner, a.owner + cell0, n16, tid, nt);
+    copy16(F.type, a.type + cell0, n16, tid, nt);
+    copy16(F.mem, blk + fb.bits, (9 * P + 16) * n16, tid, nt);
+    // this turn's slot of the armies is the state's
+    const u32x4 *fa = reinterpret_cast<const u32x4 *>(blk + fb.farmy), *sa = reinterpret_cast<const u32x4 *>(a.army + cell0);
+    u32x4 *la = reinterpret_cast<u32x4 *>(F.farmy);
+    const int na = 4 * n16, mine = f.slot * na;
+    for (int i = tid; i < na; i += nt) la[mine + i] = sa[i];
+    for (int i = tid; i < 8 * na; i += 2 * nt) {
+        const int j = min(i + nt, 8 * na - 1);
+        const u32x4 v = fa[i], w = fa[j];
+        if (i < mine || i >= mine + na) la[i] = v;
+        if (j < mine || j >= mine + na) la[j] = w;
+    }
+    f.fresh = readfirst((int)hdr[0]) != (int)kFeatMagic || (uint32_t)readfirst((int)hdr[1]) != s.episode;
     int32_t stamp[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) stamp[j] = fresh ? -1 : readfirst((int)hdr[2 + j]);
-    __syncthreads();
-
-    // owned-cell bitmaps, team vision, land and army totals (wave 0; the
-    // others wait at the barrier)
-    int land[kMaxP];
-    int64_t armt[kMaxP];
-#pragma unroll
-    for (int p = 0; p < kMaxP; ++p) { land[p] = 0; armt[p] = 0; }
-    if (wave0) {
-        for (int w = 0; w < g.NW; ++w) {
-            const int c = w * 64 + lane;
-            const int o = c < HW ? (int)Lo[c] : -1;
-            for (int p = 0; p < P; ++p) {
-                const uint64_t m = ballot(o == readfirst(p));
-                if (lane == 0) obm[p * 16 + w] = m;
-            }
-            if (o >= 0) {
-                const int32_t av = La[c];
-#pragma unroll
-                for (int p = 0; p < kMaxP; ++p)
-                    if (o == p) { land[p] += 1; armt[p] += av; }
-            }
-        }
-        wave_sync();
-        team_vision(obm, vis, g);
-#pragma unroll
-        for (int p = 0; p < kMaxP; ++p) {
-            if (p < P) {               // wave-uniform totals live in scalar registers
-                land[p] = readfirst((int)wave_sum_u32((uint32_t)land[p]));
-                const uint64_t at = (uint64_t)wave_sum_i64(armt[p]);
-                armt[p] = (int64_t)(((uint64_t)(uint32_t)readfirst((int)(at >> 32)) << 32) |
-                                    (uint32_t)readfirst((int)(uint32_t)at));
-            }
-        }
-        // the enemies' totals of each player, kept in LDS for the scoreboard ring
-        // (scalar registers are scarce across the cell loop), and the players'
-        // own totals for the other waves
-        if (lane < P) {
-            int32_t ol = 0;
-            int64_t oa = 0;
-#pragma unroll
-            for (int q = 0; q < kMaxP; ++q) {
-                if (q < P && q != lane && !(g.mode == MODE_2V2 && q == (lane ^ 2))) {
-                    ol += land[q];
-                    oa += armt[q];
-                }
-            }
-            opp_army_l[lane] = oa;
-            opp_land_l[lane] = ol;
-#pragma unroll
-            for (int q = 0; q < kMaxP; ++q)
-                if (q == lane) { armt_l[lane] = armt[q]; land_l[lane] = land[q]; }
-        }
+    for (int j = 0; j < 8; ++j) stamp[j] = f.fresh ? -1 : readfirst((int)hdr[2 + j]);
+    if (tid < 8) { F.armt[tid] = 0; F.land[tid] = 0; }
+    if (wv == nwv - 1 && lane < 32) {
+        F.cx[lane] = (float)((double)lane / (double)(g.W - 1));
+        F.cy[lane] = (float)((double)lane / (double)(g.H - 1));
     }
-    __syncthreads();
-    if (!wave0) {
-#pragma unroll
-        for (int p = 0; p < kMaxP; ++p) {
-            if (p < P) {
-                land[p] = readfirst(land_l[p]);
-                const uint64_t at = (uint64_t)armt_l[p];
-                armt[p] = (int64_t)(((uint64_t)(uint32_t)readfirst((int)(at >> 32)) << 32) |
-                                    (uint32_t)readfirst((int)(uint32_t)at));
-            }
-        }
-    }
-
-    // memory header: a block of another episode (or never used) starts empty
-    uint32_t hv = 0;                  // bit k: the frame of turn t - k is in the ring
-#pragma unroll
-    for (int k = 1; k <= kHist; ++k) {
-        const int32_t tau = t - k;
-        if (tau >= 0 && stamp[tau & 7] == tau) hv |= 1u << k;
-    }
-
-    const float ch15 = (float)((double)(t % 50) / 50.0);
-    float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * HW;
-
-    const Rsrc rm = rsrc(blk, fb.bytes);
-    const Rsrc rf = rsrc(fe, (uint32_t)(P * kFeatC * HW * 4));
-    for (int c = tid; c < HW; c += nt) {
-        const int o = Lo[c], ty = Lt[c];
-        const int32_t av = La[c];
-        const int w = c >> 6, b = c & 63;
-        uint32_t vb = 0;
-        for (int p = 0; p < P; ++p) vb |= (uint32_t)((vis[p * 16 + w] >> b) & 1ull) << p;
-
-        int hq[kHist];
-        uint32_t hqv[kHist];
-        int32_t hqa[kHist];
-#pragma unroll
-        for (int k = 0; k < kHist; ++k) {
-            const int sl = (t - k - 1) & 7;
-            const bool have = (hv >> (k + 1)) & 1u;
-            hq[k] = have ? (int)(int8_t)__builtin_amdgcn_raw_buffer_load_b8(rm, c, (int)fb.fowner + sl * S, 0) : -1;
-            hqv[k] = have ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rm, c, (int)fb.fvis + sl * S, 0) : 0u;
-            hqa[k] = have ? (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * c, (int)fb.farmy + 4 * sl * S, 0) : 0;
-        }
-        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)o, rm, c, (int)fb.fowner + slot * S, kNT);
-        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)vb, rm, c, (int)fb.fvis + slot * S, kNT);
-        __builtin_amdgcn_raw_buffer_store_b32((uint32_t)av, rm, 4 * c, (int)fb.farmy + 4 * slot * S, kNT);
-
-        const int row = div_w(c, g), col = c - row * g.W;
-        const float cx = (float)((double)col / (double)(g.W - 1));
-        const float cy = (float)((double)row / (double)(g.H - 1));
-
-        int32_t own_prev[kMaxP], en_prev[kMaxP];
-#pragma unroll
-        for (int p = 0; p < kMaxP; ++p) {
-            if (p >= P) break;
-            const bool v = (vb >> p) & 1u;
-            const bool en = enemy_of(o, p, g.mode);
-            uint32_t bits = fresh ? 0u : (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rm, c, (int)fb.bits + p * S, 0);
-            int32_t last = fresh ? 0 : (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * c, (int)fb.last + 4 * p * S, 0);
-            int32_t lturn = fresh ? 0 : (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * c, (int)fb.lturn + 4 * p * S, 0);
-            if (v) {
-                bits |= B_SEEN;
-                if (en) { bits |= B_ENEMY; lturn = t; }
-                if (ty == GENERAL) bits |= B_GENERAL;
-                if (ty == CASTLE) bits |= B_CASTLE;
-                if (ty == MOUNTAIN) bits |= B_MOUNTAIN;
-                last = en ? av : 0;
-            }
-            __builtin_amdgcn_raw_buffer_store_b8((uint8_t)bits, rm, c, (int)fb.bits + p * S, kNT);
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)last, rm, 4 * c, (int)fb.last + 4 * p * S, kNT);
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)lturn, rm, 4 * c, (int)fb.lturn + 4 * p * S, kNT);
-
-            int32_t opp_land = 0;
-            int64_t opp_army = 0;
-#pragma unroll
-            for (int q = 0; q < kMaxP; ++q) {
-                if (q < P && q != p && !(g.mode == MODE_2V2 && q == (p ^ 2))) {
-                    opp_land += land[q];
-                    opp_army += armt[q];
-                }
-            }
-            const int pb = p * kFeatC * HW * 4;
-            auto put = [&](int ch, float x) {
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rf, 4 * c, pb + ch * HW * 4, kOut);
-            };
-            put(0, (float)(v ? av : 0));
-            put(1, (float)(o == p ? av : 0));
-            put(2, (float)(v && en ? av : 0));
-            put(3, (float)(v && o < 0 ? av : 0));
-            put(4, (float)(bits & 1u));
-            put(5, (float)((bits >> 1) & 1u));
-            put(6, (float)((bits >> 2) & 1u));
-            put(7, (float)((bits >> 3) & 1u));
-            put(8, (float)((bits >> 4) & 1u));
-            put(9, (v && o < 0 && ty != MOUNTAIN) ? 1.0f : 0.0f);
-            put(10, o == p ? 1.0f : 0.0f);
-            put(11, (v && en) ? 1.0f : 0.0f);
-            put(12, v ? 0.0f : 1.0f);
-            put(13, (!v && (ty == MOUNTAIN || ty == CASTLE || (bits & B_GENERAL))) ? 1.0f : 0.0f);
-            put(14, (float)t);
-            put(15, ch15);
-            put(16, (float)land[p]);
-            put(17, (float)armt[p]);
-            put(18, (float)opp_land);
-            put(19, (float)opp_army);
-            put(20, (float)last);
-            put(21, (v || !(bits & B_ENEMY)) ? 0.0f : age_of(t - lturn));
-            put(22, cx);
-            put(23, cy);
-            own_prev[p] = o == p ? av : 0;
-            en_prev[p] = (v && en) ? av : 0;
-        }
-
-        // delta stacks: frame t-k-1 from the ring (absent: empty board)
-#pragma unroll
-        for (int k = 0; k < kHist; ++k) {
-            const int q = hq[k];
-            const uint32_t qv = hqv[k];
-            const int32_t qa = hqa[k];
-#pragma unroll
-            for (int p = 0; p < kMaxP; ++p) {
-                if (p >= P) break;
-                const int pb = p * kFeatC * HW * 4;
-                const int32_t own_k = q == p ? qa : 0;
-                const int32_t en_k = (((qv >> p) & 1u) && enemy_of(q, p, g.mode)) ? qa : 0;
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)(own_prev[p] - own_k)), rf, 4 * c,
-                                                      pb + (24 + k) * HW * 4, kOut);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)(en_prev[p] - en_k)), rf, 4 * c,
-                                                      pb + (24 + kHist + k) * HW * 4, kOut);
-                own_prev[p] = own_k;
-                en_prev[p] = en_k;
-            }
-        }
-    }
-
-    // scoreboard ring (Section V-A: the two temporal tokens): this turn's
-    // enemy totals per player, then the 512-turn windows if asked for
-    const int ts = t & (kTokenWindow - 1);
-    for (int j = tid; j < kTokenWindow; j += nt) {
-        if (fresh || j == ts)
-            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(j == ts ? t : -1), rm, 4 * j, (int)fb.tstamp, 0);
-    }
-    if (tid < P) {
-        const int64_t oa = opp_army_l[tid];
-        const int off = tid * kTokenWindow + ts;
-        const u32x2 oav = {(uint32_t)(uint64_t)oa, (uint32_t)((uint64_t)oa >> 32)};
-        __builtin_amdgcn_raw_buffer_store_b64(oav, rm, 8 * off, (int)fb.tarmy, 0);
-        __builtin_amdgcn_raw_buffer_store_b32((uint32_t)opp_land_l[tid], rm, 4 * off, (int)fb.tland, 0);
-    }
-    if (a.tokens != nullptr) {
-        const Rsrc rt = rsrc(a.tokens + (size_t)e * P * 2 * kTokenWindow, (uint32_t)(P * 2 * kTokenWindow * 4));
-        for (int j = tid; j < kTokenWindow; j += nt) {
-            const int32_t tau = t - (kTokenWindow - 1) + j;
-            const int sl = tau & (kTokenWindow - 1);
-            const bool now = j == kTokenWindow - 1;          // this turn: from registers
-            const bool have = !now && !fresh && tau >= 0 &&
-                              (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tstamp, 0) == tau;
-#pragma unroll
-            for (int p = 0; p < kMaxP; ++p) {
-                if (p >= P) break;
-                int64_t oa = 0;
-                int32_t ol = 0;
-                if (now) {
-                    oa = opp_army_l[p];
-                    ol = opp_land_l[p];
-                } else if (have) {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rm, 8 * (p * kTokenWindow + sl), (int)fb.tarmy, 0);
-                    oa = (int64_t)(((uint64_t)v.y << 32) | v.x);
-                    ol = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * (p * kTokenWindow + sl), (int)fb.tland, 0);
-                }
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)oa), rt, 4 * j,
-                                                      4 * (p * 2 * kTokenWindow), kOut);
-                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)ol), rt, 4 * j,
-                                                      4 * (p * 2 * kTokenWindow + kTokenWindow), kOut);
-            }
-        }
-    }
-
-    __syncthreads();
-    if (tid == 0) {
+    lds_barrier();
+    ring_masks(F, f, slots_held(stamp, f.t), tid, nt);
+    frame_totals(F, g, wv, nwv);
+    lds_barrier();
+    if (wv == 0) team_vision(F.obm, F.vis, g);
+    const Rsrc rm = buffer_rsrc(blk, fb.bytes);
+    if (wv == nwv - 1) scoreboard_out(F, f, fb, rm);
+    // every wave has read the header
+    if (wv == nwv - 1 && lane == 0) {
         hdr[0] = kFeatMagic;
         hdr[1] = s.episode;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) hdr[2 + j] = (uint32_t)(j == slot ? t : stamp[j]);
+        for (int j = 0; j < 8; ++j) hdr[2 + j] = (uint32_t)(j == f.slot ? f.t : stamp[j]);
     }
+    lds_barrier();
+    const bool tokens = a.tokens != nullptr;
+    const int n_tok = tokens ? token_tasks(P) : 0;
+    TokenLoad v0{}, v1{};
+    if (wv < n_tok) v0 = token_load(f, fb, rm, wv);
+    if (wv + nwv < n_tok) v1 = token_load(f, fb, rm, wv + nwv);
+    frame_update<false>(F, f, rm, fb, tid, nt);
+    lds_barrier();
+    if (tokens) {
+        float *te = a.tokens + (size_t)e * P * 2 * kTokenWindow;
+        if (wv < n_tok) token_store(F, f, v0, wv, te);
+        if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
+        for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
+    }
+    float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
+    for (int k = wv; k < plane_tasks<G>(P); k += nwv) plane_task<SHIFT, G, R>(F, f, k, fe);
+}
+
+// ---------------------------------------------------------------- rollouts
+// T turns of one env by one workgroup: features of the state, random actor,
+// step, as gen_features, gen_sample_actions and gen_step called in turn.
+// Envs are independent, so no launch boundary is needed between the turns:
+// the board, the feature memory and the frame ring stay in LDS, and per turn
+// only the outputs go to HBM (512 envs of 23x23 with tokens: 48.0 -> 19.5 us
+// a turn against two launches; 24x24 without: 35.0 -> 17.3 us, 17.2 with
+// constant planes, so it is bound by the stores).
+// Wave 0 plays the turn while the others write its planes; the planes are
+// handed out by a counter, so wave 0 joins when it is done.
+struct RollLds {
+    Lds L;                   // the live board
+    EnvScalars *s;           // its scalars after the last turn
+    int32_t *hdr;            // the memory block's header: magic, episode, stamp[8]
+    int32_t *act;            // [8] this turn's actions
+    int32_t *next;           // next plane to hand out
+};
+
+constexpr int kRollExtra = 8 * 56 + 32 + 48 + 32 + 16 + 2 * 96;
+
+__host__ __device__ inline uint32_t roll_lds_bytes(int S, int P) { return feat_lds_bytes(S, P) + (uint32_t)(20 * S + kRollExtra); }
+
+template <bool SHIFT, int G, int R>
+__global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int e = (int)xcd_env(blockIdx.x, gridDim.x), lane = lane_id();
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    const int wv = readfirst(tid >> 6), nwv = nt >> 6;
+    const FeatBlock fb = a.blk;
+    FrameCtx f;
+    f.g = a.g;
+    const Geom &g = f.g;
+    const int S = g.S, P = g.P, n16 = S >> 4, nq = S >> 2;
+    FeatLds F = feat_carve(smem, S, P);
+    RollLds rl;
+    {
+        uint8_t *x = smem + feat_lds_bytes(S, P);
+        F.own = x; x += 8 * S;
+        F.foe = x; x += 8 * S;
+        F.army = reinterpret_cast<int32_t *>(x); x += 4 * S;
+        rl.L.army = F.army;
+        rl.L.owner = F.owner;
+        rl.L.type = F.type;
+        rl.L.armyc = nullptr;
+        rl.L.obm = F.obm;
+        rl.L.vis = F.vis;
+        rl.L.gbm = reinterpret_cast<uint64_t *>(x); x += 8 * 56;
+        rl.s = reinterpret_cast<EnvScalars *>(x); x += 32;
+        rl.hdr = reinterpret_cast<int32_t *>(x); x += 48;
+        rl.act = reinterpret_cast<int32_t *>(x); x += 32;
+        rl.next = reinterpret_cast<int32_t *>(x); x += 16;
+    }
+    unsigned long long *const armt0 = reinterpret_cast<unsigned long long *>(rl.next + 4);   // totals, turn about
+    const size_t cell0 = (size_t)e * S;
+    uint8_t *blk = a.mem + (size_t)e * fb.bytes;
+    const Rsrc rm = buffer_rsrc(blk, fb.bytes);
+    copy16(rl.L.army, a.army + cell0, 4 * n16, tid, nt);
+    copy16(rl.L.owner, a.owner + cell0, n16, tid, nt);
+    copy16(rl.L.type, a.type + cell0, n16, tid, nt);
+    copy16(F.mem, blk + fb.bits, (9 * P + 48) * n16, tid, nt);
+    if (tid < 10) rl.hdr[tid] = reinterpret_cast<const int32_t *>(blk)[tid];
+    if (wv == 1 && lane < 8) reinterpret_cast<uint32_t *>(rl.s)[lane] = reinterpret_cast<const uint32_t *>(a.sc + e)[lane];
+    if (wv == 2 && lane < 24) reinterpret_cast<uint64_t *>(armt0)[lane] = 0ull;
+    if (wv == nwv - 1 && lane < 32) {
+        F.cx[lane] = (float)((double)lane / (double)(g.W - 1));
+        F.cy[lane] = (float)((double)lane / (double)(g.H - 1));
+    }
+    lds_barrier();
+    {
+        int32_t stamp[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) stamp[j] = readfirst(rl.hdr[2 + j]);
+        ring_masks(F, f, slots_held(stamp, readfirst(rl.s->turn)), tid, nt);
+    }
+
+    const uint64_t env_id = a.env_base + (uint64_t)e;
+    const int n_planes = plane_tasks<G>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
+    for (int step = 0; step < a.n_steps; ++step) {
+        // what follows from the geometry is computed anew each turn: kept
+        // over the loop it costs more scalar registers than there are
+        asm volatile("" : "+s"(f.g.S), "+s"(f.g.HW), "+s"(f.g.P), "+s"(f.g.W), "+s"(f.g.H), "+s"(f.g.NW));
+        // ---- this turn's frame: the live board into its ring slot
+        EnvScalars s;
+        {
+            uint32_t w[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = (uint32_t)readfirst((int)reinterpret_cast<const uint32_t *>(rl.s)[k]);
+            __builtin_memcpy(&s, w, 32);
+        }
+        f.t = s.turn;
+        f.slot = f.t & 7;
+        f.fresh = readfirst(rl.hdr[0]) != (int)kFeatMagic || (uint32_t)readfirst(rl.hdr[1]) != s.episode;
+        if (f.fresh) ring_masks(F, f, 0u, tid, nt);    // no earlier frames
+        F.armt = armt0 + 12 * (step & 1);
+        F.land = reinterpret_cast<int32_t *>(F.armt + 8);
+        frame_totals(F, g, wv, nwv);
+        for (int w = wv; w < g.NW; w += nwv) {
+            const int c = w * 64 + lane;
+            const uint64_t pm = ballot(c < g.HW && rl.L.type[min(c, S - 1)] != MOUNTAIN);
+            const uint64_t bm = ballot(c < g.HW && rl.L.army[min(c, S - 1)] > 1);
+            if (lane == 0) { rl.L.gbm[w] = pm; rl.L.gbm[16 + w] = bm; }
+        }
+        lds_barrier();
+        // ---- vision; the actor's draws; the scoreboard ring; the header
+        if (wv == 0) {
+            team_vision(F.obm, F.vis, g);
+        } else if (wv == 1) {
+            actor_wave(g, F.obm, rl.L.gbm, rl.L.gbm + 16, s.alive, a.actor_seed, a.step0 + (uint64_t)step, env_id, rl.act);
+            wave_sync();
+            if (lane < P) a.actions[((size_t)step * gridDim.x + (size_t)e) * P + lane] = rl.act[lane];
+        } else if (wv == 2) {
+            // the ring in HBM is read by the other waves in later turns
+            scoreboard_out(F, f, fb, rm);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        } else if (wv == 3) {
+            if (lane < 8) rl.hdr[2 + lane] = lane == f.slot ? f.t : f.fresh ? -1 : rl.hdr[2 + lane];
+            if (lane == 0) {
+                rl.hdr[0] = (int)kFeatMagic;
+                rl.hdr[1] = (int)s.episode;
+                *rl.next = 0;
+            }
+            if (lane < 12) reinterpret_cast<uint64_t *>(armt0 + 12 * ((step & 1) ^ 1))[lane] = 0ull;
+        }
+        lds_barrier();
+        TokenLoad v0{}, v1{};
+        if (wv < n_tok) v0 = token_load(f, fb, rm, wv);
+        if (wv + nwv < n_tok) v1 = token_load(f, fb, rm, wv + nwv);
+        frame_update<true>(F, f, rm, fb, tid, nt);
+        lds_barrier();
+        if (n_tok > 0) {
+            float *te = a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow;
+            if (wv < n_tok) token_store(F, f, v0, wv, te);
+            if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
+            for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
+        }
+        // ---- wave 0 plays the turn on the live board, the others write
+        if (wv == 0) {
+            const Turn r = advance(rl.L, g, a.prm, a.seed, env_id, s, lane < P ? rl.act[lane] : 0);
+            if (r.grow2 || r.grow50) {
+                for (int q = lane; q < nq; q += kWave) {
+                    const uint32_t inc = growing4(reinterpret_cast<const uint32_t *>(rl.L.owner)[q],
+                                                  reinterpret_cast<const uint32_t *>(rl.L.type)[q], r.grow2, r.grow50);
+                    int4 x = reinterpret_cast<int4 *>(rl.L.army)[q];
+                    x.x = __builtin_elementwise_add_sat(x.x, (int)(inc & 1u));
+                    x.y = __builtin_elementwise_add_sat(x.y, (int)((inc >> 8) & 1u));
+                    x.z = __builtin_elementwise_add_sat(x.z, (int)((inc >> 16) & 1u));
+                    x.w = __builtin_elementwise_add_sat(x.w, (int)(inc >> 24));
+                    reinterpret_cast<int4 *>(rl.L.army)[q] = x;
+                }
+            }
+            if (lane < P)
+                a.rewards[((size_t)step * gridDim.x + (size_t)e) * P + lane] =
+                    ((r.win >> lane) & 1u) ? 1 : (((r.lose >> lane) & 1u) ? -1 : 0);
+            if (lane == 0) {
+                a.dones[(size_t)step * gridDim.x + (size_t)e] = r.done ? 1 : 0;
+                *rl.s = s;
+            }
+        }
+        float *fe = a.feat + ((size_t)step * gridDim.x + (size_t)e) * (size_t)P * kFeatC * g.HW;
+        auto hand = [&]() { return lane == 0 ? atomicAdd(rl.next, 1) : 0; };
+        for (int k = readfirst(hand()); k < n_planes;) {
+            const int k2 = hand();                         // the next one, while this one is written
+            plane_task<SHIFT, G, R>(F, f, k, fe);
+            k = readfirst(k2);
+        }
+        lds_barrier();
+    }
+    // ---- the board and the memory back to HBM
+    copy16(a.army + cell0, rl.L.army, 4 * n16, tid, nt);
+    copy16(a.owner + cell0, rl.L.owner, n16, tid, nt);
+    copy16(a.type + cell0, rl.L.type, n16, tid, nt);
+    for (int i = tid; i < P * nq; i += nt) reinterpret_cast<uint32_t *>(F.bits)[i] &= kMemoryBits;
+    lds_barrier();
+    copy16(blk + fb.bits, F.mem, (9 * P + 48) * n16, tid, nt);
+    if (tid < 10) reinterpret_cast<int32_t *>(blk)[tid] = rl.hdr[tid];
+    if (wv == 1 && lane < 8) reinterpret_cast<uint32_t *>(a.sc + e)[lane] = reinterpret_cast<const uint32_t *>(rl.s)[lane];
 }
 
 namespace {
@@ -375,18 +876,52 @@ hipError_t feature_tables_ready()
     return e;
 }
 
+// The instance for a board: planes on 16-byte boundaries or not, two players
+// to a wave where a plane (shifted or not) takes at most half of one, rounds
+// of 64 quads of a plane.
+template <class F>
+static void by_layout(int HW, const float *feat, F &&go)
+{
+    const bool shift = HW % 4 != 0 || (reinterpret_cast<uintptr_t>(feat) & 15) != 0;
+    const int quads = (HW + (shift ? 3 : 0)) / 4 + (shift ? 1 : 0), lines = HW % 32 == 0 && (reinterpret_cast<uintptr_t>(feat) & 127) == 0 ? 0 : 7;
+    auto pick = [&](auto sh) {
+        if (quads <= 32) go(sh, std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{});
+        else if (quads + lines <= 64) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
+        else if (quads + lines <= 128) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 2>{});
+        else if (quads + lines <= 192) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 3>{});
+        else go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 5>{});
+    };
+    if (shift) pick(std::true_type{});
+    else pick(std::false_type{});
+}
+
 hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 {
-    const uint32_t lds = (uint32_t)(6 * a.g.S + 2 * a.g.P * 16 * 8 + 28 * a.g.P);
-    // waves per env: 8 for small batches and for more than 4 players (the
-    // cell loop's work grows with P), 2 where 4 would leave a ragged last
-    // round of waves on the chip, else 4 (fewer envs written at once, and
-    // the ring loads of one env's cells overlap across its waves)
-    const int nwv = (n_envs <= 1024 || a.g.P > 4) ? 8 : n_envs <= 2048 ? 2 : 4;
-    if (a.g.HW % 8 == 0)
-        hipLaunchKernelGGL(k_features<true>, dim3((unsigned)n_envs), dim3(kWave * nwv), lds, stream, a);
-    else
-        hipLaunchKernelGGL(k_features<false>, dim3((unsigned)n_envs), dim3(kWave * nwv), lds, stream, a);
+    const uint32_t lds = feat_lds_bytes(a.g.S, a.g.P);
+    // Waves per env: as many as fill a CU's 32 with the envs that fit its
+    // LDS, so that a small board's phases overlap other envs' (10x10 1v1,
+    // 30,000 envs: 8 waves 545 us, 4 waves 426, 2 waves 365; 16x16 2v2,
+    // 16,000 envs: 764, 645, 910; 25x25 FFA-8, 2,000 envs: 387, 467, 810);
+    // 8 where the batch leaves the chip idle anyway (16x16 1v1, 64 envs:
+    // 16.8, 20.2, 27.9; 700 envs: 24.8, 25.4, 32.5), and 16 where every env
+    // has a CU of its own (28x14 FFA-8, 60 envs: 39.0 -> 33.7; 24x24 1v1, 64
+    // envs: 21.6 -> 19.9; but 500 envs: 34.7 -> 39.1; features and step).
+    const uint32_t fit = 160u * 1024u / lds;
+    const int nwv = n_envs <= 256 ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
+    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds) {
+        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value>), dim3((unsigned)n_envs),
+                           dim3(kWave * nwv), lds, stream, a);
+    });
+    return hipGetLastError();
+}
+
+hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
+{
+    const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
+    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds) {
+        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value>), dim3((unsigned)n_envs),
+                           dim3(kWave * (n_envs <= 256 ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
+    });
     return hipGetLastError();
 }
 

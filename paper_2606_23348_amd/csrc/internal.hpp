@@ -139,6 +139,25 @@ struct FeatArgs {
 };
 
 hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream);
+
+// A whole rollout: n_steps turns of every env in one launch.
+struct RolloutArgs {
+    Geom g;
+    FeatBlock blk;
+    GenParamsDev prm;
+    uint64_t seed, env_base, actor_seed, step0;
+    int32_t n_steps;
+    EnvScalars *sc;
+    int8_t *owner;
+    uint8_t *type;
+    int32_t *army;
+    uint8_t *mem;
+    float *feat, *tokens;        // [T][E][P][38][H][W]; [T][E][P][2][512] or nullptr
+    int32_t *actions, *rewards;  // [T][E][P]
+    uint8_t *dones;              // [T][E]
+};
+
+hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream);
 // Entries of the channel-21 table (log(1 + dt) / 5 for dt below this).
 constexpr int kAgeTable = 65536;
 // Upload the feature kernel's tables to the current device once (blocking);
