@@ -84,7 +84,6 @@ gen::Geom geom_of(const gen_state &st)
     g.mode = st.mode;
     g.NW = (g.HW + 63) / 64;
     g.magic_w = (uint32_t)(((1u << 20) + (uint32_t)st.W - 1) / (uint32_t)st.W);
-    g.magic_hw = (uint32_t)(((uint64_t(1) << 32) + (uint64_t)g.HW - 1) / (uint64_t)g.HW);
     g.PS = st.params.obs_layout == 1 ? gen::pool_plane_stride(g.HW, g.P) : g.HW;
     return g;
 }
@@ -267,6 +266,7 @@ gen::PoolArgs pool_args(const gen_pool &pl)
     a.slot_end = (uint32_t)pl.n;
     a.wpg = (uint32_t)pl.tuning.waves_per_group;
     a.lds_per_wave = pl.lds_per_wave;
+    a.stage = pl.stage ? 1u : 0u;
     uint8_t *base = static_cast<uint8_t *>(pl.d_state);
     a.desc = reinterpret_cast<const gen::PoolDesc *>(base + pl.off_desc);
     a.sc = reinterpret_cast<gen::EnvScalars *>(base + pl.off_scalars);
@@ -695,7 +695,7 @@ int gen_pool_create(uint64_t seed, uint64_t env_base, int32_t n_envs, const gen_
         d.obs_off16 = (uint32_t)obs16;
         d.act_off = (uint32_t)acts;
         d.magic_w = g.magic_w;
-        d.magic_hw = g.magic_hw;
+        d.pad32 = 0;
         d.H = (uint8_t)sp.H;
         d.W = (uint8_t)sp.W;
         d.mode = (uint8_t)sp.mode;
@@ -726,7 +726,8 @@ int gen_pool_create(uint64_t seed, uint64_t env_base, int32_t n_envs, const gen_
     pl->state_bytes = pl->off_army + align256(cells * 4);
     pl->obs_bytes = obs16 * 16;
     pl->n_actions = acts;
-    pl->lds_per_wave = (gen::lds_bytes_for(max_s, max_p) + 15) & ~15u;
+    pl->stage = pl->obs_bytes >= gen::kStagePoolBytes;
+    pl->lds_per_wave = (gen::lds_bytes_for(max_s, max_p) + (pl->stage ? gen::kStageExtra : 0u) + 15) & ~15u;
     pool_make_order(*pl);
     *out = pl;
     return ok();

@@ -10,11 +10,13 @@ namespace gen {
 
 // ---------------------------------------------------------------- LDS carve-up
 // Per env, S = padded cells per row (multiple of 16):
-//   army  int32 [S] | owner int8 [S] | type uint8 [S] | armyc uint8 [S] + 16
+//   owner int8 [S] | type uint8 [S] | armyc uint8 [S] + 16
 //   obm   u64 [P][16]                 (cells owned by each player)
 //   vis   u64 [P][16]                 (visible cell bitmaps)
-//   gbm   u64 [3][16] + int32 [8]      (map generator scratch bitmaps, general cells)
+//   gbm   u64 [3][16] + int32 [8]      (passable and army > 1 bitmaps; map generator scratch; army totals)
 //         + u64 [4]                    (the actor's Philox block, computed early)
+//   army  int32 [S]                   (last: dead after growth, when the dense
+//                                      observation writer stages its bytes there and in what follows)
 struct Lds {
     int32_t *army;
     int8_t *owner;
@@ -27,13 +29,13 @@ __device__ __forceinline__ Lds carve(uint8_t *smem, const Geom &g)
 {
     Lds L;
     uint32_t o = 0;
-    L.army = reinterpret_cast<int32_t *>(smem + o); o += 4 * g.S;
     L.owner = reinterpret_cast<int8_t *>(smem + o); o += g.S;
     L.type = smem + o; o += g.S;
     L.armyc = smem + o; o += g.S + 16;
     L.obm = reinterpret_cast<uint64_t *>(smem + o); o += 8 * 16 * g.P;
     L.vis = reinterpret_cast<uint64_t *>(smem + o); o += 8 * 16 * g.P;
-    L.gbm = reinterpret_cast<uint64_t *>(smem + o);
+    L.gbm = reinterpret_cast<uint64_t *>(smem + o); o += 8 * 16 * 3 + 32 + 32;
+    L.army = reinterpret_cast<int32_t *>(smem + o);
     return L;
 }
 
@@ -336,11 +338,51 @@ __device__ int apply_move(const Lds &L, const Geom &g, const EnvScalars &s, int 
 // All players' moves in rotating priority (reading R5), captures applied at
 // once by the whole wave (Section IV-E transfer, reading R9 halving).
 // Returns true if a general was captured (the type row then changed).
-__device__ bool resolve_moves(const Lds &L, const Geom &g, EnvScalars &s, int32_t my_action)
+//
+// Moves whose four, six, ... cells are all different and none of which takes
+// a general do not depend on their order: they are decided and applied in
+// one pass, lane p player p's.  Each lane claims its two cells in a byte row
+// (the last writer of a cell keeps it, so at least one lane of a clash reads
+// another's claim).  Any clash or capture leaves the board untouched and
+// goes through the moves one by one, about 800 clocks each against 1,100 for
+// the pass (8 players: 6,700 -> 1,300 clocks of a wave alone).
+__device__ bool resolve_moves(const Lds &L, const Geom &g, EnvScalars &s, int32_t my_action, uint8_t *claim)
 {
     const int lane = lane_id();
+    const int my_move = lane < g.P && ((s.alive >> lane) & 1) ? decode_action(L, g, my_action) : -1;
+    if (ballot(my_move >= 0) == 0ull) return false;
+    {
+        const int src = my_move & 1023, dst = (my_move >> 10) & 1023;
+        bool slow = false, moves = false;
+        int32_t have = 0, d = 0, m = 0;
+        int o = 0;
+        if (my_move >= 0) {
+            claim[src] = (uint8_t)lane;
+            claim[dst] = (uint8_t)lane;
+        }
+        wave_sync();
+        if (my_move >= 0) {
+            slow = claim[src] != lane || claim[dst] != lane;
+            have = L.army[src];
+            d = L.army[dst];
+            o = L.owner[dst];
+            m = (my_move >> 20) & 1 ? have >> 1 : have - 1;
+            moves = L.owner[src] == lane && have > 1;
+            // a won attack on a general may be a capture
+            slow = slow || (moves && o != lane && L.type[dst] == GENERAL && !(o >= 0 && is_ally(g.mode, o, lane)) && m > d);
+        }
+        if (ballot(slow) == 0ull) {
+            if (moves) {
+                const bool join = o == lane || (o >= 0 && is_ally(g.mode, o, lane));
+                L.army[src] = have - m;
+                L.army[dst] = join ? sat_add(d, m) : m > d ? m - d : d - m;
+                if (join || m > d) L.owner[dst] = (int8_t)lane;
+            }
+            wave_sync();
+            return false;
+        }
+    }
     bool captured = false;
-    const int my_move = lane < g.P ? decode_action(L, g, my_action) : -1;
     for (int j = 0; j < g.P; ++j) {
         const int i = (s.turn + j) % g.P;
         const int packed = readlane(my_move, i);
@@ -361,6 +403,38 @@ __device__ bool resolve_moves(const Lds &L, const Geom &g, EnvScalars &s, int32_
     return captured;
 }
 
+// Cell bitmaps of the board, eight cells a thread (threads tid, tid + nt, ...):
+// those of each player, and with ACT the passable cells and those with more
+// than one unit, as bytes of the row-major bitmaps (bit = cell).  many(b): the
+// armies of cells 8 b to 8 b + 7 clamped to bytes.  (A ballot per player and
+// 64 cells took 580 clocks a word of a wave alone: 5,200 of the 17,800 of a
+// 24x24 step, with 8 players 14,000 of 40,000.)
+template <bool ACT, class Many>
+__device__ __forceinline__ void cell_bitmaps(const Geom &g, const int8_t *owner, const uint8_t *type, uint64_t *own,
+                                             uint64_t *pass, uint64_t *big, int tid, int nt, Many &&many)
+{
+    for (int b = tid; b < 8 * g.NW; b += nt) {
+        const int left = g.HW - 8 * b;                 // bytes past the map are read and masked
+        const uint32_t real = left >= 8 ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
+        const uint2 o = *reinterpret_cast<const uint2 *>(owner + 8 * b);
+        for (int p = 0; p < g.P; ++p)
+            reinterpret_cast<uint8_t *>(own + p * 16)[b] =
+                (uint8_t)(bits8(bytes_eq(o.x, (uint32_t)p), bytes_eq(o.y, (uint32_t)p)) & real);
+        if (ACT) {
+            const uint2 t = *reinterpret_cast<const uint2 *>(type + 8 * b), m = many(b);
+            const uint32_t mt = bits8(t.x & ~(t.x >> 1) & 0x01010101u, t.y & ~(t.y >> 1) & 0x01010101u);
+            reinterpret_cast<uint8_t *>(pass)[b] = (uint8_t)(~mt & real);
+            reinterpret_cast<uint8_t *>(big)[b] = (uint8_t)(bits8(bytes_gt1(m.x), bytes_gt1(m.y)) & real);
+        }
+    }
+}
+
+// Four armies clamped to bytes.
+__device__ __forceinline__ uint32_t clamp4(int4 a)
+{
+    return (uint32_t)min(a.x, 255) | ((uint32_t)min(a.y, 255) << 8) | ((uint32_t)min(a.z, 255) << 16) | ((uint32_t)min(a.w, 255) << 24);
+}
+
 // ---------------------------------------------------------------- random legal actor (reading R15)
 // Lane (p, w) holds word w of player p's bitmaps.  The legal moves of one
 // direction are the player's cells with more than one unit whose neighbour
@@ -376,8 +450,8 @@ __device__ void actor_wave(const Geom &g, const uint64_t *own, const uint64_t *p
 {
     const int lane = lane_id();
     const int NW = g.NW, W = g.W;
-    const int ppr = kWave / NW;
-    const int lp = lane / NW, w = lane - lp * NW;
+    const int lp = lane_player(NW), w = lane - lp * NW;
+    const int ppr = readlane(lp, kWave - 1) + ((readlane(w, kWave - 1) == NW - 1) ? 1 : 0);     // 64 / NW
     const ColMasks cm = col_masks(w, g);
     const uint64_t pw = pass[w];
     const uint64_t pprev = w > 0 ? pass[w - 1] : 0ull, pnext = w < NW - 1 ? pass[w + 1] : 0ull;
@@ -464,7 +538,8 @@ __device__ void actor_wave(const Geom &g, const uint64_t *own, const uint64_t *p
 // ---------------------------------------------------------------- one turn on the LDS grid
 // What a step does before growth: the moves, the turn counter, terminal and
 // rewards (Section III, Section IV-E; reading R11), the next map where a
-// finished game restarts.  Executed by one wave; `act` is lane p's action.
+// finished game restarts.  Executed by one wave; `act` is lane p's action,
+// `claim` S bytes of LDS for the moves.
 struct Turn {
     bool write_type = false;     // the type row (and the general cells) changed
     bool grow2 = false, grow50 = false, done = false;
@@ -472,7 +547,7 @@ struct Turn {
 };
 
 __device__ __forceinline__ Turn advance(const Lds &L, const Geom &g, const GenParamsDev &prm, uint64_t seed,
-                                        uint64_t env_id, EnvScalars &s, int32_t act)
+                                        uint64_t env_id, EnvScalars &s, int32_t act, uint8_t *claim)
 {
     Turn r;
     if (s.finished) {
@@ -480,7 +555,7 @@ __device__ __forceinline__ Turn advance(const Lds &L, const Geom &g, const GenPa
         return r;
     }
     const uint32_t alive0 = s.alive;
-    r.write_type = resolve_moves(L, g, s, act);
+    r.write_type = resolve_moves(L, g, s, act, claim);
     s.turn += 1;
     r.grow2 = (s.turn & 1) == 0;
     r.grow50 = (s.turn % 50) == 0;

@@ -32,7 +32,6 @@ static_assert(sizeof(EnvScalars) == 32, "scalar record is 32 bytes");
 struct Geom {
     int H, W, HW, S, P, mode, NW;
     uint32_t magic_w;    // ceil(2^20 / W): c / W == (c * magic_w) >> 20 for c < 1024
-    uint32_t magic_hw;   // ceil(2^32 / HW): b / HW == (b * magic_hw) >> 32 for b < 65536
     int PS;              // observation plane stride in bytes (HW, or HW padded to 32 bytes)
 };
 
@@ -89,7 +88,7 @@ struct PoolDesc {
     uint32_t obs_off16;  // offset of the env's observation block ([P][8] planes of
                          // pool_plane_stride(H*W, P) bytes), in 16-byte units
     uint32_t act_off;    // first int32 of the env's actions and rewards
-    uint32_t magic_w, magic_hw;
+    uint32_t magic_w, pad32;
     uint8_t H, W, mode, P;
     uint8_t cmin, cmax, dmin, pad8;
     uint32_t env;        // the env's index in the pool (the device array is in work-list order)
@@ -153,18 +152,6 @@ __device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
 // Broadcast of a wave-uniform lane's value.
 __device__ __forceinline__ int readlane(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ __forceinline__ int readfirst(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
-{
-    for (int d = 32; d >= 1; d >>= 1) v += shfl32(v, lane_id() ^ d);
-    return v;
-}
-
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v)
-{
-    for (int d = 32; d >= 1; d >>= 1) v += (int64_t)shfl64((uint64_t)v, lane_id() ^ d);
-    return v;
-}
 
 // Lane i receives v of lane i - 1, lane 0 receives `first` (a DPP wave
 // shift; every lane of the wave must be active).
@@ -302,6 +289,19 @@ __device__ __forceinline__ uint32_t bytes_eq(uint32_t x, uint32_t b)
     return (~t >> 7) & 0x01010101u;
 }
 
+// The 8 bits of two dwords of 0/1 bytes (bit i = byte i), by byte dot products.
+__device__ __forceinline__ uint32_t bits8(uint32_t lo, uint32_t hi)
+{
+    return __builtin_amdgcn_udot4(hi, 0x80402010u, __builtin_amdgcn_udot4(lo, 0x08040201u, 0u, false), false);
+}
+
+// 0x01 in every byte of x above 1, else 0x00.
+__device__ __forceinline__ uint32_t bytes_gt1(uint32_t x)
+{
+    const uint32_t y = x & 0xFEFEFEFEu;
+    return ((((y & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | y) >> 7) & 0x01010101u;
+}
+
 // Bits 0..3 of v to 0x01 in bytes 0..3.
 __device__ __forceinline__ uint32_t spread4(uint32_t v) { return (v * 0x00204081u) & 0x01010101u; }
 
@@ -312,10 +312,6 @@ __device__ __forceinline__ int32_t sat_add(int32_t a, int32_t b)
 }
 
 __device__ __forceinline__ int div_w(int c, const Geom &g) { return (int)(((uint32_t)c * g.magic_w) >> 20); }
-__device__ __forceinline__ uint32_t div_hw(uint32_t b, const Geom &g)
-{
-    return (uint32_t)(((uint64_t)b * g.magic_hw) >> 32);
-}
 
 // Bit positions b of word w (cell 64w + b) that lie in column 0 / column W-1,
 // and the positions that are real cells (< HW).
@@ -348,44 +344,57 @@ __device__ __forceinline__ ColMasks col_masks(int w, const Geom &g)
 // again by the same launch; nontemporal stores keep them from crowding the
 // caches (measured: a step at the copy ceiling instead of 20% below it).
 // Only for whole, sector-aligned runs: where two stores share a 32-byte
-// sector (unaligned observation planes) plain stores are faster.
+// sector plain stores are faster (the first and last lines of a staged run).
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void st_nt(uint32_t *p, uint32_t v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ void st_nt(uint2 *p, uint2 v)
-{
-    const u32x2 x = {v.x, v.y};
-    __builtin_nontemporal_store(x, reinterpret_cast<u32x2 *>(p));
-}
 __device__ __forceinline__ void st_nt(uint4 *p, uint4 v)
 {
     const u32x4 x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(p));
 }
 
+// 64-bit value of the lane before / after (0 at the wave's ends).
+__device__ __forceinline__ uint64_t wave_prev64(uint64_t v)
+{
+    return (uint64_t)wave_shr1((uint32_t)v, 0u) | ((uint64_t)wave_shr1((uint32_t)(v >> 32), 0u) << 32);
+}
+
+__device__ __forceinline__ uint64_t wave_next64(uint64_t v)
+{
+    return (uint64_t)wave_shl1((uint32_t)v, 0u) | ((uint64_t)wave_shl1((uint32_t)(v >> 32), 0u) << 32);
+}
+
+// Lane l as (player l / NW, word l % NW) of the cell bitmaps; the quotient by
+// a reciprocal (exact: l + 1/2 is at least 1/32 of NW away from a multiple).
+__device__ __forceinline__ int lane_player(int NW)
+{
+    return (int)(((float)lane_id() + 0.5f) * __builtin_amdgcn_rcpf((float)NW));
+}
+
 // Fog (Section IV-B; team vision R10): vis[p] = the 8-neighbour dilation of
 // the cells of p's team (p, and p ^ 2 in 2v2), horizontal 3 then vertical 3
 // on the row-major cell bitmaps.  obm and vis are [P][16] words in LDS; lane
-// (p, w) of each round handles word w of player p, 64 / NW players a round.
-// Every lane must call it (the shuffles read neighbouring words).
+// (p, w) of each round handles word w of player p, 64 / NW players a round,
+// neighbouring words by DPP moves.  Every lane must call it.
 __device__ __forceinline__ void team_vision(const uint64_t *obm, uint64_t *vis, const Geom &g)
 {
     const int lane = lane_id();
-    const int ppr = kWave / g.NW;
-    const int lp = lane / g.NW, w = lane - lp * g.NW;
+    const int lp = lane_player(g.NW), w = lane - lp * g.NW;
+    const int ppr = readlane(lp, kWave - 1) + ((readlane(w, kWave - 1) == g.NW - 1) ? 1 : 0);   // 64 / NW
     const ColMasks cm = col_masks(w, g);
     for (int p0 = 0; p0 < g.P; p0 += ppr) {
         const int p = p0 + lp;
         const bool valid = lp < ppr && p < g.P;
         uint64_t m = valid ? obm[p * 16 + w] : 0ull;
         if (valid && g.mode == MODE_2V2) m |= obm[(p ^ 2) * 16 + w];
-        uint64_t mp = shfl64(m, lane - 1), mn = shfl64(m, lane + 1);
+        uint64_t mp = wave_prev64(m), mn = wave_next64(m);
         if (w == 0) mp = 0ull;
         if (w == g.NW - 1) mn = 0ull;
         const uint64_t h = m | (((m << 1) | (mp >> 63)) & ~cm.col0) | (((m >> 1) | (mn << 63)) & ~cm.colL);
-        uint64_t hp = shfl64(h, lane - 1), hn = shfl64(h, lane + 1);
+        uint64_t hp = wave_prev64(h), hn = wave_next64(h);
         if (w == 0) hp = 0ull;
         if (w == g.NW - 1) hn = 0ull;
         const uint64_t v = (h | (h << g.W) | (hp >> (64 - g.W)) | (h >> g.W) | (hn << (64 - g.W))) & cm.valid;

@@ -181,26 +181,13 @@ __device__ __forceinline__ void ring_masks(const FeatLds &F, const FrameCtx &f, 
     }
 }
 
-// Owned-cell bitmaps and the players' land and army totals, the 64-cell
-// words shared out over the waves (armt and land zeroed before).  One LDS
-// addition per owned cell: 64 of them to few addresses cost less than a wave
-// sum per player.
-__device__ __forceinline__ void frame_totals(const FeatLds &F, const Geom &g, int wv, int nwv)
+// Army totals (zeroed before), one LDS addition per owned cell: 64 of them to
+// few addresses cost less than a wave sum per player.
+__device__ __forceinline__ void army_totals(const FeatLds &F, const Geom &g, int tid, int nt)
 {
-    const int lane = lane_id();
-    for (int w = wv; w < g.NW; w += nwv) {
-        const int c = w * 64 + lane;
-        const int o = c < g.HW ? (int)F.owner[c] : -1;
-        uint64_t mine = 0ull;                          // word w of player `lane`
-        for (int p = 0; p < g.P; ++p) {
-            const uint64_t m = ballot(o == readfirst(p));
-            if (lane == p) mine = m;
-        }
-        if (lane < g.P) {
-            F.obm[lane * 16 + w] = mine;
-            atomicAdd(&F.land[lane], __popcll(mine));
-        }
-        if (o >= 0) atomicAdd(&F.armt[o], (unsigned long long)F.army[c]);
+    for (int c = tid; c < g.HW; c += nt) {
+        const int o = F.owner[c];
+        if (o >= 0) atomicAdd(&F.armt[o], (unsigned long long)(uint32_t)F.army[c]);
     }
 }
 
@@ -576,6 +563,12 @@ __device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx 
         if (f.fresh || j == ts)
             __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(j == ts ? f.t : -1), rm, 4 * j, (int)fb.tstamp, 0);
     if (lane < f.g.P) {
+        int32_t n = 0;
+        for (int w = 0; w < f.g.NW; ++w) n += __popcll(F.obm[lane * 16 + w]);
+        F.land[lane] = n;
+    }
+    wave_sync();
+    if (lane < f.g.P) {
         int32_t ol = 0;
         int64_t oa = 0;
         for (int q = 0; q < f.g.P; ++q) {              // the enemies' totals
@@ -639,14 +632,15 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
     int32_t stamp[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) stamp[j] = f.fresh ? -1 : readfirst((int)hdr[2 + j]);
-    if (tid < 8) { F.armt[tid] = 0; F.land[tid] = 0; }
+    if (tid < 8) F.armt[tid] = 0;
     if (wv == nwv - 1 && lane < 32) {
         F.cx[lane] = (float)((double)lane / (double)(g.W - 1));
         F.cy[lane] = (float)((double)lane / (double)(g.H - 1));
     }
     lds_barrier();
     ring_masks(F, f, slots_held(stamp, f.t), tid, nt);
-    frame_totals(F, g, wv, nwv);
+    cell_bitmaps<false>(g, F.owner, F.type, F.obm, nullptr, nullptr, tid, nt, [](int) { return make_uint2(0u, 0u); });
+    army_totals(F, g, tid, nt);
     lds_barrier();
     if (wv == 0) team_vision(F.obm, F.vis, g);
     const Rsrc rm = buffer_rsrc(blk, fb.bytes);
@@ -692,11 +686,12 @@ struct RollLds {
     int32_t *hdr;            // the memory block's header: magic, episode, stamp[8]
     int32_t *act;            // [8] this turn's actions
     int32_t *next;           // next plane to hand out
+    uint8_t *claim;          // [S] for the moves
 };
 
 constexpr int kRollExtra = 8 * 56 + 32 + 48 + 32 + 16 + 2 * 96;
 
-__host__ __device__ inline uint32_t roll_lds_bytes(int S, int P) { return feat_lds_bytes(S, P) + (uint32_t)(20 * S + kRollExtra); }
+__host__ __device__ inline uint32_t roll_lds_bytes(int S, int P) { return feat_lds_bytes(S, P) + (uint32_t)(21 * S + kRollExtra); }
 
 template <bool SHIFT, int G, int R>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
@@ -717,6 +712,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         F.own = x; x += 8 * S;
         F.foe = x; x += 8 * S;
         F.army = reinterpret_cast<int32_t *>(x); x += 4 * S;
+        rl.claim = x; x += S;
         rl.L.army = F.army;
         rl.L.owner = F.owner;
         rl.L.type = F.type;
@@ -772,13 +768,11 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         if (f.fresh) ring_masks(F, f, 0u, tid, nt);    // no earlier frames
         F.armt = armt0 + 12 * (step & 1);
         F.land = reinterpret_cast<int32_t *>(F.armt + 8);
-        frame_totals(F, g, wv, nwv);
-        for (int w = wv; w < g.NW; w += nwv) {
-            const int c = w * 64 + lane;
-            const uint64_t pm = ballot(c < g.HW && rl.L.type[min(c, S - 1)] != MOUNTAIN);
-            const uint64_t bm = ballot(c < g.HW && rl.L.army[min(c, S - 1)] > 1);
-            if (lane == 0) { rl.L.gbm[w] = pm; rl.L.gbm[16 + w] = bm; }
-        }
+        cell_bitmaps<true>(g, F.owner, F.type, F.obm, rl.L.gbm, rl.L.gbm + 16, tid, nt, [&](int b) {
+            const int4 *x = reinterpret_cast<const int4 *>(F.army) + 2 * b;
+            return make_uint2(clamp4(x[0]), clamp4(x[1]));
+        });
+        army_totals(F, g, tid, nt);
         lds_barrier();
         // ---- vision; the actor's draws; the scoreboard ring; the header
         if (wv == 0) {
@@ -814,7 +808,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         }
         // ---- wave 0 plays the turn on the live board, the others write
         if (wv == 0) {
-            const Turn r = advance(rl.L, g, a.prm, a.seed, env_id, s, lane < P ? rl.act[lane] : 0);
+            const Turn r = advance(rl.L, g, a.prm, a.seed, env_id, s, lane < P ? rl.act[lane] : 0, rl.claim);
             if (r.grow2 || r.grow50) {
                 for (int q = lane; q < nq; q += kWave) {
                     const uint32_t inc = growing4(reinterpret_cast<const uint32_t *>(rl.L.owner)[q],

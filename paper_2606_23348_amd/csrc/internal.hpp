@@ -47,6 +47,7 @@ struct PoolArgs {
     uint32_t n_envs, wpg, lds_per_wave;
     uint32_t slot_begin, slot_end;    // the segment of the work list this launch steps
     uint32_t actor;              // 1: draw the next actions after the step (ACT kernels)
+    uint32_t stage;              // 1: planes of more than one round of stores go through the staged writer
     const PoolDesc *desc;        // work list: the descriptor of each slot's env
     EnvScalars *sc;
     int8_t *owner;
@@ -193,12 +194,18 @@ hipError_t launch_stream_spread(void *dst, const void *src, uint32_t n16, uint32
 
 uint32_t lds_bytes(const Geom &g);
 uint32_t lds_bytes_for(int S, int P);
+// A pool whose observation is at least this large stages its planes in LDS,
+// which takes kStageExtra more bytes of it (19x19 to 23x23, 81,136 envs: 249
+// -> 229 us per step; 18x18 to 25x25, 10,000 envs, about 100 MB: 34.6 -> 33.0;
+// the mixed 10x10 to 25x25, 131,072 envs: 290 -> 288; 2,000 envs: 10.6 -> 14.4,
+// so smaller pools do not).
+constexpr uint64_t kStagePoolBytes = 64000000ull;
+constexpr uint32_t kStageExtra = 384;
 // One workgroup per env of the launch (total_envs = the requests' env
 // counts summed): workgroup b steps env b - first[i] of request i, the last
 // i with first[i] <= b.
 // all_uniform: every request's group record has uniform set.
 hipError_t launch_serve(const ServeLaunch &la, uint32_t total_envs, uint32_t lds, bool all_uniform, hipStream_t stream);
-int obs_variant(int HW, int P);
 hipError_t launch_pool(const PoolArgs &a, int kind, bool act, uint32_t grid, uint32_t nwv, hipStream_t stream);
 hipError_t launch_step(const EnvArgs &a, int n_envs, hipStream_t stream);
 hipError_t launch_reset(const EnvArgs &a, int n_envs, hipStream_t stream);
@@ -238,6 +245,7 @@ struct gen_pool {
     uint64_t off_scalars = 0, off_desc = 0, off_owner = 0, off_type = 0, off_army = 0;
     uint64_t state_bytes = 0, obs_bytes = 0, n_actions = 0;
     uint32_t lds_per_wave = 0;
+    bool stage = false;                   // see kStagePoolBytes
     int32_t max_cells = 0;
     gen_pool_tuning tuning{1, 0, 0, 0};
     std::vector<gen_pool_bucket> buckets;  // per-bucket packing (gen_pool_set_buckets); empty = pool-wide

@@ -2,7 +2,9 @@
 // (arxiv 2606.23348, Section IV).  One wave64 owns one environment: the grid
 // (owner int8, type uint8, army int32) is loaded from HBM into LDS once, the
 // whole step runs on it, and owner/army plus the uint8 observation stream
-// back out with 16-byte stores.  No MFMA: nothing here is a contraction.
+// back out.  No MFMA: nothing here is a contraction.
+#include <algorithm>
+
 #include "board.hpp"
 #include "device.hpp"
 #include "internal.hpp"
@@ -15,12 +17,26 @@ uint32_t lds_bytes_for(int S, int P)
     return (uint32_t)(4 * S + S + S + (S + 16) + 8 * 16 * (2 * P + 3) + 32 + 32);
 }
 
+// The staged writer's runs: four planes of a player, or all eight where the
+// quads of a plane (and one more for a shifted one) fit half a wave.
+constexpr int kSmallBoard = 121;
+constexpr int kOneRound = 256;         // cells whose quads are one wave's
+__host__ __device__ static inline int planes_per_run(int PS) { return PS <= kSmallBoard ? 8 : 4; }
+
+// Its staging of one wave: a run, the line carried from the run before, the
+// bytes a quad at the end writes past them.
+__host__ __device__ static inline uint32_t stage_bytes(const Geom &g)
+{
+    return (uint32_t)(planes_per_run(g.PS) * ((g.PS + 15) & ~15) + 128 + 48);
+}
+
 // ---------------------------------------------------------------- fused env kernel
 enum { K_STEP = 0, K_RESET = 1, K_OBSERVE = 2 };
-// Observation writers: planes of a multiple of 4 cells (dword aligned), any
-// other size, or planes padded to a multiple of 4 bytes (the layout of a
-// pool's ragged observations, so envs of every shape take the dword writer).
-enum { OBS_QUAD = 0, OBS_STREAM = 1, OBS_PADDED = 2 };
+// Observation writers: planes of a multiple of 4 cells (dword aligned) stored
+// where they lie, any other size staged in LDS, planes padded to a multiple
+// of 4 bytes (the layout of a pool's ragged observations, so envs of every
+// shape take the dword writer), or aligned planes staged.
+enum { OBS_QUAD = 0, OBS_STREAM = 1, OBS_PADDED = 2, OBS_STAGED = 3 };
 
 // Player-independent bits of the four cells of quad q, one 0x01 per cell
 // byte (SWAR over the owner and type bytes).
@@ -84,114 +100,133 @@ __device__ __forceinline__ void quad_store(const Lds &L, const Geom &g, const Rs
         __builtin_amdgcn_raw_buffer_store_b32(v[ch] & keep, ro, 4 * q, (p * 8 + ch) * PS, AUX);
 }
 
-// Code bytes of the four cells of quad q for player p (bit k = channel k,
-// k < 7; bit 6 set = fog): one register per quad for the stream writer,
-// which extracts the channels one at a time.
-__device__ __forceinline__ uint32_t code_quad(const Lds &L, int p, uint32_t ally, int q)
-{
-    const QuadCells c = quad_cells(L, q);
-    const uint32_t vb = (uint32_t)(L.vis[p * 16 + (q >> 4)] >> ((q & 15) * 4)) & 0xFu;
-    const uint32_t visb = spread4(vb);
-    const uint32_t eqp = bytes_eq(c.o4, (uint32_t)p);
-    const uint32_t eqa = ally == (uint32_t)p ? eqp : bytes_eq(c.o4, ally);
-    const uint32_t enemy = (c.neutral ^ 0x01010101u) & ~eqp & ~eqa;
-    return eqp | ((enemy & visb) << 1) | ((c.plain_n & visb) << 2) | ((c.mtn & visb) << 3) | ((c.cas & visb) << 4) |
-           ((c.gen & visb) << 5) | ((visb ^ 0x01010101u) << 6);
-}
-
-// Army bytes of a quad on the cells its code bytes mark visible.
-__device__ __forceinline__ uint32_t army_visible(uint32_t ac, uint32_t code4)
-{
-    return ac & ((((code4 >> 6) & 0x01010101u) ^ 0x01010101u) * 0xFFu);
-}
-
-// Code byte of one cell for player p (bit k = channel k < 7, as quad_planes), for the few
-// output dwords that hold bytes of two planes.
-__device__ __forceinline__ uint32_t code_cell(const Lds &L, int p, uint32_t ally, int c)
-{
-    const int o = L.owner[c];
-    const uint32_t t = L.type[c];
-    const bool vis = (L.vis[p * 16 + (c >> 6)] >> (c & 63)) & 1ull;
-    const bool neutral = o < 0;
-    const bool enemy = !neutral && o != p && (uint32_t)o != ally;
-    uint32_t code = (o == p) ? 1u : 0u;
-    if (vis) {
-        code |= (enemy ? 2u : 0u) | ((neutral && t != (uint32_t)MOUNTAIN) ? 4u : 0u) |
-                (t == (uint32_t)MOUNTAIN ? 8u : 0u) | (t == (uint32_t)CASTLE ? 16u : 0u) |
-                (t == (uint32_t)GENERAL ? 32u : 0u);
-    } else {
-        code |= 64u;
-    }
-    return code;
-}
-
-// Observation byte b of the env block (plane b / HW, cell b % HW).
-__device__ __forceinline__ uint32_t obs_byte(const Lds &L, const Geom &g, uint32_t b)
-{
-    const uint32_t q = div_hw(b, g), c = b - q * g.HW, p = q >> 3, ch = q & 7;
-    const uint32_t ally = g.mode == MODE_2V2 ? (p ^ 2u) : p;
-    const uint32_t cd = code_cell(L, (int)p, ally, (int)c);
-    return ch < 7 ? (cd >> ch) & 1u : (((cd >> 6) & 1u) ? 0u : L.armyc[c]);
-}
-
 // Two waves per env: wave 0 writes the planes of players 0 .. obs_split(P) - 1
 // and then runs the actor, wave 1 the rest (3 of 8 and 5 of 8 players
-// balance the two; measured against 4 and 4: FFA-8 25x25 226 -> 217 us).
+// balance the two).
 __device__ __forceinline__ int obs_split(int P) { return (P * 3) >> 3; }
 
-// The unaligned-plane writer's main pass for players p_begin .. p_end - 1
-// (every lane of the wave; the dwords that hold bytes of two planes are left
-// to the caller's byte-wise pass).
-__device__ __forceinline__ void obs_stream_planes(const Lds &L, const Geom &g, uint8_t *obs, int p_begin, int p_end)
+// Waves per env in the staged writer: its n runs shared out, fewer for wave 0,
+// which goes on to the actor (about one run's time).
+struct RunRange { int begin, end; };
+
+__device__ __forceinline__ RunRange wave_runs(const Geom &g, int wave, int nwv, bool act)
 {
-    const int lane = lane_id();
-    const int nq = g.HW >> 2;                                   // whole quads
-    const int rounds = (nq + 1 + kWave - 1) / kWave;            // quads 0 .. nq
-    const Rsrc ro = buffer_rsrc(obs, (uint32_t)(g.P * 8 * g.HW));
-    const uint32_t HWu = (uint32_t)g.HW;
-    const uint32_t m1 = HWu & 3u, m2 = (2u * HWu) & 3u, m3 = (3u * HWu) & 3u;
-    const uint32_t M = 0x01010101u;
-    for (int p = p_begin; p < p_end; ++p) {
+    const int n = g.P * 8 / planes_per_run(g.PS), own = act ? 1 : 0;
+    if (nwv == 1) return {0, n};
+    const int c0 = max(0, (n + own) / nwv - own);
+    if (wave == 0) return {0, c0};
+    return {c0 + (n - c0) * (wave - 1) / (nwv - 1), c0 + (n - c0) * wave / (nwv - 1)};
+}
+
+// Dense planes, runs [runs.begin, runs.end), by one wave: the bytes are put
+// together in LDS and leave in the tensor's order as whole 128-byte lines, 16
+// bytes a lane; the bytes of a line that the next run finishes are carried
+// over, and only the range's first and last lines (shared with a neighbour)
+// are written in part.  Planes of an odd number of cells start anywhere in a
+// dword (WHOLE: they never do): each dword is realigned with the lane before
+// and added to a cleared stage, so the dwords across two planes need no case
+// of their own.  The cells are decoded once for all players: R rounds of 64
+// quads, or with HALF lanes 32 to 63 take channels 4 to 7 of the quads of
+// lanes 0 to 31.  (Before, every plane's dwords were stored where they lie,
+// each plane's first and last lines in parts: us per step: FFA-8 25x25, 16,384 envs 215 -> 129; 2v2 17x19, 30,000 envs
+// 134 -> 90; 1v1 25x25, 65,536 envs 278 -> 200; 9x11, 124 -> 98.)
+template <bool WHOLE, int R, bool HALF>
+__device__ __forceinline__ void stage_runs(const Lds &L, const Geom &g, uint8_t *obs, RunRange runs, uint8_t *stage)
+{
+    constexpr int kPlanes = HALF ? 8 : 4;
+    const int lane = lane_id(), HW = g.HW, PS = g.PS;                  // cells, bytes from plane to plane
+    const int cells = (HW + 3) >> 2, nq = (PS + 3) >> 2;               // quads of cells, of bytes
+    const uint32_t tail = (HW & 3) ? (1u << (8 * (HW & 3))) - 1u : ~0u;
+    const int d = (int)(reinterpret_cast<uintptr_t>(obs) & 127u);
+    const Rsrc ro = buffer_rsrc(obs - d, (uint32_t)(d + g.P * 8 * PS));
+    const int first = d + runs.begin * kPlanes * PS;   // from the line at or before the block
+    QuadCells qc[R];
+    uint32_t ac[R], keep[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int q = HALF ? lane & 31 : kWave * k + lane, qi = min(q, cells - 1);
+        keep[k] = q < cells - 1 ? ~0u : q == cells - 1 ? tail : 0u;
+        qc[k] = quad_cells(L, qi);
+        ac[k] = reinterpret_cast<const uint32_t *>(L.armyc)[qi];
+    }
+    if (!WHOLE)
+        for (int i = lane; i < (int)(stage_bytes(g) >> 4); i += kWave) reinterpret_cast<uint4 *>(stage)[i] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t carry = 0u;                               // lane i: dword i of the line the last run left unfinished
+    for (int n = runs.begin; n < runs.end; ++n) {
+        const int p = HALF ? n : n >> 1;
+        const bool upper = HALF ? lane >= 32 : (n & 1) != 0;           // channels 4 to 7
         const uint32_t ally = g.mode == MODE_2V2 ? (uint32_t)(p ^ 2) : (uint32_t)p;
-        const uint32_t pbase = (uint32_t)p * 8u * HWu;         // byte offset of plane (p, 0), a multiple of 8
-        uint32_t carry_c = 0u, carry_a = 0u;
-        for (int r = 0; r < rounds; ++r) {
-            const int j = r * kWave + lane;
-            const int qj = j < (g.S >> 2) ? j : 0;              // stays inside the padded row
-            const uint32_t code = code_quad(L, p, ally, qj);
-            const uint32_t ac = reinterpret_cast<const uint32_t *>(L.armyc)[qj];
-            const uint32_t pc = wave_shr1(code, carry_c), pa = wave_shr1(ac, carry_a);
-            carry_c = (uint32_t)readlane((int)code, kWave - 1);
-            carry_a = (uint32_t)readlane((int)ac, kWave - 1);
-            const uint32_t c1 = m1 == 0u ? code : __builtin_amdgcn_alignbyte(code, pc, 4u - m1);
-            const uint32_t c2 = m2 == 0u ? code : __builtin_amdgcn_alignbyte(code, pc, 4u - m2);
-            const uint32_t c3 = m3 == 0u ? code : __builtin_amdgcn_alignbyte(code, pc, 4u - m3);
-            const uint32_t a3 = m3 == 0u ? ac : __builtin_amdgcn_alignbyte(ac, pa, 4u - m3);
-            // interior: bytes 4j - m .. 4j - m + 3 all inside the plane.
-            // Plain (cached) stores: the 32-byte sectors at plane
-            // boundaries are shared by two stores and the cache merges
-            // them; nontemporal partial-sector writes measured 1.5x
-            // slower on these shapes.
-            const int vo = 4 * j;
-            if (vo + 4 <= g.HW) {
-                __builtin_amdgcn_raw_buffer_store_b32(code & M, ro, vo, (int)(pbase & ~3u), 0);
-                __builtin_amdgcn_raw_buffer_store_b32((code >> 4) & M, ro, vo, (int)((pbase + 4u * HWu) & ~3u), 0);
+        const int at = d + n * kPlanes * PS, line = at & ~127, end = at + kPlanes * PS;
+        uint32_t visb[R];
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int qi = min(HALF ? lane & 31 : kWave * k + lane, cells - 1);
+            visb[k] = spread4((uint32_t)(L.vis[p * 16 + (qi >> 4)] >> ((qi & 15) * 4)) & 0xFu);
+        }
+        wave_sync();
+        if (lane < 32) reinterpret_cast<uint32_t *>(stage)[lane] = carry;
+        wave_sync();
+        [[maybe_unused]] uint32_t before[4] = {0u, 0u, 0u, 0u};         // the last quad of the round before
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int q = HALF ? lane & 31 : kWave * k + lane;
+            uint32_t v[4] = {0u, 0u, 0u, 0u}, u[4] = {0u, 0u, 0u, 0u};
+            if (HALF || upper) {
+                u[0] = qc[k].cas & visb[k];
+                u[1] = qc[k].gen & visb[k];
+                u[2] = visb[k] ^ 0x01010101u;
+                u[3] = ac[k] & (visb[k] * 0xFFu);
             }
-            if (vo >= (int)m1 && vo + 4 - (int)m1 <= g.HW) {
-                __builtin_amdgcn_raw_buffer_store_b32((c1 >> 1) & M, ro, vo, (int)((pbase + HWu) & ~3u), 0);
-                __builtin_amdgcn_raw_buffer_store_b32((c1 >> 5) & M, ro, vo, (int)((pbase + 5u * HWu) & ~3u), 0);
+            if (HALF || !upper) {
+                const uint32_t eqp = bytes_eq(qc[k].o4, (uint32_t)p);
+                const uint32_t eqa = ally == (uint32_t)p ? eqp : bytes_eq(qc[k].o4, ally);
+                v[0] = eqp;
+                v[1] = (qc[k].neutral ^ 0x01010101u) & ~eqp & ~eqa & visb[k];
+                v[2] = qc[k].plain_n & visb[k];
+                v[3] = qc[k].mtn & visb[k];
             }
-            if (vo >= (int)m2 && vo + 4 - (int)m2 <= g.HW) {
-                __builtin_amdgcn_raw_buffer_store_b32((c2 >> 2) & M, ro, vo, (int)((pbase + 2u * HWu) & ~3u), 0);
-                __builtin_amdgcn_raw_buffer_store_b32((c2 >> 6) & M, ro, vo, (int)((pbase + 6u * HWu) & ~3u), 0);
-            }
-            if (vo >= (int)m3 && vo + 4 - (int)m3 <= g.HW) {
-                __builtin_amdgcn_raw_buffer_store_b32((c3 >> 3) & M, ro, vo, (int)((pbase + 3u * HWu) & ~3u), 0);
-                __builtin_amdgcn_raw_buffer_store_b32(army_visible(a3, c3), ro, vo, (int)((pbase + 7u * HWu) & ~3u),
-                                                      0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int x = at - line + j * PS;      // the plane's place in the stage, m bytes into a dword
+                const uint32_t m = (uint32_t)x & 3u, c = (upper ? u[j] : v[j]) & keep[k];
+                uint32_t *to = reinterpret_cast<uint32_t *>(stage + ((HALF && upper ? x + 4 * PS : x) & ~3)) + q;
+                if (WHOLE) {
+                    if (q < nq) *to = c;
+                    continue;
+                }
+                uint32_t out = c;
+                if (m != 0u) out = __builtin_amdgcn_alignbyte(c, wave_shr1(c, before[j]), 4u - m);
+                if (k + 1 < R) before[j] = (uint32_t)readlane((int)c, kWave - 1);
+                if (q <= nq) atomicOr(to, out);
             }
         }
+        wave_sync();
+        // whole lines out; a cleared stage is left for the next run
+        const int whole = (end & ~127) - line, shared = line < first ? 128 : 0;
+        const int i = 4 * lane, rest = end - line - whole;   // bytes of the line the next run finishes
+        const bool last = n + 1 == runs.end;
+        carry = i < rest ? *reinterpret_cast<const uint32_t *>(stage + whole + i) : 0u;
+        if (shared != 0 && (whole > 0 || last) && i >= first - line && i < (whole > 0 ? 128 : end - line))
+            __builtin_amdgcn_raw_buffer_store_b32(*reinterpret_cast<const uint32_t *>(stage + i), ro, i, line, 0);
+        for (int j = 16 * lane; j < end - line; j += 16 * kWave) {
+            u32x4 *x = reinterpret_cast<u32x4 *>(stage + j);
+            const u32x4 v = *x;
+            if (j >= shared && j < whole) __builtin_amdgcn_raw_buffer_store_b128(v, ro, j, line, kAuxNT);
+            if (!WHOLE) *x = u32x4{0u, 0u, 0u, 0u};
+        }
+        if (last && whole >= shared && i < rest) __builtin_amdgcn_raw_buffer_store_b32(carry, ro, i, line + whole, 0);
     }
+}
+
+template <bool WHOLE>
+__device__ __forceinline__ void obs_dense_planes(const Lds &L, const Geom &g, uint8_t *obs, RunRange runs, uint8_t *stage)
+{
+    const int quads = (g.PS + 3) / 4 + (WHOLE ? 0 : 1);
+    if (g.PS <= kSmallBoard) stage_runs<WHOLE, 1, true>(L, g, obs, runs, stage);
+    else if (quads <= 64) stage_runs<WHOLE, 1, false>(L, g, obs, runs, stage);
+    else if (quads <= 128) stage_runs<WHOLE, 2, false>(L, g, obs, runs, stage);
+    else if (quads <= 192) stage_runs<WHOLE, 3, false>(L, g, obs, runs, stage);
+    else stage_runs<WHOLE, 4, false>(L, g, obs, runs, stage);
 }
 
 // Padded planes (plane stride g.PS, a multiple of 32 bytes): the dword
@@ -231,7 +266,8 @@ struct EnvIO {
     uint64_t env_id;            // global id (keys every draw)
     uint64_t actor_step;        // actor step index when the tick is not used
     bool use_tick;              // keep the per-env step counter; the actor draws with it
-    int nwv = 1;                // waves of the workgroup sharing the unaligned observation planes
+    int nwv = 1;                // waves of the workgroup sharing the observation planes
+    bool stage = false;         // padded planes may go through the staged writer
 };
 
 // One environment step (or reset / observation) on one wave.  OBSV selects
@@ -312,7 +348,7 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
         wave_sync();
         if (KIND == K_STEP) {
             if (io.use_tick) s.tick += 1;
-            const Turn r = advance(L, g, prm, seed, env_id, s, act);
+            const Turn r = advance(L, g, prm, seed, env_id, s, act, L.armyc);
             write_type = r.write_type;
             grow2 = r.grow2;
             grow50 = r.grow50;
@@ -323,11 +359,10 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
     }
 
     // ---- growth (Section IV-C), state store, army clamp, scoreboard
-    int land_acc[kMaxP];
-    int64_t army_acc[kMaxP];
+    unsigned long long *const tot = reinterpret_cast<unsigned long long *>(L.gbm + 32);    // army totals (SB)
     if (SB) {
-#pragma unroll
-        for (int p = 0; p < kMaxP; ++p) { land_acc[p] = 0; army_acc[p] = 0; }
+        if (lane < kMaxP) tot[lane] = 0ull;
+        wave_sync();
     }
     {
         const int nq = g.S >> 2;
@@ -343,14 +378,11 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
             const uint32_t inc = growing4(o4, t4, grow2, grow50);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int o = (int8_t)(o4 >> (8 * k));
+                [[maybe_unused]] const int o = (int8_t)(o4 >> (8 * k));
                 av[k] = __builtin_elementwise_add_sat(av[k], (int32_t)((inc >> (8 * k)) & 1u));
-                if (SB) {
-#pragma unroll
-                    for (int p = 0; p < kMaxP; ++p) {
-                        if (o == p) { land_acc[p] += 1; army_acc[p] += av[k]; }
-                    }
-                }
+                // one LDS addition per owned cell (a wave sum per player took
+                // 1,100 clocks each)
+                if (SB && o >= 0) atomicAdd(&tot[o], (unsigned long long)(uint32_t)av[k]);
             }
             if (KIND != K_OBSERVE) {
                 st_nt(reinterpret_cast<uint4 *>(ga + q),
@@ -364,55 +396,31 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
             reinterpret_cast<uint32_t *>(L.armyc)[q] = ac;
         }
     }
-    if (SB) {
-        for (int p = 0; p < g.P; ++p) {
-            int lp = 0;
-            int64_t ap = 0;
-#pragma unroll
-            for (int t = 0; t < kMaxP; ++t) if (t == p) { lp = land_acc[t]; ap = army_acc[t]; }
-            lp = (int)wave_sum_u32((uint32_t)lp);
-            ap = wave_sum_i64(ap);
-            if (lane == 0) {
-                io.land[p] = lp;
-                io.army_tot[p] = ap;
-            }
-        }
-    }
-
-    // ---- per-player owned-cell bitmaps (one ballot per player per 64 cells);
-    // with the fused actor also the passable and army > 1 bitmaps
-    // The reads of cells past the map (c >= H*W, up to 63 bytes past a row)
-    // stay inside the env's LDS block; a scalar mask drops their bits.
-    for (int w = 0; w < g.NW; ++w) {
-        const int c = w * 64 + lane;
-        const int rem = g.HW - 64 * w;
-        const uint64_t real = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
-        const int o = L.owner[c];
-        for (int p = 0; p < g.P; ++p) {
-            // (the player index as an opaque scalar: one compare per ballot
-            // rather than a strength-reduced running difference)
-            const uint64_t m = ballot(o == readfirst(p)) & real;
-            if (lane == 0) L.obm[p * 16 + w] = m;
-        }
-        if (ACT) {
-            const uint64_t pm = ballot(L.type[c] != MOUNTAIN) & real;
-            const uint64_t bm = ballot(L.armyc[c] > 1) & real;
-            if (lane == 0) { L.gbm[w] = pm; L.gbm[16 + w] = bm; }
-        }
-    }
+    // ---- per-player owned-cell bitmaps, with the fused actor also the
+    // passable and army > 1 bitmaps
     wave_sync();
+    auto many = [&](int b) { return reinterpret_cast<const uint2 *>(L.armyc)[b]; };
+    cell_bitmaps<ACT>(g, L.owner, L.type, L.obm, L.gbm, L.gbm + 16, lane, kWave, many);
+    wave_sync();
+
+    if (SB && lane < g.P) {
+        int land = 0;
+        for (int w = 0; w < g.NW; ++w) land += __popcll(L.obm[lane * 16 + w]);
+        io.land[lane] = land;
+        io.army_tot[lane] = (int64_t)tot[lane];
+    }
 
     // ---- fog (Section IV-B, team vision R10)
     team_vision(L.obm, L.vis, g);
     wave_sync();
-    // a second wave of the workgroup (FFA with unaligned planes) waits here
+    // the workgroup's further waves, which only write planes, wait here
     // for the state and the vision, then writes the later players' planes
-    if ((OBSV == OBS_STREAM || OBSV == OBS_PADDED) && io.nwv > 1) __syncthreads();
+    if (OBSV != OBS_QUAD && io.nwv > 1) __syncthreads();
 
     // Planes of a multiple of 4 cells: each lane takes 4 cells, computes their
     // bytes of all 8 channel planes in registers and stores them directly
     // (4-byte stores, 256 contiguous bytes per wave store).  Other shapes
-    // realign the same dwords with lane shuffles below.
+    // stage the bytes in LDS.
     if (OBSV == OBS_QUAD || OBSV == OBS_PADDED) {
         if (io.obs != nullptr) {
             // Quads outer: a quad's owner and type bits decoded once for
@@ -425,36 +433,14 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
                     const uint32_t ac = reinterpret_cast<const uint32_t *>(L.armyc)[q];
                     for (int p = 0; p < g.P; ++p) quad_store(L, g, ro, qc, ac, p, q, g.HW);
                 }
+            } else if (io.stage && io.nwv == 1 && g.HW > kOneRound && (g.PS & 127) != 0) {
+                obs_dense_planes<true>(L, g, io.obs, wave_runs(g, 0, 1, ACT), reinterpret_cast<uint8_t *>(L.army));
             } else {
                 obs_padded_planes(L, g, io.obs, 0, io.nwv > 1 ? obs_split(g.P) : g.P);
             }
         }
     } else if (io.obs != nullptr) {
-        // ---- other plane sizes: plane (p, ch) starts m = (8p + ch)·HW mod 4
-        // bytes into a dword.  Channels ch and ch + 4 share m (4·HW is a
-        // multiple of 4), so a player's planes fall into four alignment
-        // classes k = ch mod 4 with m_k = k·HW mod 4 (m_0 = 0).  Lane j
-        // computes quad j's code bytes (code_quad) and army bytes; output
-        // dword j of a plane of class k is the last m_k bytes of quad j-1
-        // (lane j-1's, by a wave shift, or carried over from the previous
-        // round) followed by the first 4-m_k of quad j.  The realignment
-        // moves whole bytes and the channels are bits of a byte, so each
-        // class realigns the code dword once and masks its two channels out
-        // of it.  Dwords that hold bytes of two planes are left to a
-        // byte-wise pass after the loop.
-        obs_stream_planes(L, g, io.obs, 0, io.nwv > 1 ? obs_split(g.P) : g.P);
-        uint32_t *ob = reinterpret_cast<uint32_t *>(io.obs);
-        // the dwords across plane boundaries: at most one per plane start
-        const int n_planes = g.P * 8;
-        for (int i = 1 + lane; i < n_planes; i += kWave) {
-            const uint32_t B0 = (uint32_t)(i * g.HW);
-            if ((B0 & 3u) == 0) continue;
-            const uint32_t b = B0 & ~3u;
-            uint32_t v = 0;
-#pragma nounroll
-            for (int k = 0; k < 4; ++k) v |= obs_byte(L, g, b + k) << (8 * k);
-            ob[b >> 2] = v;
-        }
+        obs_dense_planes<OBSV == OBS_STAGED>(L, g, io.obs, wave_runs(g, 0, io.nwv, ACT), reinterpret_cast<uint8_t *>(L.army));
     }
     wave_sync();
 
@@ -489,10 +475,11 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
 // The scoreboard kernels would spill vector registers to scratch under that
 // limit, and the other plane sizes measured slower at 25x25; they keep the
 // default.
-// NWV = 2 (steps of FFA boards with unaligned planes): a second wave per env
-// writes the observation planes of the players from obs_split(P) on.
+// NWV = 2 (steps of more than 4 players with padded planes): a second wave per
+// env writes the planes of the players from obs_split(P) on.  NWV = 8: up to 8
+// waves share the staged writer's runs (odd planes).
 template <int KIND, int OBSV, bool SB, bool ACT, int NWV>
-__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB || OBSV != OBS_QUAD) ? 1 : 8, 8))) void k_env(EnvArgs a)
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB || (OBSV != OBS_QUAD && OBSV != OBS_STAGED)) ? 1 : 8, 8))) void k_env(EnvArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const int e = (int)xcd_env(blockIdx.x, gridDim.x);
@@ -514,20 +501,21 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB ||
     io.actor_step = a.step_idx;
     io.use_tick = false;
     if (NWV > 1) {
-        static_assert(NWV == 1 || OBSV == OBS_STREAM || OBSV == OBS_PADDED,
-                      "a second wave only shares the unaligned- and padded-plane writers");
-        const int wv = readfirst((int)(threadIdx.x >> 6));
+        static_assert(NWV == 1 || OBSV != OBS_QUAD, "further waves only share the staged and padded-plane writers");
+        const int wv = readfirst((int)(threadIdx.x >> 6)), nwv = OBSV == OBS_PADDED ? 2 : readfirst((int)(blockDim.x >> 6));
         if (wv > 0) {
             // exactly one barrier, matching the one wave 0 passes after the vision
             const Lds L = carve(smem, g);
             __syncthreads();
             if (io.obs != nullptr) {
-                if (OBSV == OBS_STREAM) obs_stream_planes(L, g, io.obs, obs_split(g.P), g.P);
+                if (OBSV == OBS_STREAM || OBSV == OBS_STAGED)
+                    obs_dense_planes<OBSV == OBS_STAGED>(L, g, io.obs, wave_runs(g, wv, nwv, ACT),
+                                                         reinterpret_cast<uint8_t *>(L.army) + (uint32_t)wv * stage_bytes(g));
                 else obs_padded_planes(L, g, io.obs, obs_split(g.P), g.P);
             }
             return;
         }
-        io.nwv = NWV;
+        io.nwv = nwv;
     }
     env_body<KIND, OBSV, SB, ACT>(smem, g, a.prm, a.seed, a.actor_seed, io);
 }
@@ -543,7 +531,7 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB ||
 // two-wave step.
 // One pool env on the calling wave (slot = position in the work list;
 // wave = the wave's index within the env, of nwv).
-template <int KIND, bool ACT>
+template <int KIND, bool ACT, bool STAGE>
 __device__ __forceinline__ void pool_env_d(const PoolArgs &a, uint8_t *smem, const PoolDesc &d, int nwv = 1,
                                            int wave = 0)
 {
@@ -557,7 +545,6 @@ __device__ __forceinline__ void pool_env_d(const PoolArgs &a, uint8_t *smem, con
     g.mode = d.mode;
     g.NW = (g.HW + 63) >> 6;
     g.magic_w = d.magic_w;
-    g.magic_hw = d.magic_hw;
     g.PS = pool_plane_stride(g.HW, g.P);
     uint8_t *obs = a.obs != nullptr ? a.obs + (size_t)d.obs_off16 * 16 : nullptr;
     if (wave > 0) {
@@ -587,13 +574,14 @@ __device__ __forceinline__ void pool_env_d(const PoolArgs &a, uint8_t *smem, con
     io.actor_step = 0;
     io.use_tick = true;
     io.nwv = nwv;
+    io.stage = STAGE && a.stage != 0u;
     env_body<KIND, OBS_PADDED, false, ACT>(smem, g, prm, a.seed, a.actor_seed, io);
 }
 
-template <int KIND, bool ACT>
+template <int KIND, bool ACT, bool STAGE>
 __device__ __forceinline__ void pool_env(const PoolArgs &a, uint8_t *smem, uint32_t slot, int nwv = 1, int wave = 0)
 {
-    pool_env_d<KIND, ACT>(a, smem, a.desc[slot], nwv, wave);
+    pool_env_d<KIND, ACT, STAGE>(a, smem, a.desc[slot], nwv, wave);
 }
 
 // PERSIST = false: one env per wave (per workgroup with NWV = 2), the grid
@@ -609,16 +597,16 @@ __global__ __launch_bounds__(256) void k_pool(PoolArgs a)
     const uint32_t wave = (uint32_t)readfirst((int)(threadIdx.x >> 6));
     if (NWV == 2) {
         const uint32_t slot = a.slot_begin + blockIdx.x;
-        if (slot < a.slot_end) pool_env<KIND, ACT>(a, smem, slot, 2, (int)wave);
+        if (slot < a.slot_end) pool_env<KIND, ACT, false>(a, smem, slot, 2, (int)wave);
         return;
     }
     uint8_t *mine = smem + wave * a.lds_per_wave;
     if (PERSIST) {
         for (uint32_t slot = a.slot_begin + blockIdx.x * a.wpg + wave; slot < a.slot_end; slot += gridDim.x * a.wpg)
-            pool_env<KIND, ACT>(a, mine, slot);
+            pool_env<KIND, ACT, false>(a, mine, slot);
     } else {
         const uint32_t slot = a.slot_begin + xcd_chunk32(blockIdx.x, gridDim.x) * a.wpg + wave;
-        if (slot < a.slot_end) pool_env<KIND, ACT>(a, mine, slot);
+        if (slot < a.slot_end) pool_env<KIND, ACT, true>(a, mine, slot);
     }
 }
 
@@ -633,26 +621,18 @@ __global__ __launch_bounds__(64) void k_sample(SampleArgs a)
     const uint64_t env_id = a.env_base + (uint64_t)e;
     const size_t cell0 = (size_t)e * g.S;
     const uint32_t alive = a.sc[e].alive;
-    // owner and type rows into LDS; army only as the "more than one unit" bit
+    // owner and type rows into LDS; armies clamped to a byte
     const int n16 = g.S >> 4;
     for (int i = lane; i < n16; i += kWave) {
         reinterpret_cast<uint4 *>(L.owner)[i] = reinterpret_cast<const uint4 *>(a.owner + cell0)[i];
         reinterpret_cast<uint4 *>(L.type)[i] = reinterpret_cast<const uint4 *>(a.type + cell0)[i];
     }
-    wave_sync();
-    for (int w = 0; w < g.NW; ++w) {
-        const int c = w * 64 + lane;
-        const bool real = c < g.HW;
-        const int o = real ? (int)L.owner[c] : -1;
-        const bool many = real && a.army[cell0 + c] > 1;
-        for (int p = 0; p < g.P; ++p) {
-            const uint64_t m = ballot(o == readfirst(p));
-            if (lane == 0) L.obm[p * 16 + w] = m;
-        }
-        const uint64_t pm = ballot(real && L.type[c] != MOUNTAIN);
-        const uint64_t bm = ballot(many);
-        if (lane == 0) { L.gbm[w] = pm; L.gbm[16 + w] = bm; }
+    for (int q = lane; q < 4 * n16; q += kWave) {
+        reinterpret_cast<uint32_t *>(L.armyc)[q] = clamp4(reinterpret_cast<const int4 *>(a.army + cell0)[q]);
     }
+    wave_sync();
+    auto many = [&](int b) { return reinterpret_cast<const uint2 *>(L.armyc)[b]; };
+    cell_bitmaps<true>(g, L.owner, L.type, L.obm, L.gbm, L.gbm + 16, lane, kWave, many);
     wave_sync();
     actor_wave(g, L.obm, L.gbm, L.gbm + 16, alive, a.actor_seed, a.step_idx, env_id, a.actions + (size_t)e * g.P);
 }
@@ -660,47 +640,69 @@ __global__ __launch_bounds__(64) void k_sample(SampleArgs a)
 // ---------------------------------------------------------------- launchers
 uint32_t lds_bytes(const Geom &g) { return lds_bytes_for(g.S, g.P); }
 
-int obs_variant(int HW, int P)
+// Waves per env of the staged writer for odd planes: as many as the batch
+// leaves room for, up to a wave per run; two where an env has 10 or more runs
+// (us per step with 1, 2, 4, 8 waves: FFA-8 25x25, 500 envs 28.6, 20.3, 16.0,
+// 14.5; 2,000 envs 31.1, 26.0, 28.1, 34.2; 16,384 envs 143, 129, 152, 228;
+// 2v2 17x19, 500 envs 13.2, 10.5, 9.3, 9.2; 2,000 envs 15.6, 13.7, 16.7, 23.5;
+// 4,096 envs 19.8, 21.8, 26.8, 43.0).
+static int dense_waves(const EnvArgs &a, int n_envs)
 {
-    (void)P;
-    return HW % 4 == 0 ? OBS_QUAD : OBS_STREAM;
+    if (a.obs == nullptr) return 1;
+    const int runs = a.g.P * 8 / planes_per_run(a.g.PS);
+    if (n_envs <= 512) return std::min(8, runs);
+    if (n_envs <= 1024) return std::min(4, runs);
+    return n_envs <= 2048 || (runs >= 10 && n_envs <= 16384) ? 2 : 1;
 }
 
-static int obs_variant(const Geom &g) { return obs_variant(g.HW, g.P); }
+// Aligned planes through the staged writer: where a plane takes more than one
+// round of stores its last line meets the next plane's first one eight planes
+// later, and the line leaves the L2 in parts.  Planes of whole lines have no
+// such line; planes of whole 64-byte halves lose only when the batch's
+// observation is beyond the Infinity Cache.  (us per step, stored where they
+// lie and staged: 1v1 20x20, 65,536 envs 233, 143; 2v2 20x20, 40,000 envs 250,
+// 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 16x17, 8,000 envs 19.0, 20.8; 24x24,
+// 65,536 envs 220, 202; 30,000 envs 66, 73; 16x16, 65,536 envs 80, 98; 28x32,
+// 8,000 envs 31, 36; observations alone of 65,536 envs 1v1 24x24 173, 158.  A
+// reset's maps keep the waves apart, so it gains nothing: 24x24 177, 238.)
+static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
+{
+    if (kind == K_RESET || a.obs == nullptr || a.g.HW <= kOneRound || a.g.PS % 128 == 0) return false;
+    const uint64_t bytes = (uint64_t)n_envs * (uint64_t)(a.g.P * 8 * a.g.PS);
+    return bytes >= (a.g.PS % 64 != 0 ? 30000000ull : 400000000ull);
+}
 
 template <int KIND, bool SB, bool ACT>
 static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
 {
     const dim3 grid((unsigned)n_envs), block(kWave);
-    const uint32_t lds = lds_bytes(a.g);
+    const uint32_t lds = lds_bytes(a.g), lds_dense = lds - 4u * (uint32_t)a.g.S + stage_bytes(a.g);
     if (a.g.PS != a.g.HW) {
         // planes padded to 32 bytes: the dword writer for every shape; more
-        // than 4 players share it between two waves, as the unaligned writer
+        // than 4 players share it between two waves
         if constexpr (KIND == K_STEP) {
             if (a.g.P > 4 && a.obs != nullptr && n_envs <= 16384) {
                 hipLaunchKernelGGL((k_env<KIND, OBS_PADDED, SB, ACT, 2>), grid, dim3(2 * kWave), lds, stream, a);
                 return hipGetLastError();
             }
         }
-        hipLaunchKernelGGL((k_env<KIND, OBS_PADDED, SB, ACT, 1>), grid, block, lds, stream, a);
+        if (stage_whole(a, n_envs, KIND))
+            hipLaunchKernelGGL((k_env<KIND, OBS_STAGED, SB, ACT, 1>), grid, block, lds_dense, stream, a);
+        else
+            hipLaunchKernelGGL((k_env<KIND, OBS_PADDED, SB, ACT, 1>), grid, block, lds, stream, a);
         return hipGetLastError();
     }
-    switch (obs_variant(a.g)) {
-    case OBS_QUAD: hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, lds, stream, a); break;
-    default:
-        // steps of boards with more than 4 players and unaligned planes: the
-        // observation (most of the work) is shared by two waves per env when
-        // the batch leaves room for the second wave (measured: FFA-8 25x25
-        // with 16,384 envs 249 -> 226 us; 17x19 with 32,768 envs a little
-        // slower, so larger batches keep one wave)
-        if constexpr (KIND == K_STEP) {
-            if (a.g.P > 4 && a.obs != nullptr && n_envs <= 16384) {
-                hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 2>), grid, dim3(2 * kWave), lds, stream, a);
-                break;
-            }
-        }
-        hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 1>), grid, block, lds, stream, a);
-        break;
+    const int nwv = KIND == K_RESET ? 1 : dense_waves(a, n_envs);
+    const bool staged = a.g.HW % 4 != 0;
+    if (staged && nwv > 1) {
+        if constexpr (KIND != K_RESET)
+            hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 8>), grid, dim3(kWave * nwv), lds_dense + (uint32_t)(nwv - 1) * stage_bytes(a.g), stream, a);
+    } else if (staged) {
+        hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 1>), grid, block, lds_dense, stream, a);
+    } else if (stage_whole(a, n_envs, KIND)) {
+        hipLaunchKernelGGL((k_env<KIND, OBS_STAGED, SB, ACT, 1>), grid, block, lds_dense, stream, a);
+    } else {
+        hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, lds, stream, a);
     }
     return hipGetLastError();
 }
@@ -769,6 +771,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UNI ? 8 : 1,
     a.slot_end = r.n_envs;
     a.wpg = 1;
     a.lds_per_wave = 0;
+    a.stage = 0;
     a.actor = r.actor;
     a.desc = reinterpret_cast<const PoolDesc *>(arena + r.off_desc);
     a.sc = reinterpret_cast<EnvScalars *>(arena + r.off_sc);
@@ -787,9 +790,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UNI ? 8 : 1,
         d.obs_off16 = slot * r.obs16_per_env;
         d.act_off = slot * d.P;
         d.env = slot;
-        pool_env_d<K_STEP, true>(a, smem, d);
+        pool_env_d<K_STEP, true, false>(a, smem, d);
     } else {
-        pool_env<K_STEP, true>(a, smem, slot);
+        pool_env<K_STEP, true, false>(a, smem, slot);
     }
 }
 
