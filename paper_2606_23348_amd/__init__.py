@@ -185,7 +185,13 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int | None:
     if stream is None:
+        # the calling thread's current stream of its current device.  The raw
+        # handle is asked for where torch has it: building a Stream object for
+        # each call took 2.9 of a small step's 7.8 us on the host (the handle 0.4)
         import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return getattr(stream, "cuda_stream", stream)
 
