@@ -539,15 +539,21 @@ __device__ void actor_wave(const Geom &g, const uint64_t *own, const uint64_t *p
 // What a step does before growth: the moves, the turn counter, terminal and
 // rewards (Section III, Section IV-E; reading R11), the next map where a
 // finished game restarts.  Executed by one wave; `act` is lane p's action,
-// `claim` S bytes of LDS for the moves.
+// `claim` S bytes of LDS for the moves, src.map() the generator's settings.
+struct MapArgs {
+    GenParamsDev prm;
+    uint64_t seed, env_id;
+};
+
 struct Turn {
     bool write_type = false;     // the type row (and the general cells) changed
     bool grow2 = false, grow50 = false, done = false;
     uint32_t win = 0, lose = 0;  // player masks
 };
 
-__device__ __forceinline__ Turn advance(const Lds &L, const Geom &g, const GenParamsDev &prm, uint64_t seed,
-                                        uint64_t env_id, EnvScalars &s, int32_t act, uint8_t *claim)
+template <class Src>
+__device__ __forceinline__ Turn advance(const Lds &L, const Geom &g, const Src &src, EnvScalars &s, int32_t act,
+                                        uint8_t *claim)
 {
     Turn r;
     if (s.finished) {
@@ -573,8 +579,9 @@ __device__ __forceinline__ Turn advance(const Lds &L, const Geom &g, const GenPa
         if (__popc(alive) == 1) { r.done = true; r.win = alive; }
     }
     if (r.done) {
-        if (prm.auto_reset) {
-            mapgen_wave(L, g, prm, seed, env_id, s.episode + 1u, s);
+        const MapArgs m = src.map();
+        if (m.prm.auto_reset) {
+            mapgen_wave(L, g, m.prm, m.seed, m.env_id, s.episode + 1u, s);
             r.write_type = true;
             r.grow2 = r.grow50 = false;
         } else {

@@ -101,6 +101,28 @@ struct GenParamsDev {
     int generator, dmax, radius;     // official generator: BFS spacing cap, castle radius
 };
 
+// ---------------------------------------------------------------- read-only records
+// A record that no launch in flight writes (kernel arguments, a group's
+// record), read again from memory at this point.  Held from the kernel's
+// start, the step's arguments are about 50 scalar registers live across the
+// moves and the map generator, and the spills of what does not fit are vector
+// instructions; a scalar load at each place of use is not (scalar spills of
+// the 1v1 step 89 -> 38; us per step: 10x10 1v1, 65,536 envs 81.1 -> 79.0;
+// mixed pool of 131,072 envs 286 -> 283; resets of 24x24 206 -> 200).
+template <class T>
+__device__ __forceinline__ const T &fresh(const void *p)
+{
+    uint64_t v = reinterpret_cast<uint64_t>(p);
+    asm volatile("" : "+s"(v));
+    return *(const T *)(const __attribute__((address_space(4))) T *)v;
+}
+
+template <class T>
+__device__ __forceinline__ const T &fresh_args()
+{
+    return fresh<T>((const void *)__builtin_amdgcn_kernarg_segment_ptr());
+}
+
 // ---------------------------------------------------------------- wave ops
 // Make LDS writes of one lane visible to the other lanes of the same wave and
 // keep the compiler from moving LDS accesses across this point.  What it

@@ -693,6 +693,16 @@ constexpr int kRollExtra = 8 * 56 + 32 + 48 + 32 + 16 + 2 * 96;
 
 __host__ __device__ inline uint32_t roll_lds_bytes(int S, int P) { return feat_lds_bytes(S, P) + (uint32_t)(21 * S + kRollExtra); }
 
+// The next map's settings, read where a game ends (see fresh).
+struct RolloutSrc {
+    int e;
+    __device__ __forceinline__ MapArgs map() const
+    {
+        const RolloutArgs &a = fresh_args<RolloutArgs>();
+        return {a.prm, a.seed, a.env_base + (uint64_t)e};
+    }
+};
+
 template <bool SHIFT, int G, int R>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
 {
@@ -808,7 +818,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         }
         // ---- wave 0 plays the turn on the live board, the others write
         if (wv == 0) {
-            const Turn r = advance(rl.L, g, a.prm, a.seed, env_id, s, lane < P ? rl.act[lane] : 0, rl.claim);
+            const Turn r = advance(rl.L, g, RolloutSrc{e}, s, lane < P ? rl.act[lane] : 0, rl.claim);
             if (r.grow2 || r.grow50) {
                 for (int q = lane; q < nq; q += kWave) {
                     const uint32_t inc = growing4(reinterpret_cast<const uint32_t *>(rl.L.owner)[q],

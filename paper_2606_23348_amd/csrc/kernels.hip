@@ -264,6 +264,7 @@ struct EnvIO {
     int32_t *land;              // scoreboard (SB)
     int64_t *army_tot;
     uint64_t env_id;            // global id (keys every draw)
+    uint64_t actor_seed;
     uint64_t actor_step;        // actor step index when the tick is not used
     bool use_tick;              // keep the per-env step counter; the actor draws with it
     int nwv = 1;                // waves of the workgroup sharing the observation planes
@@ -272,24 +273,25 @@ struct EnvIO {
 
 // One environment step (or reset / observation) on one wave.  OBSV selects
 // the observation writer and layout at compile time (OBS_PADDED for the
-// mixed shapes of a pool).
-template <int KIND, int OBSV, bool SB, bool ACT>
-__device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const GenParamsDev &prm, uint64_t seed,
-                                         uint64_t actor_seed, const EnvIO &io)
+// mixed shapes of a pool).  src.io() and src.map() read the env's arguments
+// where they are needed (see fresh).
+template <int KIND, int OBSV, bool SB, bool ACT, class Src>
+__device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Src &src)
 {
     const int lane = lane_id();
     const Lds L = carve(smem, g);
-    const uint64_t env_id = io.env_id;
 
     EnvScalars s;
     bool write_type = false, grow2 = false, grow50 = false, done = false;
     uint32_t win = 0, lose = 0;
 
     if (KIND == K_RESET) {
-        mapgen_wave(L, g, prm, seed, env_id, 0u, s);
+        const MapArgs m = src.map();
+        mapgen_wave(L, g, m.prm, m.seed, m.env_id, 0u, s);
         s.tick = 0;
         write_type = true;
     } else {
+        const EnvIO io = src.io();
         s = *io.sc;
         const int n16 = g.S >> 4;
         const uint4 *go = reinterpret_cast<const uint4 *>(io.owner);
@@ -320,7 +322,7 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
             if (io.next_actions != nullptr) {
                 const uint64_t tick = (uint64_t)s.tick + ((KIND == K_STEP && io.use_tick) ? 1u : 0u);
                 uint64_t w0, w1;
-                actor_block(actor_seed, env_id, io.use_tick ? tick : io.actor_step, w0, w1);
+                actor_block(io.actor_seed, io.env_id, io.use_tick ? tick : io.actor_step, w0, w1);
                 if ((lane & 31) == 0) {
                     uint64_t *pb = L.gbm + 52 + (lane >> 4);
                     pb[0] = w0;
@@ -348,7 +350,7 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
         wave_sync();
         if (KIND == K_STEP) {
             if (io.use_tick) s.tick += 1;
-            const Turn r = advance(L, g, prm, seed, env_id, s, act, L.armyc);
+            const Turn r = advance(L, g, src, s, act, L.armyc);
             write_type = r.write_type;
             grow2 = r.grow2;
             grow50 = r.grow50;
@@ -357,6 +359,8 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
             lose = r.lose;
         }
     }
+
+    const EnvIO io = src.io();
 
     // ---- growth (Section IV-C), state store, army clamp, scoreboard
     unsigned long long *const tot = reinterpret_cast<unsigned long long *>(L.gbm + 32);    // army totals (SB)
@@ -446,7 +450,7 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
 
     // ---- fused random actor for the next step, on the final state
     if (ACT && io.next_actions != nullptr)
-        actor_wave(g, L.obm, L.gbm, L.gbm + 16, s.alive, actor_seed, io.use_tick ? s.tick : io.actor_step, env_id,
+        actor_wave(g, L.obm, L.gbm, L.gbm + 16, s.alive, io.actor_seed, io.use_tick ? s.tick : io.actor_step, io.env_id,
                    io.next_actions, KIND != K_RESET ? L.gbm + 52 : nullptr);
 
     // ---- rewards, done, scalars
@@ -478,46 +482,65 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Gen
 // NWV = 2 (steps of more than 4 players with padded planes): a second wave per
 // env writes the planes of the players from obs_split(P) on.  NWV = 8: up to 8
 // waves share the staged writer's runs (odd planes).
+struct EnvSrc {
+    int e, nwv;
+
+    __device__ __forceinline__ EnvIO io() const
+    {
+        const EnvArgs &a = fresh_args<EnvArgs>();
+        const size_t cell0 = (size_t)e * a.g.S, player0 = (size_t)e * a.g.P;
+        EnvIO io;
+        io.sc = a.sc + e;
+        io.owner = a.owner + cell0;
+        io.type = a.type + cell0;
+        io.army = a.army + cell0;
+        io.actions = a.actions + player0;
+        io.next_actions = a.next_actions + player0;
+        io.rewards = a.rewards + player0;
+        io.done = a.dones + e;
+        io.obs = a.obs != nullptr ? a.obs + (size_t)e * (size_t)(a.g.P * 8 * a.g.PS) : nullptr;
+        io.land = a.land + player0;
+        io.army_tot = a.army_tot + player0;
+        io.env_id = a.env_base + (uint64_t)e;
+        io.actor_seed = a.actor_seed;
+        io.actor_step = a.step_idx;
+        io.use_tick = false;
+        io.nwv = nwv;
+        return io;
+    }
+
+    __device__ __forceinline__ MapArgs map() const
+    {
+        const EnvArgs &a = fresh_args<EnvArgs>();
+        return {a.prm, a.seed, a.env_base + (uint64_t)e};
+    }
+};
+
 template <int KIND, int OBSV, bool SB, bool ACT, int NWV>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB || (OBSV != OBS_QUAD && OBSV != OBS_STAGED)) ? 1 : 8, 8))) void k_env(EnvArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
-    const int e = (int)xcd_env(blockIdx.x, gridDim.x);
     const Geom g = a.g;
-    const size_t cell0 = (size_t)e * g.S;
-    EnvIO io;
-    io.sc = a.sc + e;
-    io.owner = a.owner + cell0;
-    io.type = a.type + cell0;
-    io.army = a.army + cell0;
-    io.actions = a.actions + (size_t)e * g.P;
-    io.next_actions = a.next_actions + (size_t)e * g.P;
-    io.rewards = a.rewards + (size_t)e * g.P;
-    io.done = a.dones + e;
-    io.obs = a.obs != nullptr ? a.obs + (size_t)e * (size_t)(g.P * 8 * g.PS) : nullptr;
-    io.land = a.land + (size_t)e * g.P;
-    io.army_tot = a.army_tot + (size_t)e * g.P;
-    io.env_id = a.env_base + (uint64_t)e;
-    io.actor_step = a.step_idx;
-    io.use_tick = false;
+    EnvSrc src{(int)xcd_env(blockIdx.x, gridDim.x), 1};
     if (NWV > 1) {
         static_assert(NWV == 1 || OBSV != OBS_QUAD, "further waves only share the staged and padded-plane writers");
-        const int wv = readfirst((int)(threadIdx.x >> 6)), nwv = OBSV == OBS_PADDED ? 2 : readfirst((int)(blockDim.x >> 6));
+        const int wv = readfirst((int)(threadIdx.x >> 6));
+        src.nwv = OBSV == OBS_PADDED ? 2 : readfirst((int)(blockDim.x >> 6));
         if (wv > 0) {
             // exactly one barrier, matching the one wave 0 passes after the vision
             const Lds L = carve(smem, g);
             __syncthreads();
-            if (io.obs != nullptr) {
+            uint8_t *obs = src.io().obs;
+            if (obs != nullptr) {
                 if (OBSV == OBS_STREAM || OBSV == OBS_STAGED)
-                    obs_dense_planes<OBSV == OBS_STAGED>(L, g, io.obs, wave_runs(g, wv, nwv, ACT),
+                    obs_dense_planes<OBSV == OBS_STAGED>(L, g, obs, wave_runs(g, wv, src.nwv, ACT),
                                                          reinterpret_cast<uint8_t *>(L.army) + (uint32_t)wv * stage_bytes(g));
-                else obs_padded_planes(L, g, io.obs, obs_split(g.P), g.P);
+                else obs_padded_planes(L, g, obs, obs_split(g.P), g.P);
             }
             return;
         }
-        io.nwv = nwv;
     }
-    env_body<KIND, OBSV, SB, ACT>(smem, g, a.prm, a.seed, a.actor_seed, io);
+    env_body<KIND, OBSV, SB, ACT>(smem, g, src);
 }
 
 // ---------------------------------------------------------------- batched pool (mixed shapes)
@@ -531,11 +554,56 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB ||
 // two-wave step.
 // One pool env on the calling wave (slot = position in the work list;
 // wave = the wave's index within the env, of nwv).
-template <int KIND, bool ACT, bool STAGE>
-__device__ __forceinline__ void pool_env_d(const PoolArgs &a, uint8_t *smem, const PoolDesc &d, int nwv = 1,
+// Args: fresh() of the launch's arguments as PoolArgs.
+template <class Args, bool STAGE>
+struct PoolSrc {
+    Args args;
+    PoolDesc d;
+    int nwv;
+
+    __device__ __forceinline__ EnvIO io() const
+    {
+        const PoolArgs &a = args.fresh();
+        EnvIO io;
+        io.sc = a.sc + d.env;
+        io.owner = a.owner + d.cell_off;
+        io.type = a.type + d.cell_off;
+        io.army = a.army + d.cell_off;
+        io.actions = a.actions + d.act_off;
+        io.next_actions = a.actor ? a.actions + d.act_off : nullptr;
+        io.rewards = a.rewards + d.act_off;
+        io.done = a.dones + d.env;
+        io.obs = a.obs != nullptr ? a.obs + (size_t)d.obs_off16 * 16 : nullptr;
+        io.land = nullptr;
+        io.army_tot = nullptr;
+        io.env_id = a.env_base + d.env;
+        io.actor_seed = a.actor_seed;
+        io.actor_step = 0;
+        io.use_tick = true;
+        io.nwv = nwv;
+        io.stage = STAGE && a.stage != 0u;
+        return io;
+    }
+
+    __device__ __forceinline__ MapArgs map() const
+    {
+        const PoolArgs &a = args.fresh();
+        MapArgs m{a.prm, a.seed, a.env_base + d.env};
+        m.prm.cmin = d.cmin;
+        m.prm.cmax = d.cmax;
+        m.prm.dmin = d.dmin;
+        return m;
+    }
+};
+
+struct PoolLaunch {
+    __device__ __forceinline__ const PoolArgs &fresh() const { return fresh_args<PoolArgs>(); }
+};
+
+template <int KIND, bool ACT, bool STAGE, class Args>
+__device__ __forceinline__ void pool_env_d(const Args &args, uint8_t *smem, const PoolDesc &d, int nwv = 1,
                                            int wave = 0)
 {
-    const uint32_t e = d.env;
     Geom g;
     g.H = d.H;
     g.W = d.W;
@@ -546,42 +614,16 @@ __device__ __forceinline__ void pool_env_d(const PoolArgs &a, uint8_t *smem, con
     g.NW = (g.HW + 63) >> 6;
     g.magic_w = d.magic_w;
     g.PS = pool_plane_stride(g.HW, g.P);
-    uint8_t *obs = a.obs != nullptr ? a.obs + (size_t)d.obs_off16 * 16 : nullptr;
+    const PoolSrc<Args, STAGE> src{args, d, nwv};
     if (wave > 0) {
         // exactly one barrier, matching the one wave 0 passes after the vision
         const Lds L = carve(smem, g);
         __syncthreads();
+        uint8_t *obs = src.io().obs;
         if (obs != nullptr) obs_padded_planes(L, g, obs, obs_split(g.P), g.P);
         return;
     }
-    GenParamsDev prm = a.prm;
-    prm.cmin = d.cmin;
-    prm.cmax = d.cmax;
-    prm.dmin = d.dmin;
-    EnvIO io;
-    io.sc = a.sc + e;
-    io.owner = a.owner + d.cell_off;
-    io.type = a.type + d.cell_off;
-    io.army = a.army + d.cell_off;
-    io.actions = a.actions + d.act_off;
-    io.next_actions = a.actor ? a.actions + d.act_off : nullptr;
-    io.rewards = a.rewards + d.act_off;
-    io.done = a.dones + e;
-    io.obs = obs;
-    io.land = nullptr;
-    io.army_tot = nullptr;
-    io.env_id = a.env_base + e;
-    io.actor_step = 0;
-    io.use_tick = true;
-    io.nwv = nwv;
-    io.stage = STAGE && a.stage != 0u;
-    env_body<KIND, OBS_PADDED, false, ACT>(smem, g, prm, a.seed, a.actor_seed, io);
-}
-
-template <int KIND, bool ACT, bool STAGE>
-__device__ __forceinline__ void pool_env(const PoolArgs &a, uint8_t *smem, uint32_t slot, int nwv = 1, int wave = 0)
-{
-    pool_env_d<KIND, ACT, STAGE>(a, smem, a.desc[slot], nwv, wave);
+    env_body<KIND, OBS_PADDED, false, ACT>(smem, g, src);
 }
 
 // PERSIST = false: one env per wave (per workgroup with NWV = 2), the grid
@@ -597,16 +639,16 @@ __global__ __launch_bounds__(256) void k_pool(PoolArgs a)
     const uint32_t wave = (uint32_t)readfirst((int)(threadIdx.x >> 6));
     if (NWV == 2) {
         const uint32_t slot = a.slot_begin + blockIdx.x;
-        if (slot < a.slot_end) pool_env<KIND, ACT, false>(a, smem, slot, 2, (int)wave);
+        if (slot < a.slot_end) pool_env_d<KIND, ACT, false>(PoolLaunch{}, smem, a.desc[slot], 2, (int)wave);
         return;
     }
     uint8_t *mine = smem + wave * a.lds_per_wave;
     if (PERSIST) {
         for (uint32_t slot = a.slot_begin + blockIdx.x * a.wpg + wave; slot < a.slot_end; slot += gridDim.x * a.wpg)
-            pool_env<KIND, ACT, false>(a, mine, slot);
+            pool_env_d<KIND, ACT, false>(PoolLaunch{}, mine, a.desc[slot]);
     } else {
         const uint32_t slot = a.slot_begin + xcd_chunk32(blockIdx.x, gridDim.x) * a.wpg + wave;
-        if (slot < a.slot_end) pool_env<KIND, ACT, true>(a, mine, slot);
+        if (slot < a.slot_end) pool_env_d<KIND, ACT, true>(PoolLaunch{}, mine, a.desc[slot]);
     }
 }
 
@@ -744,6 +786,32 @@ hipError_t launch_observe(const EnvArgs &a, int n_envs, hipStream_t stream)
 // 1v1 groups fit 8 in LDS); the other keeps the default budget, since the
 // LDS of its largest board limits it to fewer waves anyway (served mix
 // 401.5 -> 410 M frames/s without the 8-wave budget's spills).
+struct ServeLaunchOf {
+    const ServeReq *req;
+
+    __device__ __forceinline__ PoolArgs fresh() const
+    {
+        const ServeReq &r = gen::fresh<ServeReq>(req);
+        uint8_t *const arena = fresh_args<ServeLaunch>().arena;
+        PoolArgs a;
+        a.prm = r.prm;
+        a.seed = r.seed;
+        a.env_base = r.env_base;
+        a.actor_seed = r.actor_seed;
+        a.actor = r.actor;
+        a.stage = 0;
+        a.sc = reinterpret_cast<EnvScalars *>(arena + r.off_sc);
+        a.owner = reinterpret_cast<int8_t *>(arena + r.off_owner);
+        a.type = arena + r.off_type;
+        a.army = reinterpret_cast<int32_t *>(arena + r.off_army);
+        a.actions = reinterpret_cast<int32_t *>(arena + r.off_actions);
+        a.rewards = reinterpret_cast<int32_t *>(arena + r.off_rewards);
+        a.dones = arena + r.off_dones;
+        a.obs = r.off_obs != ~0ull ? arena + r.off_obs : nullptr;
+        return a;
+    }
+};
+
 template <bool UNI>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UNI ? 8 : 1, 8))) void k_serve(ServeLaunch la)
 {
@@ -761,27 +829,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UNI ? 8 : 1,
     const ServeReq &r = la.groups[la.idx[lo]];
     const uint32_t slot = b - la.first[lo];
     if (slot >= r.n_envs) return;
-    PoolArgs a;
-    a.prm = r.prm;
-    a.seed = r.seed;
-    a.env_base = r.env_base;
-    a.actor_seed = r.actor_seed;
-    a.n_envs = r.n_envs;
-    a.slot_begin = 0;
-    a.slot_end = r.n_envs;
-    a.wpg = 1;
-    a.lds_per_wave = 0;
-    a.stage = 0;
-    a.actor = r.actor;
-    a.desc = reinterpret_cast<const PoolDesc *>(arena + r.off_desc);
-    a.sc = reinterpret_cast<EnvScalars *>(arena + r.off_sc);
-    a.owner = reinterpret_cast<int8_t *>(arena + r.off_owner);
-    a.type = arena + r.off_type;
-    a.army = reinterpret_cast<int32_t *>(arena + r.off_army);
-    a.actions = reinterpret_cast<int32_t *>(arena + r.off_actions);
-    a.rewards = reinterpret_cast<int32_t *>(arena + r.off_rewards);
-    a.dones = arena + r.off_dones;
-    a.obs = r.off_obs != ~0ull ? arena + r.off_obs : nullptr;
     if (UNI) {
         // every env of a uniform group has the template's shape and
         // settings: its descriptor follows from the slot
@@ -790,9 +837,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(UNI ? 8 : 1,
         d.obs_off16 = slot * r.obs16_per_env;
         d.act_off = slot * d.P;
         d.env = slot;
-        pool_env_d<K_STEP, true, false>(a, smem, d);
+        pool_env_d<K_STEP, true, false>(ServeLaunchOf{&r}, smem, d);
     } else {
-        pool_env<K_STEP, true, false>(a, smem, slot);
+        pool_env_d<K_STEP, true, false>(ServeLaunchOf{&r}, smem, reinterpret_cast<const PoolDesc *>(arena + r.off_desc)[slot]);
     }
 }
 
