@@ -714,6 +714,22 @@ static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
     return bytes >= (a.g.PS % 64 != 0 ? 30000000ull : 400000000ull);
 }
 
+// LDS of the dword writers by one wave: with more than 4 players and planes of more than
+// one line a batch is held to 16 waves a CU, since the lines that two planes
+// share leave the L2 in parts when the 32 waves that would fit all store
+// (us per step with 32 and 16 waves: FFA-8 12x12, 32,768 envs 92, 75; FFA-8
+// 12x13 108, 86; FFA-8 14x14, 16,384 envs 68, 63; FFA-6 14x14, 32,768 envs 93,
+// 71; FFA-5 14x14 74, 64; FFA-8 12x12 padded, 32,768 envs 94, 77; planes within a line or fewer players need the
+// waves: FFA-8 10x10 62, 74; 2v2 14x14, 50,000 envs 73, 88; below 8,192 envs
+// the same either way).
+constexpr uint32_t kSixteenWavesLds = 10240;
+
+static uint32_t dword_lds(const EnvArgs &a, int n_envs, uint32_t lds)
+{
+    const bool held = a.obs != nullptr && a.g.P > 4 && a.g.HW > 128 && n_envs >= 8192;
+    return held ? std::max(lds, kSixteenWavesLds) : lds;
+}
+
 template <int KIND, bool SB, bool ACT>
 static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
 {
@@ -731,7 +747,7 @@ static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
         if (stage_whole(a, n_envs, KIND))
             hipLaunchKernelGGL((k_env<KIND, OBS_STAGED, SB, ACT, 1>), grid, block, lds_dense, stream, a);
         else
-            hipLaunchKernelGGL((k_env<KIND, OBS_PADDED, SB, ACT, 1>), grid, block, lds, stream, a);
+            hipLaunchKernelGGL((k_env<KIND, OBS_PADDED, SB, ACT, 1>), grid, block, dword_lds(a, n_envs, lds), stream, a);
         return hipGetLastError();
     }
     const int nwv = KIND == K_RESET ? 1 : dense_waves(a, n_envs);
@@ -744,7 +760,7 @@ static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
     } else if (stage_whole(a, n_envs, KIND)) {
         hipLaunchKernelGGL((k_env<KIND, OBS_STAGED, SB, ACT, 1>), grid, block, lds_dense, stream, a);
     } else {
-        hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, lds, stream, a);
+        hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, dword_lds(a, n_envs, lds), stream, a);
     }
     return hipGetLastError();
 }

@@ -94,6 +94,13 @@ def test_scoreboard_and_separate_actor(H, W, mode, P):
     check(H, W, mode, P, 40, 12, scoreboard=True, fused=False)
 
 
+@pytest.mark.parametrize("H,W,P,E,padded", [(12, 12, 8, 8192, False), (12, 11, 5, 8191, False), (8, 16, 8, 8192, False),
+                                            (11, 12, 5, 8192, False), (13, 13, 6, 16400, True)])
+def test_more_than_four_players_in_large_batches(H, W, P, E, padded):
+    """Aligned planes of more than 128 cells, 8,192 envs and more: fewer waves a CU."""
+    check(H, W, 2, P, E, 1, padded=padded)
+
+
 def test_pool_from_64_megabytes():
     """A pool large enough for the staged writer (boards of 16x16 to 25x25, all
     modes): every env against the oracle, two steps."""
