@@ -292,16 +292,18 @@ __device__ __forceinline__ float4 bytes_to_f(uint32_t m)
 }
 
 // Channel ch (wave-uniform) of player p at the quads of cells c[0], c[1], ...
-// (any cell with ANY, else multiples of 4): the channel is decided once for all R quads of a lane,
-// whose LDS reads are then in flight together.
-template <bool ANY, int R>
-__device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int p, int ch, const int (&c)[R], float4 (&x)[R])
+// (any cell with ANY, else multiples of 4; the second half of them of player
+// p + 1 with PAIR, or of p again after the last): the channel is decided once
+// for all R quads of a lane, whose LDS reads are then in flight together.
+template <bool ANY, bool PAIR, int R>
+__device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int p0, int ch, const int (&c)[R], float4 (&x)[R])
 {
     const Geom &g = f.g;
     const int S = g.S;
+    auto player = [&](int k) { return PAIR && k >= R / 2 ? min(p0 + 1, g.P - 1) : p0; };
     auto each = [&](auto &&value) {
 #pragma unroll
-        for (int k = 0; k < R; ++k) x[k] = value(c[k]);
+        for (int k = 0; k < R; ++k) x[k] = value(c[k], player(k));
     };
     if (ch >= 24) {
         // army of the frame of turn t - k minus that of t - k - 1 on the
@@ -309,47 +311,48 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
         const int k = ch - (ch >= 24 + kHist ? 24 + kHist : 24);
         const uint8_t *mask = ch >= 24 + kHist ? F.foe : F.own;
         const int o0 = ((f.t - k) & 7) * S, o1 = ((f.t - k - 1) & 7) * S;
-        each([&](int q) {
+        each([&](int q, int p) {
             const int4 u = keep4(ld16<ANY>(F.farmy + o0 + q), ld4<ANY>(mask + o0 + q), p), v = keep4(ld16<ANY>(F.farmy + o1 + q), ld4<ANY>(mask + o1 + q), p);
             return make_float4((float)(u.x - v.x), (float)(u.y - v.y), (float)(u.z - v.z), (float)(u.w - v.w));
         });
         return;
     }
-    const uint8_t *bits = F.bits + p * S;
     const int now = f.slot * S;
     switch (ch) {
     case 0: case 1: case 2: case 3: {
-        const uint8_t *mask = ch == 1 ? F.own + now : ch == 2 ? F.foe + now : bits;
-        const int bit = ch == 0 ? (int)B_NOW : ch == 3 ? (int)B_NEUTRAL : p;
-        each([&](int q) {
-            const int4 v = keep4(ld16<ANY>(F.farmy + now + q), ld4<ANY>(mask + q), bit);
+        const uint8_t *mask = ch == 1 ? F.own + now : ch == 2 ? F.foe + now : F.bits;
+        const bool own = ch == 1 || ch == 2;
+        each([&](int q, int p) {
+            const int4 v = keep4(ld16<ANY>(F.farmy + now + q), ld4<ANY>(mask + (own ? 0 : p * S) + q), own ? p : ch == 0 ? (int)B_NOW : (int)B_NEUTRAL);
             return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
         });
         break;
     }
     case 4: case 5: case 6: case 7: case 8:
-        each([&](int q) { return bytes_to_f((ld4<ANY>(bits + q) >> (ch - 4)) & kOnes); });
+        each([&](int q, int p) { return bytes_to_f((ld4<ANY>(F.bits + p * S + q) >> (ch - 4)) & kOnes); });
         break;
     case 10: case 11: {
         const uint8_t *mask = ch == 10 ? F.own + now : F.foe + now;
-        each([&](int q) { return bytes_to_f((ld4<ANY>(mask + q) >> p) & kOnes); });
+        each([&](int q, int p) { return bytes_to_f((ld4<ANY>(mask + q) >> p) & kOnes); });
         break;
     }
     case 9: case 12: case 13: {
         const uint32_t in = ch == 9 ? 0u : kOnes, all = ch == 12 ? kOnes : 0u;     // not visible; every such cell
-        each([&](int q) {
-            const uint32_t b = ld4<ANY>(bits + q);
+        each([&](int q, int p) {
+            const uint32_t b = ld4<ANY>(F.bits + p * S + q);
             return bytes_to_f(((b >> B_NOW) ^ in) & ((b >> B_PLACE) | all) & kOnes);
         });
         break;
     }
     case 14: case 15: case 16: case 17: case 18: case 19: {
-        const float v = F.flat[p * 6 + ch - 14];
-        each([&](int) { return make_float4(v, v, v, v); });
+        each([&](int, int p) {
+            const float v = F.flat[p * 6 + ch - 14];
+            return make_float4(v, v, v, v);
+        });
         break;
     }
     case 20:
-        each([&](int q) {
+        each([&](int q, int p) {
             const int4 v = ld16<ANY>(F.last + p * S + q);
             return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
         });
@@ -358,8 +361,8 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
         // age of the sightings before, not visible now; gaps beyond the
         // table are computed in a loop of their own (one copy of log1p)
         bool far = false;
-        each([&](int q) {
-            const uint32_t b = ld4<ANY>(bits + q), m = ~(b >> B_NOW) & (b >> B_ENEMY);
+        each([&](int q, int p) {
+            const uint32_t b = ld4<ANY>(F.bits + p * S + q), m = ~(b >> B_NOW) & (b >> B_ENEMY);
             const int4 lt = ld16<ANY>(F.lturn + p * S + q);
             float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             auto age = [&](uint32_t bit, int32_t then, float &to) {
@@ -385,7 +388,8 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
                 int q = 0;
 #pragma unroll
                 for (int k = 0; k < R; ++k) q = n >> 2 == k ? max(c[k] + (n & 3), 0) : q;
-                const uint32_t b = bits[q];
+                const int p = player(n >> 2);
+                const uint32_t b = F.bits[p * S + q];
                 const uint32_t dt = (uint32_t)(f.t - F.lturn[p * S + q]);
                 if (((b >> B_NOW) & 1u) || !((b >> B_ENEMY) & 1u) || dt < (uint32_t)kAgeTable) continue;
                 const float v = (float)(log1p((double)(int32_t)dt) / 5.0);
@@ -402,7 +406,7 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
     }
     default: {
         const float *v = ch == 22 ? F.cx : F.cy;
-        each([&](int q) {
+        each([&](int q, int p) {
             int r[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -437,36 +441,15 @@ __device__ __forceinline__ void shift_run(float4 (&x)[R])
     }
 }
 
-// Plane (p, ch) of one player (of 64 / G players, G lanes each: boards whose
-// planes leave most of a wave idle), by one wave, in 16-byte stores on
-// 16-byte boundaries, each round's run of 1 KB on a 128-byte one: lane i
-// stores the quad of cells from 4 i - sh on, sh the floats between that
-// boundary and the plane.  Where planes start inside 16 bytes (SHIFT) a lane
-// reads the quad at the multiple of 4 above that and the wave shifts (reading
-// LDS off its boundaries: 23x23 rollout 1,295 -> 1,400 us; small boards,
-// G < 64, do, their players' shifts differ), and the quads across a plane's
-// ends are written in part.  ro: the env's block from the 128-byte boundary
-// at or before its first float, d floats into it.
-// R: rounds of 64 quads that cover a plane (G < 64: one).
+// The quads x of one plane, shifted where they have to be, to its place: sh
+// floats past the byte offset base of ro.
 template <bool SHIFT, int G, int R>
-__device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, int p0, int ch, const Rsrc &ro, int d)
+__device__ __forceinline__ void plane_store(float4 *px, int sh, int base, int HW, int gl, const Rsrc &ro)
 {
-    const Geom &g = f.g;
-    const int HW = g.HW, lane = lane_id(), gl = lane & (G - 1);
-    int p = G == kWave ? p0 : p0 + lane / G;
-    const bool real = G == kWave || p < g.P;
-    p = G == kWave ? p : min(p, g.P - 1);
-    const int fo = d + (p * kFeatC + ch) * HW;         // the plane's first float
-    const int sh = fo & (G == kWave ? 31 : 3);
-    const int base = 4 * (fo - sh);
     const int vo = G == kWave ? 0 : base, so = G == kWave ? base : 0;
-    int c[R];
     float4 x[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k)
-        c[k] = G == kWave ? min(max(4 * (kWave * k + gl) - (sh & ~3), 0), g.S - 4)
-                          : min(max(4 * gl - sh, SHIFT ? -3 : 0), SHIFT ? HW - 1 : HW - 4);
-    channel<SHIFT && G != kWave, R>(F, f, p, ch, c, x);
+    for (int k = 0; k < R; ++k) x[k] = px[k];
     if (SHIFT && G == kWave) {
         if ((sh & 3) == 1) shift_run<1>(x);
         else if ((sh & 3) == 2) shift_run<2>(x);
@@ -476,7 +459,7 @@ __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, i
     for (int k = 0; k < R; ++k) {
         const int c0 = 4 * (kWave * k + gl) - sh, at = vo + 16 * (kWave * k + gl);
         const u32x4 v = {__float_as_uint(x[k].x), __float_as_uint(x[k].y), __float_as_uint(x[k].z), __float_as_uint(x[k].w)};
-        if (real && c0 >= 0 && c0 + 4 <= HW) __builtin_amdgcn_raw_buffer_store_b128(v, ro, at, so, kAuxNT);
+        if (c0 >= 0 && c0 + 4 <= HW) __builtin_amdgcn_raw_buffer_store_b128(v, ro, at, so, kAuxNT);
         if (!SHIFT) continue;
         if (G == kWave) {                              // how much of an end's quad is the same for the wave
             const int head = sh & 3, tail = (HW + sh) & 3;
@@ -494,7 +477,7 @@ __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, i
                     else __builtin_amdgcn_raw_buffer_store_b96(u32x3{v.x, v.y, v.z}, ro, at, so, kEdge);
                 }
             }
-        } else if (real && ((c0 < 0 && c0 > -4) || (c0 < HW && c0 + 4 > HW))) {
+        } else if ((c0 < 0 && c0 > -4) || (c0 < HW && c0 + 4 > HW)) {
             if (c0 >= 0) __builtin_amdgcn_raw_buffer_store_b32(v.x, ro, at, so, kEdge);
             if (c0 + 1 >= 0 && c0 + 1 < HW) __builtin_amdgcn_raw_buffer_store_b32(v.y, ro, at + 4, so, kEdge);
             if (c0 + 2 >= 0 && c0 + 2 < HW) __builtin_amdgcn_raw_buffer_store_b32(v.z, ro, at + 8, so, kEdge);
@@ -503,18 +486,59 @@ __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, i
     }
 }
 
+// Plane (p, ch) of one player (of 64 / G players, G lanes each: boards whose
+// planes leave most of a wave idle; of two players with PAIR), by one wave, in
+// 16-byte stores on 16-byte boundaries, each round's run of 1 KB on a 128-byte
+// one: lane i stores the quad of cells from 4 i - sh on, sh the floats between
+// that boundary and the plane.  Where planes start inside 16 bytes (SHIFT) a
+// lane reads the quad at the multiple of 4 above that and the wave shifts
+// (reading LDS off its boundaries: 23x23 rollout 1,295 -> 1,400 us; small
+// boards, G < 64, do, their players' shifts differ), and the quads across a
+// plane's ends are written in part.  ro: the env's block from the 128-byte
+// boundary at or before its first float, d floats into it.
+// R: rounds of 64 quads that cover a plane (G < 64: one).
+template <bool SHIFT, int G, int R, bool PAIR>
+__device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, int p0, int ch, const Rsrc &ro, int d)
+{
+    constexpr int N = PAIR ? 2 : 1;                    // players of one after the other
+    const Geom &g = f.g;
+    const int HW = g.HW, lane = lane_id(), gl = lane & (G - 1);
+    const int p = G == kWave ? p0 : min(p0 + lane / G, g.P - 1);
+    int sh[N], base[N], c[N * R];
+    float4 x[N * R];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        const int fo = d + ((p + n) * kFeatC + ch) * HW;   // the plane's first float
+        sh[n] = fo & (G == kWave ? 31 : 3);
+        base[n] = 4 * (fo - sh[n]);
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            c[n * R + k] = G == kWave ? min(max(4 * (kWave * k + gl) - (sh[n] & ~3), 0), g.S - 4)
+                                      : min(max(4 * gl - sh[n], SHIFT ? -3 : 0), SHIFT ? HW - 1 : HW - 4);
+    }
+    channel<SHIFT && G != kWave, PAIR, N * R>(F, f, p, ch, c, x);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        if (G == kWave ? p0 + n < g.P : p0 + lane / G < g.P) plane_store<SHIFT, G, R>(x + n * R, sh[n], base[n], HW, gl, ro);
+    }
+}
+
 // The env's planes as tasks for one wave each, in the order of the tensor:
 // the waves of a workgroup then write next to each other.
-template <int G>
-__device__ __forceinline__ int plane_tasks(int P) { return (P + kWave / G - 1) / (kWave / G) * kFeatC; }
+template <int G, bool PAIR>
+__device__ __forceinline__ int plane_tasks(int P)
+{
+    constexpr int n = PAIR ? 2 : kWave / G;            // players to a task
+    return (P + n - 1) / n * kFeatC;
+}
 
-template <bool SHIFT, int G, int R>
+template <bool SHIFT, int G, int R, bool PAIR>
 __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, int k, float *fe)
 {
     const int d = (int)(((uintptr_t)fe >> 2) & 31);
     const Rsrc ro = buffer_rsrc(fe - d, 4u * (uint32_t)(d + f.g.P * kFeatC * f.g.HW));
     const int grp = k / kFeatC;
-    plane_out<SHIFT, G, R>(F, f, grp * (kWave / G), k - grp * kFeatC, ro, d);
+    plane_out<SHIFT, G, R, PAIR>(F, f, grp * (PAIR ? 2 : kWave / G), k - grp * kFeatC, ro, d);
 }
 
 // Token windows: 64 of the 512 turns of one player's two rows (the enemies'
@@ -592,7 +616,7 @@ __device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx 
 
 }  // namespace
 
-template <bool SHIFT, int G, int R>
+template <bool SHIFT, int G, int R, bool PAIR>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -667,7 +691,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
         for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
-    for (int k = wv; k < plane_tasks<G>(P); k += nwv) plane_task<SHIFT, G, R>(F, f, k, fe);
+    for (int k = wv; k < plane_tasks<G, PAIR>(P); k += nwv) plane_task<SHIFT, G, R, PAIR>(F, f, k, fe);
 }
 
 // ---------------------------------------------------------------- rollouts
@@ -703,7 +727,7 @@ struct RolloutSrc {
     }
 };
 
-template <bool SHIFT, int G, int R>
+template <bool SHIFT, int G, int R, bool PAIR>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -759,7 +783,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
     }
 
     const uint64_t env_id = a.env_base + (uint64_t)e;
-    const int n_planes = plane_tasks<G>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
+    const int n_planes = plane_tasks<G, PAIR>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
     for (int step = 0; step < a.n_steps; ++step) {
         // what follows from the geometry is computed anew each turn: kept
         // over the loop it costs more scalar registers than there are
@@ -843,7 +867,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         auto hand = [&]() { return lane == 0 ? atomicAdd(rl.next, 1) : 0; };
         for (int k = readfirst(hand()); k < n_planes;) {
             const int k2 = hand();                         // the next one, while this one is written
-            plane_task<SHIFT, G, R>(F, f, k, fe);
+            plane_task<SHIFT, G, R, PAIR>(F, f, k, fe);
             k = readfirst(k2);
         }
         lds_barrier();
@@ -882,18 +906,26 @@ hipError_t feature_tables_ready()
 
 // The instance for a board: planes on 16-byte boundaries or not, two players
 // to a wave where a plane (shifted or not) takes at most half of one, rounds
-// of 64 quads of a plane.
+// of 64 quads of a plane.  Up to two rounds a wave takes the planes of two
+// players one after the other: finding a channel's way costs it about as much
+// as a round (features and step with one player to a task and two: 16x16 1v1,
+// 32,000 envs 890, 705 us; 16x16 2v2, 16,000 envs 715, 612; 13x15 1v1, 20,000
+// envs 512, 464; 17x19 2v2, 2,000 envs 120, 115; with three rounds the same
+// either way: 25x25, 3,000 envs of 3 players 232, 234).
 template <class F>
 static void by_layout(int HW, const float *feat, F &&go)
 {
     const bool shift = HW % 4 != 0 || (reinterpret_cast<uintptr_t>(feat) & 15) != 0;
     const int quads = (HW + (shift ? 3 : 0)) / 4 + (shift ? 1 : 0), lines = HW % 32 == 0 && (reinterpret_cast<uintptr_t>(feat) & 127) == 0 ? 0 : 7;
     auto pick = [&](auto sh) {
-        if (quads <= 32) go(sh, std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{});
-        else if (quads + lines <= 64) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 1>{});
-        else if (quads + lines <= 128) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 2>{});
-        else if (quads + lines <= 192) go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 3>{});
-        else go(sh, std::integral_constant<int, 64>{}, std::integral_constant<int, 5>{});
+        constexpr std::integral_constant<int, 64> wave{};
+        constexpr std::true_type two{};                // players to a task
+        constexpr std::false_type one{};
+        if (quads <= 32) go(sh, std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, one);
+        else if (quads + lines <= 64) go(sh, wave, std::integral_constant<int, 1>{}, two);
+        else if (quads + lines <= 128) go(sh, wave, std::integral_constant<int, 2>{}, two);
+        else if (quads + lines <= 192) go(sh, wave, std::integral_constant<int, 3>{}, one);
+        else go(sh, wave, std::integral_constant<int, 5>{}, one);
     };
     if (shift) pick(std::true_type{});
     else pick(std::false_type{});
@@ -912,8 +944,8 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     // envs: 21.6 -> 19.9; but 500 envs: 34.7 -> 39.1; features and step).
     const uint32_t fit = 160u * 1024u / lds;
     const int nwv = n_envs <= 256 ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
-    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds) {
-        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value>), dim3((unsigned)n_envs),
+    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds, auto pair) {
+        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(pair)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
     });
     return hipGetLastError();
@@ -922,8 +954,8 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
     const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
-    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds) {
-        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value>), dim3((unsigned)n_envs),
+    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds, auto pair) {
+        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(pair)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * (n_envs <= 256 ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
     });
     return hipGetLastError();

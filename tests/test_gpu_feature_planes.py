@@ -106,3 +106,27 @@ def test_rollout_in_one_launch(H, W, mode, P, E, T, over):
         gen.gen_features(b.st, b.fmem, feat, tok)      # Batch.features() would start a memory of its own here
         want, wtok = oracle.features(cfg, ost, mem, tokens=True)
         assert np.array_equal(bits(feat.cpu().numpy()), bits(want)) and np.array_equal(tok.cpu().numpy(), wtok)
+
+
+@pytest.mark.parametrize("P", [2, 3, 5, 8])
+@pytest.mark.parametrize("H,W", [(16, 16), (12, 19), (15, 15), (17, 17), (15, 30), (22, 22), (9, 25), (23, 21)])
+def test_two_players_to_a_task(H, W, P):
+    """One and two rounds of 64 quads (and the boards next to them), odd player counts: the last task has one player."""
+    import torch
+    E = 2
+    gen, b, cfg, ost, mem = make(H, W, 2, P, E, seed=H * W + P)
+    fmem = torch.zeros(gen.gen_feat_mem_bytes(b.st), dtype=torch.uint8, device="cuda")
+    n = E * P * 38 * H * W
+    raw = torch.full((n + 64,), 7.0, dtype=torch.float32, device="cuda")
+    feat = raw[3:3 + n] if W % 3 == 0 else raw[:n]
+    torch.cuda.synchronize()
+    b.sample(9, 0)
+    for t in range(9):
+        gen.gen_features(b.st, fmem, feat)
+        want = oracle.features(cfg, ost, mem)
+        assert np.array_equal(bits(feat.cpu().numpy().reshape(want.shape)), bits(want)), f"step {t}"
+        b.step_sample(9, t + 1)
+        oracle.step(cfg, ost, oracle.sample(cfg, ost, 9, t))
+    got = raw.cpu().numpy()
+    lo = 3 if W % 3 == 0 else 0
+    assert (got[:lo] == 7.0).all() and (got[lo + n:] == 7.0).all()
