@@ -925,6 +925,7 @@ static void by_layout(int HW, const float *feat, F &&go)
         else if (quads + lines <= 64) go(sh, wave, std::integral_constant<int, 1>{}, two);
         else if (quads + lines <= 128) go(sh, wave, std::integral_constant<int, 2>{}, two);
         else if (quads + lines <= 192) go(sh, wave, std::integral_constant<int, 3>{}, one);
+        else if (quads + lines <= 256) go(sh, wave, std::integral_constant<int, 4>{}, one);
         else go(sh, wave, std::integral_constant<int, 5>{}, one);
     };
     if (shift) pick(std::true_type{});
@@ -942,8 +943,13 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     // 16.8, 20.2, 27.9; 700 envs: 24.8, 25.4, 32.5), and 16 where every env
     // has a CU of its own (28x14 FFA-8, 60 envs: 39.0 -> 33.7; 24x24 1v1, 64
     // envs: 21.6 -> 19.9; but 500 envs: 34.7 -> 39.1; features and step).
+    // 16 also where the LDS leaves room for one env, or for two of more than
+    // 4 players (8 and 16 waves: 31x31 FFA-8, 800 envs 285, 259; 28x32 FFA-7
+    // with tokens, 2,385 envs 630, 548; 31x31 2v2, 1,500 envs 252, 224; 25x25
+    // FFA-8, 1,024 envs 209, 196; but 31x30 1v1, 6,000 envs 490, 552).
     const uint32_t fit = 160u * 1024u / lds;
-    const int nwv = n_envs <= 256 ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
+    const bool most = n_envs <= 256 || fit == 1 || (fit == 2 && a.g.P > 4);
+    const int nwv = most ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
     by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds, auto pair) {
         hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(pair)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);

@@ -57,7 +57,8 @@ def test_planes(H, W, mode, P, shift):
 
 
 @pytest.mark.parametrize("H,W,mode,P,E", [(10, 10, 0, 2, 1100), (16, 16, 1, 4, 1030), (9, 7, 2, 8, 1040), (24, 24, 0, 2, 1030),
-                                             (12, 11, 2, 3, 256), (12, 11, 2, 3, 257)])
+                                             (12, 11, 2, 3, 256), (12, 11, 2, 3, 257), (25, 25, 2, 8, 258),
+                                             (31, 31, 1, 4, 258), (32, 31, 0, 2, 260), (32, 32, 2, 8, 257)])
 def test_waves_per_env(H, W, mode, P, E):
     """More than 1,024 envs: 2, 4 or 8 waves per env by the board's LDS; 16 up to 256 envs."""
     gen, b, cfg, ost, mem = make(H, W, mode, P, E, seed=E)
