@@ -703,24 +703,27 @@ static int dense_waves(const EnvArgs &a, int n_envs)
 // such line; planes of whole 64-byte halves lose only when the batch's
 // observation is beyond the Infinity Cache.  (us per step, stored where they
 // lie and staged: 1v1 20x20, 65,536 envs 233, 143; 2v2 20x20, 40,000 envs 250,
-// 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 16x17, 8,000 envs 19.0, 20.8; 24x24,
+// 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 14x20, 8,192 envs 21.8, 20.2; 24x24,
 // 65,536 envs 220, 202; 30,000 envs 66, 73; 16x16, 65,536 envs 80, 98; 28x32,
-// 8,000 envs 31, 36; observations alone of 65,536 envs 1v1 24x24 173, 158.  A
-// reset's maps keep the waves apart, so it gains nothing: 24x24 177, 238.)
+// 8,000 envs 31, 36; observations alone of 65,536 envs 1v1 24x24 173, 158.
+// A second round of a few cells pays later: 13x20, 8,192 envs 18.6, 20.8;
+// 20,000 envs 44.4, 40.4; 65,536 envs 135, 113.  A reset's maps keep the
+// waves apart, so it gains nothing: 24x24 177, 238.)
 static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
 {
     if (kind == K_RESET || a.obs == nullptr || a.g.HW <= kOneRound || a.g.PS % 128 == 0) return false;
     const uint64_t bytes = (uint64_t)n_envs * (uint64_t)(a.g.P * 8 * a.g.PS);
-    return bytes >= (a.g.PS % 64 != 0 ? 30000000ull : 400000000ull);
+    const uint64_t parts = a.g.HW <= kOneRound + 16 ? 64000000ull : 30000000ull;
+    return bytes >= (a.g.PS % 64 != 0 ? parts : 400000000ull);
 }
 
-// LDS of the dword writers by one wave: with more than 4 players and planes of more than
-// one line a batch is held to 16 waves a CU, since the lines that two planes
+// LDS of the dword writers by one wave: with more than 4 players and planes
+// of more than one line a batch is held to 16 waves a CU, since the lines that two planes
 // share leave the L2 in parts when the 32 waves that would fit all store
 // (us per step with 32 and 16 waves: FFA-8 12x12, 32,768 envs 92, 75; FFA-8
 // 12x13 108, 86; FFA-8 14x14, 16,384 envs 68, 63; FFA-6 14x14, 32,768 envs 93,
-// 71; FFA-5 14x14 74, 64; FFA-8 12x12 padded, 32,768 envs 94, 77; planes within a line or fewer players need the
-// waves: FFA-8 10x10 62, 74; 2v2 14x14, 50,000 envs 73, 88; below 8,192 envs
+// 71; FFA-5 14x14 74, 64; FFA-8 12x12 padded, 32,768 envs 94, 77; planes
+// within a line or fewer players need the waves: FFA-8 10x10 62, 74; 2v2 14x14, 50,000 envs 73, 88; below 8,192 envs
 // the same either way).
 constexpr uint32_t kSixteenWavesLds = 10240;
 
