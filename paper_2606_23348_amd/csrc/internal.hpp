@@ -29,6 +29,7 @@ struct EnvArgs {
     int64_t *army_tot;
     int32_t *next_actions;        // fused actor output (nullptr: no actor)
     uint64_t actor_seed, step_idx;
+    uint32_t paired;              // aligned planes stored two at a time (set by the launch)
 };
 
 struct SampleArgs {

@@ -250,6 +250,46 @@ __device__ __forceinline__ void obs_padded_planes(const Lds &L, const Geom &g, u
     }
 }
 
+// Dense planes that end in the middle of a line, two at a time: channels 2 i
+// and 2 i + 1 are one run of whole lines, stored 64 quads at a time, so that
+// the line they share is one store's (HALF: whether a store's quads are the
+// first plane's, the second's or both).  Plane by plane that line is written
+// in halves two rounds apart; together in LDS (the staged writer) the run
+// costs instructions that a launch after a pause, at lower clocks, feels.
+// us per step of 1v1 24x24, 65,536 envs, plane by plane, staged, in pairs:
+// one batch after a pause 132, 172, 131; on and on 138, 144, 130; several
+// batches in turn 224, 203, 203.
+template <int HALF>
+__device__ __forceinline__ void pair_stores(const Lds &L, const Geom &g, const Rsrc &ro, int Q, int n)
+{
+    const bool odd = HALF == 2 ? Q >= n : HALF == 1;       // the run's quad Q is of the second plane
+    const int q = odd ? Q - n : Q;
+    const QuadCells qc = quad_cells(L, q);
+    const uint32_t ac = reinterpret_cast<const uint32_t *>(L.armyc)[q];
+    for (int p = 0; p < g.P; ++p) {
+        const uint32_t ally = g.mode == MODE_2V2 ? (uint32_t)(p ^ 2) : (uint32_t)p;
+        uint32_t v[8];
+        quad_planes(L, qc, ac, p, ally, q, v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = HALF == 0 ? v[2 * i] : HALF == 1 ? v[2 * i + 1] : odd ? v[2 * i + 1] : v[2 * i];
+            __builtin_amdgcn_raw_buffer_store_b32(x, ro, 4 * Q, (p * 8 + 2 * i) * g.HW, kAuxNT);
+        }
+    }
+}
+
+__device__ __forceinline__ void obs_paired_planes(const Lds &L, const Geom &g, const Rsrc &ro)
+{
+    const int n = g.HW >> 2;
+    for (int at = 0; at < 2 * n; at += kWave) {
+        const int Q = at + lane_id();
+        if (Q >= 2 * n) continue;
+        if (at + kWave <= n) pair_stores<0>(L, g, ro, Q, n);
+        else if (at >= n) pair_stores<1>(L, g, ro, Q, n);
+        else pair_stores<2>(L, g, ro, Q, n);
+    }
+}
+
 // Per-env inputs and outputs of one step (pointers into this env's rows).
 struct EnvIO {
     EnvScalars *sc;
@@ -269,6 +309,7 @@ struct EnvIO {
     bool use_tick;              // keep the per-env step counter; the actor draws with it
     int nwv = 1;                // waves of the workgroup sharing the observation planes
     bool stage = false;         // padded planes may go through the staged writer
+    bool paired = false;        // EnvArgs::paired
 };
 
 // One environment step (or reset / observation) on one wave.  OBSV selects
@@ -432,7 +473,8 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Src
             if (OBSV == OBS_QUAD) {
                 const int nq = g.HW >> 2;
                 const Rsrc ro = buffer_rsrc(io.obs, (uint32_t)(g.P * 8 * g.HW));
-                for (int q = lane; q < nq; q += kWave) {
+                if (io.paired) obs_paired_planes(L, g, ro);
+                else for (int q = lane; q < nq; q += kWave) {
                     const QuadCells qc = quad_cells(L, q);
                     const uint32_t ac = reinterpret_cast<const uint32_t *>(L.armyc)[q];
                     for (int p = 0; p < g.P; ++p) quad_store(L, g, ro, qc, ac, p, q, g.HW);
@@ -506,6 +548,7 @@ struct EnvSrc {
         io.actor_step = a.step_idx;
         io.use_tick = false;
         io.nwv = nwv;
+        io.paired = a.paired != 0u;
         return io;
     }
 
@@ -703,18 +746,32 @@ static int dense_waves(const EnvArgs &a, int n_envs)
 // such line; planes of whole 64-byte halves lose only when the batch's
 // observation is beyond the Infinity Cache.  (us per step, stored where they
 // lie and staged: 1v1 20x20, 65,536 envs 233, 143; 2v2 20x20, 40,000 envs 250,
-// 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 14x20, 8,192 envs 21.8, 20.2; 24x24,
-// 65,536 envs 220, 202; 30,000 envs 66, 73; 16x16, 65,536 envs 80, 98; 28x32,
-// 8,000 envs 31, 36; observations alone of 65,536 envs 1v1 24x24 173, 158.
-// A second round of a few cells pays later: 13x20, 8,192 envs 18.6, 20.8;
-// 20,000 envs 44.4, 40.4; 65,536 envs 135, 113.  A reset's maps keep the
-// waves apart, so it gains nothing: 24x24 177, 238.)
+// 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 14x20, 8,192 envs 21.8, 20.2; 16x16,
+// 65,536 envs 80, 98; 28x32, 8,000 envs 31, 36; 2v2 21x21 padded to 448, 28,000
+// envs 87, 78.  A second round of a few cells pays later: 13x20, 8,192 envs
+// 18.6, 20.8; 20,000 envs 44.4, 40.4; 65,536 envs 135, 113.  A reset's maps
+// keep the waves apart, so it gains nothing: 24x24 177, 238.)
 static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
 {
     if (kind == K_RESET || a.obs == nullptr || a.g.HW <= kOneRound || a.g.PS % 128 == 0) return false;
     const uint64_t bytes = (uint64_t)n_envs * (uint64_t)(a.g.P * 8 * a.g.PS);
     const uint64_t parts = a.g.HW <= kOneRound + 16 ? 64000000ull : 30000000ull;
     return bytes >= (a.g.PS % 64 != 0 ? parts : 400000000ull);
+}
+
+// Dense planes in pairs: those of more than a round of stores that end in the
+// middle of a line, where the observation no longer sits in the L2s (us per
+// step, plane by plane and in pairs: 24x24 1v1, 2,048 envs 9.7, 9.9; 4,096
+// envs 14.0, 13.6; 8,192 envs 24.3, 21.6; FFA-8 24x24, 1,024 envs 15.9, 16.5;
+// 2,048 envs 23.4, 22.0; 2v2 24x24, 28,000 envs 118, 99; FFA-6 16x20, 16,384
+// envs 60, 53; 26x32 1v1, 30,000 envs 147, 129; 16x20 1v1 has too little to
+// store per decoded cell: 32,768 envs 45.5, 48.0; boards of one round: 12x16
+// 1v1, 65,536 envs 77, 82).
+static bool pair_planes(const EnvArgs &a, int n_envs)
+{
+    if (a.obs == nullptr || a.g.PS != a.g.HW || a.g.HW <= kOneRound || a.g.HW % 128 != 64 || n_envs < 2048) return false;
+    const uint64_t bytes = (uint64_t)n_envs * (uint64_t)(a.g.P * 8 * a.g.PS);
+    return bytes >= (a.g.P * a.g.HW < 800 ? 400000000ull : 35000000ull);
 }
 
 // LDS of the dword writers by one wave: with more than 4 players and planes
@@ -754,16 +811,18 @@ static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
         return hipGetLastError();
     }
     const int nwv = KIND == K_RESET ? 1 : dense_waves(a, n_envs);
-    const bool staged = a.g.HW % 4 != 0;
+    const bool staged = a.g.HW % 4 != 0, paired = pair_planes(a, n_envs);
     if (staged && nwv > 1) {
         if constexpr (KIND != K_RESET)
             hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 8>), grid, dim3(kWave * nwv), lds_dense + (uint32_t)(nwv - 1) * stage_bytes(a.g), stream, a);
     } else if (staged) {
         hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 1>), grid, block, lds_dense, stream, a);
-    } else if (stage_whole(a, n_envs, KIND)) {
+    } else if (!paired && stage_whole(a, n_envs, KIND)) {
         hipLaunchKernelGGL((k_env<KIND, OBS_STAGED, SB, ACT, 1>), grid, block, lds_dense, stream, a);
     } else {
-        hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, dword_lds(a, n_envs, lds), stream, a);
+        EnvArgs b = a;
+        b.paired = paired ? 1u : 0u;
+        hipLaunchKernelGGL((k_env<KIND, OBS_QUAD, SB, ACT, 1>), grid, block, dword_lds(a, n_envs, lds), stream, b);
     }
     return hipGetLastError();
 }

@@ -101,6 +101,14 @@ def test_more_than_four_players_in_large_batches(H, W, P, E, padded):
     check(H, W, 2, P, E, 1, padded=padded)
 
 
+@pytest.mark.parametrize("off", [0, 16, 64])
+@pytest.mark.parametrize("H,W,mode,P,E", [(24, 24, 0, 2, 4000), (16, 20, 2, 6, 2300), (28, 16, 1, 4, 2600), (32, 30, 2, 3, 2048), (32, 26, 0, 2, 2700)])
+def test_planes_in_pairs(H, W, mode, P, E, off):
+    """Planes that end in the middle of a line, two at a time (from 2,048 envs and 35 MB of observation on)."""
+    assert E * P * 8 * H * W >= 35_000_000 and H * W % 128 == 64
+    check(H, W, mode, P, E, 2, off=off)
+
+
 def test_pool_from_64_megabytes():
     """A pool large enough for the staged writer (boards of 16x16 to 25x25, all
     modes): every env against the oracle, two steps."""
