@@ -292,15 +292,15 @@ __device__ __forceinline__ float4 bytes_to_f(uint32_t m)
 }
 
 // Channel ch (wave-uniform) of player p at the quads of cells c[0], c[1], ...
-// (any cell with ANY, else multiples of 4; the second half of them of player
-// p + 1 with PAIR, or of p again after the last): the channel is decided once
+// (any cell with ANY, else multiples of 4; with N players those
+// of player p first, then p + 1's and so on, the last player's again after it): the channel is decided once
 // for all R quads of a lane, whose LDS reads are then in flight together.
-template <bool ANY, bool PAIR, int R>
+template <bool ANY, int N, int R>
 __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int p0, int ch, const int (&c)[R], float4 (&x)[R])
 {
     const Geom &g = f.g;
     const int S = g.S;
-    auto player = [&](int k) { return PAIR && k >= R / 2 ? min(p0 + 1, g.P - 1) : p0; };
+    auto player = [&](int k) { return N == 1 ? p0 : min(p0 + k / (R / N), g.P - 1); };
     auto each = [&](auto &&value) {
 #pragma unroll
         for (int k = 0; k < R; ++k) x[k] = value(c[k], player(k));
@@ -487,7 +487,7 @@ __device__ __forceinline__ void plane_store(float4 *px, int sh, int base, int HW
 }
 
 // Plane (p, ch) of one player (of 64 / G players, G lanes each: boards whose
-// planes leave most of a wave idle; of two players with PAIR), by one wave, in
+// planes leave most of a wave idle; of N players, one after the other), by one wave, in
 // 16-byte stores on 16-byte boundaries, each round's run of 1 KB on a 128-byte
 // one: lane i stores the quad of cells from 4 i - sh on, sh the floats between
 // that boundary and the plane.  Where planes start inside 16 bytes (SHIFT) a
@@ -497,10 +497,9 @@ __device__ __forceinline__ void plane_store(float4 *px, int sh, int base, int HW
 // plane's ends are written in part.  ro: the env's block from the 128-byte
 // boundary at or before its first float, d floats into it.
 // R: rounds of 64 quads that cover a plane (G < 64: one).
-template <bool SHIFT, int G, int R, bool PAIR>
+template <bool SHIFT, int G, int R, int N>
 __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, int p0, int ch, const Rsrc &ro, int d)
 {
-    constexpr int N = PAIR ? 2 : 1;                    // players of one after the other
     const Geom &g = f.g;
     const int HW = g.HW, lane = lane_id(), gl = lane & (G - 1);
     const int p = G == kWave ? p0 : min(p0 + lane / G, g.P - 1);
@@ -516,7 +515,7 @@ __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, i
             c[n * R + k] = G == kWave ? min(max(4 * (kWave * k + gl) - (sh[n] & ~3), 0), g.S - 4)
                                       : min(max(4 * gl - sh[n], SHIFT ? -3 : 0), SHIFT ? HW - 1 : HW - 4);
     }
-    channel<SHIFT && G != kWave, PAIR, N * R>(F, f, p, ch, c, x);
+    channel<SHIFT && G != kWave, N, N * R>(F, f, p, ch, c, x);
 #pragma unroll
     for (int n = 0; n < N; ++n) {
         if (G == kWave ? p0 + n < g.P : p0 + lane / G < g.P) plane_store<SHIFT, G, R>(x + n * R, sh[n], base[n], HW, gl, ro);
@@ -525,20 +524,20 @@ __device__ __forceinline__ void plane_out(const FeatLds &F, const FrameCtx &f, i
 
 // The env's planes as tasks for one wave each, in the order of the tensor:
 // the waves of a workgroup then write next to each other.
-template <int G, bool PAIR>
+template <int G, int N>
 __device__ __forceinline__ int plane_tasks(int P)
 {
-    constexpr int n = PAIR ? 2 : kWave / G;            // players to a task
+    constexpr int n = N * (kWave / G);                 // players to a task
     return (P + n - 1) / n * kFeatC;
 }
 
-template <bool SHIFT, int G, int R, bool PAIR>
+template <bool SHIFT, int G, int R, int N>
 __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, int k, float *fe)
 {
     const int d = (int)(((uintptr_t)fe >> 2) & 31);
     const Rsrc ro = buffer_rsrc(fe - d, 4u * (uint32_t)(d + f.g.P * kFeatC * f.g.HW));
     const int grp = k / kFeatC;
-    plane_out<SHIFT, G, R, PAIR>(F, f, grp * (PAIR ? 2 : kWave / G), k - grp * kFeatC, ro, d);
+    plane_out<SHIFT, G, R, N>(F, f, grp * N * (kWave / G), k - grp * kFeatC, ro, d);
 }
 
 // Token windows: 64 of the 512 turns of one player's two rows (the enemies'
@@ -616,7 +615,7 @@ __device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx 
 
 }  // namespace
 
-template <bool SHIFT, int G, int R, bool PAIR>
+template <bool SHIFT, int G, int R, int N>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -691,7 +690,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
         for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
-    for (int k = wv; k < plane_tasks<G, PAIR>(P); k += nwv) plane_task<SHIFT, G, R, PAIR>(F, f, k, fe);
+    for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
 }
 
 // ---------------------------------------------------------------- rollouts
@@ -727,7 +726,7 @@ struct RolloutSrc {
     }
 };
 
-template <bool SHIFT, int G, int R, bool PAIR>
+template <bool SHIFT, int G, int R, int N>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -783,7 +782,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
     }
 
     const uint64_t env_id = a.env_base + (uint64_t)e;
-    const int n_planes = plane_tasks<G, PAIR>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
+    const int n_planes = plane_tasks<G, N>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
     for (int step = 0; step < a.n_steps; ++step) {
         // what follows from the geometry is computed anew each turn: kept
         // over the loop it costs more scalar registers than there are
@@ -867,7 +866,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         auto hand = [&]() { return lane == 0 ? atomicAdd(rl.next, 1) : 0; };
         for (int k = readfirst(hand()); k < n_planes;) {
             const int k2 = hand();                         // the next one, while this one is written
-            plane_task<SHIFT, G, R, PAIR>(F, f, k, fe);
+            plane_task<SHIFT, G, R, N>(F, f, k, fe);
             k = readfirst(k2);
         }
         lds_barrier();
@@ -906,23 +905,31 @@ hipError_t feature_tables_ready()
 
 // The instance for a board: planes on 16-byte boundaries or not, two players
 // to a wave where a plane (shifted or not) takes at most half of one, rounds
-// of 64 quads of a plane.  Up to two rounds a wave takes the planes of two
-// players one after the other: finding a channel's way costs it about as much
-// as a round (features and step with one player to a task and two: 16x16 1v1,
-// 32,000 envs 890, 705 us; 16x16 2v2, 16,000 envs 715, 612; 13x15 1v1, 20,000
-// envs 512, 464; 17x19 2v2, 2,000 envs 120, 115; with three rounds the same
-// either way: 25x25, 3,000 envs of 3 players 232, 234).
+// of 64 quads of a plane.  Up to two rounds a wave takes the planes of
+// several players one after the other: finding a channel's branch costs it about
+// as much as a round (features and step with one player to a task and two:
+// 16x16 1v1, 32,000 envs 890, 705 us; 13x15 1v1, 20,000 envs 512, 464; 17x19
+// 2v2, 2,000 envs 120, 115; with three rounds the same either way: 25x25,
+// 3,000 envs of 3 players 232, 234).  Of one round it takes three players'
+// where that leaves no more than one idle, else four's (two and three or
+// four: 13x15 FFA-7 with tokens, 338 envs 48.0, 44.9; 8x20 FFA-3, 5,225 envs
+// 111, 108; 14x14 FFA-8, 2,000 envs 150, 148; 16x16 2v2, 16,000 envs 610, 617;
+// 16 turns of rollout of 12x16 2v2, 400 envs 224, 207).
 template <class F>
-static void by_layout(int HW, const float *feat, F &&go)
+static void by_layout(int HW, int P, const float *feat, F &&go)
 {
     const bool shift = HW % 4 != 0 || (reinterpret_cast<uintptr_t>(feat) & 15) != 0;
     const int quads = (HW + (shift ? 3 : 0)) / 4 + (shift ? 1 : 0), lines = HW % 32 == 0 && (reinterpret_cast<uintptr_t>(feat) & 127) == 0 ? 0 : 7;
     auto pick = [&](auto sh) {
         constexpr std::integral_constant<int, 64> wave{};
-        constexpr std::true_type two{};                // players to a task
-        constexpr std::false_type one{};
+        constexpr std::integral_constant<int, 1> one{};    // players to a task
+        constexpr std::integral_constant<int, 2> two{};
         if (quads <= 32) go(sh, std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, one);
-        else if (quads + lines <= 64) go(sh, wave, std::integral_constant<int, 1>{}, two);
+        else if (quads + lines <= 64) {
+            if (P == 2) go(sh, wave, std::integral_constant<int, 1>{}, two);
+            else if (P == 4 || P > 6) go(sh, wave, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+            else go(sh, wave, std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{});
+        }
         else if (quads + lines <= 128) go(sh, wave, std::integral_constant<int, 2>{}, two);
         else if (quads + lines <= 192) go(sh, wave, std::integral_constant<int, 3>{}, one);
         else if (quads + lines <= 256) go(sh, wave, std::integral_constant<int, 4>{}, one);
@@ -950,8 +957,8 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     const uint32_t fit = 160u * 1024u / lds;
     const bool most = n_envs <= 256 || fit == 1 || (fit == 2 && a.g.P > 4);
     const int nwv = most ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
-    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds, auto pair) {
-        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(pair)::value>), dim3((unsigned)n_envs),
+    by_layout(a.g.HW, a.g.P, a.feat, [&](auto shift, auto lanes, auto rounds, auto players) {
+        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(players)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
     });
     return hipGetLastError();
@@ -960,8 +967,8 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
     const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
-    by_layout(a.g.HW, a.feat, [&](auto shift, auto lanes, auto rounds, auto pair) {
-        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(pair)::value>), dim3((unsigned)n_envs),
+    by_layout(a.g.HW, a.g.P, a.feat, [&](auto shift, auto lanes, auto rounds, auto players) {
+        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(players)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * (n_envs <= 256 ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
     });
     return hipGetLastError();
