@@ -956,7 +956,10 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     // FFA-8, 1,024 envs 209, 196; but 31x30 1v1, 6,000 envs 490, 552).
     const uint32_t fit = 160u * 1024u / lds;
     const bool most = n_envs <= 256 || fit == 1 || (fit == 2 && a.g.P > 4);
-    const int nwv = most ? kFeatMostWaves : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
+    // 12 below 512 envs, where some CUs hold one env and some two (8, 12 and 16
+    // waves: 9x14 2v2, 286 envs 29.7, 28.1; 9x19 FFA-5, 325 envs 33.9, 32.8,
+    // 39; 24x24 1v1, 320 envs 29.5, 28.8; 13x15 FFA-7, 338 envs 44.9, 45.6, 53).
+    const int nwv = most ? kFeatMostWaves : n_envs < 512 ? 12 : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
     by_layout(a.g.HW, a.g.P, a.feat, [&](auto shift, auto lanes, auto rounds, auto players) {
         hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(players)::value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
