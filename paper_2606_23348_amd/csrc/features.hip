@@ -151,11 +151,13 @@ __device__ __forceinline__ uint32_t slots_held(const int32_t (&stamp)[8], int t)
 }
 
 // The two masks of a quad (see FeatLds) from its owner and visibility bytes.
-// An owner byte is a player (0..7) or 0xFF; the shift takes its low 5 bits.
+// A byte that is no player (0xFF: none; 8 and up never stand in a valid
+// state) sets no bit.
 __device__ __forceinline__ uint32_t own_mask(uint32_t o4)
 {
-    return ((1u << (o4 & 31u)) & 0xFFu) | (((1u << ((o4 >> 8) & 31u)) & 0xFFu) << 8) |
-           (((1u << ((o4 >> 16) & 31u)) & 0xFFu) << 16) | ((1u << ((o4 >> 24) & 31u)) << 24);
+    const uint32_t m = (1u << (o4 & 7u)) | ((1u << ((o4 >> 8) & 7u)) << 8) | ((1u << ((o4 >> 16) & 7u)) << 16) |
+                       ((1u << ((o4 >> 24) & 7u)) << 24);
+    return m & (bytes_eq(o4 & 0xF8F8F8F8u, 0u) * 0xFFu);
 }
 
 __device__ __forceinline__ uint32_t foe_mask(uint32_t o4, uint32_t own, uint32_t vis, int mode)
@@ -187,7 +189,7 @@ __device__ __forceinline__ void army_totals(const FeatLds &F, const Geom &g, int
 {
     for (int c = tid; c < g.HW; c += nt) {
         const int o = F.owner[c];
-        if (o >= 0) atomicAdd(&F.armt[o], (unsigned long long)(uint32_t)F.army[c]);
+        if ((uint32_t)o < (uint32_t)kMaxP) atomicAdd(&F.armt[o], (unsigned long long)(long long)F.army[c]);
     }
 }
 

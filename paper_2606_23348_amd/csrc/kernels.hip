@@ -427,7 +427,8 @@ __device__ __forceinline__ void env_body(uint8_t *smem, const Geom &g, const Src
                 av[k] = __builtin_elementwise_add_sat(av[k], (int32_t)((inc >> (8 * k)) & 1u));
                 // one LDS addition per owned cell (a wave sum per player took
                 // 1,100 clocks each)
-                if (SB && o >= 0) atomicAdd(&tot[o], (unsigned long long)(uint32_t)av[k]);
+                // (the address is from the state's bytes: only a player's is one of the totals)
+                if (SB && (uint32_t)o < (uint32_t)kMaxP) atomicAdd(&tot[o], (unsigned long long)(long long)av[k]);
             }
             if (KIND != K_OBSERVE) {
                 st_nt(reinterpret_cast<uint4 *>(ga + q),
