@@ -726,8 +726,8 @@ int gen_pool_create(uint64_t seed, uint64_t env_base, int32_t n_envs, const gen_
     pl->state_bytes = pl->off_army + align256(cells * 4);
     pl->obs_bytes = obs16 * 16;
     pl->n_actions = acts;
-    pl->stage = pl->obs_bytes >= gen::kStagePoolBytes;
-    pl->lds_per_wave = (gen::lds_bytes_for(max_s, max_p) + (pl->stage ? gen::kStageExtra : 0u) + 15) & ~15u;
+    pl->stage = pl->obs_bytes >= gen::kStagePoolBytes && pl->max_cells > gen::kOneRound;
+    pl->lds_per_wave = (gen::lds_bytes_for(max_s, max_p) + 15) & ~15u;
     pool_make_order(*pl);
     *out = pl;
     return ok();

@@ -195,13 +195,15 @@ hipError_t launch_stream_spread(void *dst, const void *src, uint32_t n16, uint32
 
 uint32_t lds_bytes(const Geom &g);
 uint32_t lds_bytes_for(int S, int P);
-// A pool whose observation is at least this large stages its planes in LDS,
-// which takes kStageExtra more bytes of it (19x19 to 23x23, 81,136 envs: 249
+// A pool whose observation is at least this large stages the planes of its
+// boards above kOneRound cells in LDS (19x19 to 23x23, 81,136 envs: 249
 // -> 229 us per step; 18x18 to 25x25, 10,000 envs, about 100 MB: 34.6 -> 33.0;
 // the mixed 10x10 to 25x25, 131,072 envs: 290 -> 288; 2,000 envs: 10.6 -> 14.4,
-// so smaller pools do not).
+// so smaller pools do not).  Only the one-shot grid of one wave per env does,
+// and only its launches ask for the kStageExtra bytes more that it takes.
 constexpr uint64_t kStagePoolBytes = 64000000ull;
 constexpr uint32_t kStageExtra = 384;
+constexpr int kOneRound = 256;            // cells whose quads are one wave's
 // One workgroup per env of the launch (total_envs = the requests' env
 // counts summed): workgroup b steps env b - first[i] of request i, the last
 // i with first[i] <= b.
@@ -246,7 +248,7 @@ struct gen_pool {
     uint64_t off_scalars = 0, off_desc = 0, off_owner = 0, off_type = 0, off_army = 0;
     uint64_t state_bytes = 0, obs_bytes = 0, n_actions = 0;
     uint32_t lds_per_wave = 0;
-    bool stage = false;                   // see kStagePoolBytes
+    bool stage = false;                   // see kStagePoolBytes (some board is above kOneRound cells)
     int32_t max_cells = 0;
     gen_pool_tuning tuning{1, 0, 0, 0};
     std::vector<gen_pool_bucket> buckets;  // per-bucket packing (gen_pool_set_buckets); empty = pool-wide

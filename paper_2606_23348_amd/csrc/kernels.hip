@@ -20,7 +20,6 @@ uint32_t lds_bytes_for(int S, int P)
 // The staged writer's runs: four planes of a player, or all eight where the
 // quads of a plane (and one more for a shifted one) fit half a wave.
 constexpr int kSmallBoard = 121;
-constexpr int kOneRound = 256;         // cells whose quads are one wave's
 __host__ __device__ static inline int planes_per_run(int PS) { return PS <= kSmallBoard ? 8 : 4; }
 
 // Its staging of one wave: a run, the line carried from the run before, the
@@ -945,8 +944,11 @@ static hipError_t launch_pool_act(const PoolArgs &a, uint32_t grid, uint32_t nwv
     const uint32_t n = a.slot_end - a.slot_begin;
     if (nwv == 2) return launch_pool_kind<KIND, ACT, false, 2>(a, n, stream);
     const uint32_t full = (n + a.wpg - 1) / a.wpg;
-    if (grid == 0 || grid >= full) return launch_pool_kind<KIND, ACT, false, 1>(a, full, stream);
-    return launch_pool_kind<KIND, ACT, true, 1>(a, grid, stream);
+    if (grid != 0 && grid < full) return launch_pool_kind<KIND, ACT, true, 1>(a, grid, stream);
+    PoolArgs b = a;
+    b.stage = a.stage != 0u && a.obs != nullptr ? 1u : 0u;
+    b.lds_per_wave += b.stage != 0u ? kStageExtra : 0u;
+    return launch_pool_kind<KIND, ACT, false, 1>(b, full, stream);
 }
 
 // One segment of the work list [a.slot_begin, a.slot_end): grid == 0 one
