@@ -542,40 +542,60 @@ __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, 
     plane_out<SHIFT, G, R, N>(F, f, grp * N * (kWave / G), k - grp * kFeatC, ro, d);
 }
 
-// Token windows: 64 of the 512 turns of one player's two rows (the enemies'
-// army and land) per task.  The loads of a wave's first two tasks are issued
-// before the turn's memory update and their values stored after it, so the
-// ring's latency is hidden (as a last task of a few waves the windows cost
-// 1.1 ms of the 3.9 of 65,536 envs of 24x24).
+// Token windows: 64 of the 512 turns of `players` players' two rows (the
+// enemies' army and land) per task.  The loads of a wave's first two tasks are
+// issued before the turn's memory update and their values stored after it, so
+// the ring's latency is hidden (as a last task of a few waves the windows cost
+// 1.1 ms of the 3.9 of 65,536 envs of 24x24); those left are loaded two at a
+// time.  Two players share the turns' stamps and halve the tasks, which small
+// boards' 2 or 4 waves and many players feel (one player to a task and two,
+// features and step, us: 8x8 FFA-3, 3,426 envs 78 -> 71; 8x24 2v2, 2,568 envs
+// 96 -> 92; 10x10 1v1, 30,000 envs 552 -> 521; 32 turns of rollout of 23x23,
+// 512 envs 654 -> 642; 16 of 17x19 2v2, 400 envs 395 -> 382).  Feature launches
+// of boards of three rounds and more, which have 8 waves and more, keep one:
+// 24x24, 65,536 envs 3,192, 3,289.
+template <int players>
 struct TokenLoad {
-    int32_t stamp, land;
-    u32x2 army;
+    int32_t stamp, land[players];
+    u32x2 army[players];
 };
 
-__device__ __forceinline__ int token_tasks(int P) { return P * (kTokenWindow / kWave); }
+template <int players>
+__device__ __forceinline__ int token_tasks(int P) { return (P + players - 1) / players * (kTokenWindow / kWave); }
 
-__device__ __forceinline__ TokenLoad token_load(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
+template <int players>
+__device__ __forceinline__ TokenLoad<players> token_load(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
 {
-    const int p = k >> 3, j = (k & 7) * kWave + lane_id();
+    const int p0 = (k >> 3) * players, j = (k & 7) * kWave + lane_id();
     const int sl = (f.t - (kTokenWindow - 1) + j) & (kTokenWindow - 1);
-    TokenLoad v;
+    TokenLoad<players> v;
     v.stamp = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tstamp, 0);
-    v.army = __builtin_amdgcn_raw_buffer_load_b64(rm, 8 * sl, (int)fb.tarmy + 8 * p * kTokenWindow, 0);
-    v.land = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tland + 4 * p * kTokenWindow, 0);
+#pragma unroll
+    for (int i = 0; i < players; ++i) {
+        const int p = min(p0 + i, f.g.P - 1);          // an odd last player's twice
+        v.army[i] = __builtin_amdgcn_raw_buffer_load_b64(rm, 8 * sl, (int)fb.tarmy + 8 * p * kTokenWindow, 0);
+        v.land[i] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tland + 4 * p * kTokenWindow, 0);
+    }
     return v;
 }
 
-__device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f, const TokenLoad &v, int k, float *te)
+template <int players>
+__device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f, const TokenLoad<players> &v, int k, float *te)
 {
-    const int p = k >> 3, j = (k & 7) * kWave + lane_id();
+    const int p0 = (k >> 3) * players, j = (k & 7) * kWave + lane_id();
     const int32_t tau = f.t - (kTokenWindow - 1) + j;
-    const Rsrc rt = buffer_rsrc(te + (size_t)p * 2 * kTokenWindow, 8u * kTokenWindow);
     const bool now = j == kTokenWindow - 1;                  // this turn: channels 19 and 18
     const bool have = !f.fresh && tau >= 0 && v.stamp == tau;
-    const float army = now ? F.flat[p * 6 + 5] : have ? (float)(int64_t)(((uint64_t)v.army.y << 32) | v.army.x) : 0.0f;
-    const float land = now ? F.flat[p * 6 + 4] : have ? (float)v.land : 0.0f;
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(army), rt, 4 * j, 0, kAuxNT);
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(land), rt, 4 * j, 4 * kTokenWindow, kAuxNT);
+#pragma unroll
+    for (int i = 0; i < players; ++i) {
+        const int p = p0 + i;
+        if (p >= f.g.P) break;
+        const Rsrc rt = buffer_rsrc(te + (size_t)p * 2 * kTokenWindow, 8u * kTokenWindow);
+        const float army = now ? F.flat[p * 6 + 5] : have ? (float)(int64_t)(((uint64_t)v.army[i].y << 32) | v.army[i].x) : 0.0f;
+        const float land = now ? F.flat[p * 6 + 4] : have ? (float)v.land[i] : 0.0f;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(army), rt, 4 * j, 0, kAuxNT);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(land), rt, 4 * j, 4 * kTokenWindow, kAuxNT);
+    }
 }
 
 // Channels 14 to 19 of each player, and this turn's entry of the scoreboard
@@ -679,17 +699,23 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
     }
     lds_barrier();
     const bool tokens = a.tokens != nullptr;
-    const int n_tok = tokens ? token_tasks(P) : 0;
-    TokenLoad v0{}, v1{};
-    if (wv < n_tok) v0 = token_load(f, fb, rm, wv);
-    if (wv + nwv < n_tok) v1 = token_load(f, fb, rm, wv + nwv);
+    constexpr int kTp = R >= 3 ? 1 : 2;                // see token_load
+    const int n_tok = tokens ? token_tasks<kTp>(P) : 0;
+    TokenLoad<kTp> v0{}, v1{};
+    if (wv < n_tok) v0 = token_load<kTp>(f, fb, rm, wv);
+    if (wv + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, wv + nwv);
     frame_update<false>(F, f, rm, fb, tid, nt);
     lds_barrier();
     if (tokens) {
         float *te = a.tokens + (size_t)e * P * 2 * kTokenWindow;
         if (wv < n_tok) token_store(F, f, v0, wv, te);
         if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
-        for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
+        for (int k = wv + 2 * nwv; k < n_tok; k += 2 * nwv) {
+            v0 = token_load<kTp>(f, fb, rm, k);
+            if (k + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, k + nwv);
+            token_store(F, f, v0, k, te);
+            if (k + nwv < n_tok) token_store(F, f, v1, k + nwv, te);
+        }
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
     for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
@@ -784,7 +810,8 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
     }
 
     const uint64_t env_id = a.env_base + (uint64_t)e;
-    const int n_planes = plane_tasks<G, N>(P), n_tok = a.tokens != nullptr ? token_tasks(P) : 0;
+    constexpr int kTp = 2;                             // players to a token task
+    const int n_planes = plane_tasks<G, N>(P), n_tok = a.tokens != nullptr ? token_tasks<kTp>(P) : 0;
     for (int step = 0; step < a.n_steps; ++step) {
         // what follows from the geometry is computed anew each turn: kept
         // over the loop it costs more scalar registers than there are
@@ -830,16 +857,21 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
             if (lane < 12) reinterpret_cast<uint64_t *>(armt0 + 12 * ((step & 1) ^ 1))[lane] = 0ull;
         }
         lds_barrier();
-        TokenLoad v0{}, v1{};
-        if (wv < n_tok) v0 = token_load(f, fb, rm, wv);
-        if (wv + nwv < n_tok) v1 = token_load(f, fb, rm, wv + nwv);
+        TokenLoad<kTp> v0{}, v1{};
+        if (wv < n_tok) v0 = token_load<kTp>(f, fb, rm, wv);
+        if (wv + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, wv + nwv);
         frame_update<true>(F, f, rm, fb, tid, nt);
         lds_barrier();
         if (n_tok > 0) {
             float *te = a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow;
             if (wv < n_tok) token_store(F, f, v0, wv, te);
             if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
-            for (int k = wv + 2 * nwv; k < n_tok; k += nwv) token_store(F, f, token_load(f, fb, rm, k), k, te);
+            for (int k = wv + 2 * nwv; k < n_tok; k += 2 * nwv) {
+                v0 = token_load<kTp>(f, fb, rm, k);
+                if (k + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, k + nwv);
+                token_store(F, f, v0, k, te);
+                if (k + nwv < n_tok) token_store(F, f, v1, k + nwv, te);
+            }
         }
         // ---- wave 0 plays the turn on the live board, the others write
         if (wv == 0) {
