@@ -543,17 +543,12 @@ __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, 
 }
 
 // Token windows: 64 of the 512 turns of `players` players' two rows (the
-// enemies' army and land) per task.  The loads of a wave's first two tasks are
-// issued before the turn's memory update and their values stored after it, so
-// the ring's latency is hidden (as a last task of a few waves the windows cost
-// 1.1 ms of the 3.9 of 65,536 envs of 24x24); those left are loaded two at a
-// time.  Two players share the turns' stamps and halve the tasks, which small
-// boards' 2 or 4 waves and many players feel (one player to a task and two,
-// features and step, us: 8x8 FFA-3, 3,426 envs 78 -> 71; 8x24 2v2, 2,568 envs
-// 96 -> 92; 10x10 1v1, 30,000 envs 552 -> 521; 32 turns of rollout of 23x23,
-// 512 envs 654 -> 642; 16 of 17x19 2v2, 400 envs 395 -> 382).  Feature launches
-// of boards of three rounds and more, which have 8 waves and more, keep one:
-// 24x24, 65,536 envs 3,192, 3,289.
+// enemies' army and land) per task.  Two players share the turns' stamps and
+// halve the tasks, which small boards' 2 or 4 waves and many players feel (one
+// player to a task and two, features and step, us: 8x8 FFA-3, 3,426 envs 78 ->
+// 62; 10x10 1v1, 30,000 envs 552 -> 515; 12x12 FFA-8, 3,996 envs 283 -> 270; 32
+// turns of rollout of 23x23, 512 envs 661 -> 642; 16 of 17x19 2v2, 400 envs 394
+// -> 386).
 template <int players>
 struct TokenLoad {
     int32_t stamp, land[players];
@@ -595,6 +590,61 @@ __device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f,
         const float land = now ? F.flat[p * 6 + 4] : have ? (float)v.land[i] : 0.0f;
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(army), rt, 4 * j, 0, kAuxNT);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(land), rt, 4 * j, 4 * kTokenWindow, kAuxNT);
+    }
+}
+
+// The windows of one wave where few envs share a CU (boards of three rounds
+// and more, rollouts): the loads of its first two tasks are issued before the
+// turn's memory update and their values stored after it, so the ring's latency
+// is hidden (as a last task of a few waves the windows cost 1.1 ms of the 3.9
+// of 65,536 envs of 24x24); those left are loaded two at a time.  Feature
+// launches keep one player to a task: 24x24, 65,536 envs 3,192, 3,289 with two.
+template <int players>
+struct TokenWave {
+    TokenLoad<players> v0{}, v1{};
+    int n = 0;               // tasks, 0 without tokens
+
+    __device__ __forceinline__ void start(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, bool tokens, int wv, int nwv)
+    {
+        n = tokens ? token_tasks<players>(f.g.P) : 0;
+        if (wv < n) v0 = token_load<players>(f, fb, rm, wv);
+        if (wv + nwv < n) v1 = token_load<players>(f, fb, rm, wv + nwv);
+    }
+
+    __device__ __forceinline__ void finish(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv, int nwv)
+    {
+        if (wv < n) token_store(F, f, v0, wv, te);
+        if (wv + nwv < n) token_store(F, f, v1, wv + nwv, te);
+        for (int k = wv + 2 * nwv; k < n; k += 2 * nwv) {
+            v0 = token_load<players>(f, fb, rm, k);
+            if (k + nwv < n) v1 = token_load<players>(f, fb, rm, k + nwv);
+            token_store(F, f, v0, k, te);
+            if (k + nwv < n) token_store(F, f, v1, k + nwv, te);
+        }
+    }
+};
+
+// The windows of one wave where several envs share a CU, whose phases hide the
+// latency: all of them after the update, two tasks' loads at a time.  Every
+// load is waited for here: one left pending at the end is waited for in each
+// plane after it, together with that plane's stores (12x12 1v1, 12,000 envs
+// without tokens 184 us, with such a load 235).
+template <int players>
+__device__ __forceinline__ void token_windows(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv,
+                                              int nwv)
+{
+    auto settle = [](TokenLoad<players> &v) {
+        asm volatile("" : "+v"(v.stamp));
+#pragma unroll
+        for (int i = 0; i < players; ++i) asm volatile("" : "+v"(v.land[i]), "+v"(v.army[i].x), "+v"(v.army[i].y));
+    };
+    const int n = token_tasks<players>(f.g.P);
+    for (int k = wv; k < n; k += 2 * nwv) {
+        TokenLoad<players> v0 = token_load<players>(f, fb, rm, k), v1 = token_load<players>(f, fb, rm, min(k + nwv, n - 1));
+        settle(v0);
+        token_store(F, f, v0, k, te);
+        settle(v1);
+        if (k + nwv < n) token_store(F, f, v1, k + nwv, te);
     }
 }
 
@@ -699,23 +749,17 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
     }
     lds_barrier();
     const bool tokens = a.tokens != nullptr;
-    constexpr int kTp = R >= 3 ? 1 : 2;                // see token_load
-    const int n_tok = tokens ? token_tasks<kTp>(P) : 0;
-    TokenLoad<kTp> v0{}, v1{};
-    if (wv < n_tok) v0 = token_load<kTp>(f, fb, rm, wv);
-    if (wv + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, wv + nwv);
-    frame_update<false>(F, f, rm, fb, tid, nt);
-    lds_barrier();
-    if (tokens) {
-        float *te = a.tokens + (size_t)e * P * 2 * kTokenWindow;
-        if (wv < n_tok) token_store(F, f, v0, wv, te);
-        if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
-        for (int k = wv + 2 * nwv; k < n_tok; k += 2 * nwv) {
-            v0 = token_load<kTp>(f, fb, rm, k);
-            if (k + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, k + nwv);
-            token_store(F, f, v0, k, te);
-            if (k + nwv < n_tok) token_store(F, f, v1, k + nwv, te);
-        }
+    float *te = tokens ? a.tokens + (size_t)e * P * 2 * kTokenWindow : nullptr;
+    if constexpr (R >= 3) {
+        TokenWave<1> tw;
+        tw.start(f, fb, rm, tokens, wv, nwv);
+        frame_update<false>(F, f, rm, fb, tid, nt);
+        lds_barrier();
+        if (tokens) tw.finish(F, f, fb, rm, te, wv, nwv);
+    } else {
+        frame_update<false>(F, f, rm, fb, tid, nt);
+        lds_barrier();
+        if (tokens) token_windows<2>(F, f, fb, rm, te, wv, nwv);
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
     for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
@@ -810,8 +854,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
     }
 
     const uint64_t env_id = a.env_base + (uint64_t)e;
-    constexpr int kTp = 2;                             // players to a token task
-    const int n_planes = plane_tasks<G, N>(P), n_tok = a.tokens != nullptr ? token_tasks<kTp>(P) : 0;
+    const int n_planes = plane_tasks<G, N>(P);
     for (int step = 0; step < a.n_steps; ++step) {
         // what follows from the geometry is computed anew each turn: kept
         // over the loop it costs more scalar registers than there are
@@ -857,22 +900,11 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
             if (lane < 12) reinterpret_cast<uint64_t *>(armt0 + 12 * ((step & 1) ^ 1))[lane] = 0ull;
         }
         lds_barrier();
-        TokenLoad<kTp> v0{}, v1{};
-        if (wv < n_tok) v0 = token_load<kTp>(f, fb, rm, wv);
-        if (wv + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, wv + nwv);
+        TokenWave<2> tw;
+        tw.start(f, fb, rm, a.tokens != nullptr, wv, nwv);
         frame_update<true>(F, f, rm, fb, tid, nt);
         lds_barrier();
-        if (n_tok > 0) {
-            float *te = a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow;
-            if (wv < n_tok) token_store(F, f, v0, wv, te);
-            if (wv + nwv < n_tok) token_store(F, f, v1, wv + nwv, te);
-            for (int k = wv + 2 * nwv; k < n_tok; k += 2 * nwv) {
-                v0 = token_load<kTp>(f, fb, rm, k);
-                if (k + nwv < n_tok) v1 = token_load<kTp>(f, fb, rm, k + nwv);
-                token_store(F, f, v0, k, te);
-                if (k + nwv < n_tok) token_store(F, f, v1, k + nwv, te);
-            }
-        }
+        if (a.tokens != nullptr) tw.finish(F, f, fb, rm, a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow, wv, nwv);
         // ---- wave 0 plays the turn on the live board, the others write
         if (wv == 0) {
             const Turn r = advance(rl.L, g, RolloutSrc{e}, s, lane < P ? rl.act[lane] : 0, rl.claim);
