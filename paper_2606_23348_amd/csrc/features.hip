@@ -558,18 +558,41 @@ struct TokenLoad {
 template <int players>
 __device__ __forceinline__ int token_tasks(int P) { return (P + players - 1) / players * (kTokenWindow / kWave); }
 
-template <int players>
-__device__ __forceinline__ TokenLoad<players> token_load(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
+// The turn of this lane in task k (before the episode: negative).
+__device__ __forceinline__ int32_t token_turn(const FrameCtx &f, int k) { return f.t - (kTokenWindow - 1) + (k & 7) * kWave + lane_id(); }
+
+// Whether some turn of task k may be in the ring (wave-uniform).
+__device__ __forceinline__ bool token_some(const FrameCtx &f, int k)
 {
-    const int p0 = (k >> 3) * players, j = (k & 7) * kWave + lane_id();
-    const int sl = (f.t - (kTokenWindow - 1) + j) & (kTokenWindow - 1);
-    TokenLoad<players> v;
-    v.stamp = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tstamp, 0);
+    return !f.fresh && f.t - (kTokenWindow - 1) + (k & 7) * kWave + kWave - 1 >= 0;
+}
+
+// The turn that the lane's slot of the ring holds.
+__device__ __forceinline__ int32_t token_stamp(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
+{
+    return (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * (token_turn(f, k) & (kTokenWindow - 1)), (int)fb.tstamp, 0);
+}
+
+template <int players>
+__device__ __forceinline__ void token_values(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k, TokenLoad<players> &v)
+{
+    const int p0 = (k >> 3) * players, sl = token_turn(f, k) & (kTokenWindow - 1);
 #pragma unroll
     for (int i = 0; i < players; ++i) {
         const int p = min(p0 + i, f.g.P - 1);          // an odd last player's twice
         v.army[i] = __builtin_amdgcn_raw_buffer_load_b64(rm, 8 * sl, (int)fb.tarmy + 8 * p * kTokenWindow, 0);
         v.land[i] = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rm, 4 * sl, (int)fb.tland + 4 * p * kTokenWindow, 0);
+    }
+}
+
+template <int players>
+__device__ __forceinline__ TokenLoad<players> token_load(const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, int k)
+{
+    TokenLoad<players> v{};
+    v.stamp = -1;
+    if (token_some(f, k)) {
+        v.stamp = token_stamp(f, fb, rm, k);
+        token_values(f, fb, rm, k, v);
     }
     return v;
 }
@@ -578,7 +601,7 @@ template <int players>
 __device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f, const TokenLoad<players> &v, int k, float *te)
 {
     const int p0 = (k >> 3) * players, j = (k & 7) * kWave + lane_id();
-    const int32_t tau = f.t - (kTokenWindow - 1) + j;
+    const int32_t tau = token_turn(f, k);
     const bool now = j == kTokenWindow - 1;                  // this turn: channels 19 and 18
     const bool have = !f.fresh && tau >= 0 && v.stamp == tau;
 #pragma unroll
@@ -625,22 +648,36 @@ struct TokenWave {
 };
 
 // The windows of one wave where several envs share a CU, whose phases hide the
-// latency: all of them after the update, two tasks' loads at a time.  Every
-// load is waited for here: one left pending at the end is waited for in each
-// plane after it, together with that plane's stores (12x12 1v1, 12,000 envs
-// without tokens 184 us, with such a load 235).
+// latency: all of them after the update, two tasks at a time, their stamps
+// first, and only turns that the ring holds are loaded (a ring that few turns
+// were recorded in: 8x16 2v2, 6,000 envs with every turn loaded 192, 151;
+// 16x16 2v2, 2,600 envs 115, 107).  Every load is waited for here: one left
+// pending at the end is waited for in each plane after it, together with that
+// plane's stores (12x12 1v1, 12,000 envs without tokens 182 us, with such a
+// load 235).
 template <int players>
 __device__ __forceinline__ void token_windows(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv,
                                               int nwv)
 {
+    auto stamp = [&](int k) {
+        TokenLoad<players> v{};
+        v.stamp = token_some(f, k) ? token_stamp(f, fb, rm, k) : -1;
+        return v;
+    };
+    auto values = [&](int k, TokenLoad<players> &v) {
+        if (v.stamp == token_turn(f, k) && v.stamp >= 0) token_values(f, fb, rm, k, v);
+    };
     auto settle = [](TokenLoad<players> &v) {
-        asm volatile("" : "+v"(v.stamp));
 #pragma unroll
         for (int i = 0; i < players; ++i) asm volatile("" : "+v"(v.land[i]), "+v"(v.army[i].x), "+v"(v.army[i].y));
     };
     const int n = token_tasks<players>(f.g.P);
     for (int k = wv; k < n; k += 2 * nwv) {
-        TokenLoad<players> v0 = token_load<players>(f, fb, rm, k), v1 = token_load<players>(f, fb, rm, min(k + nwv, n - 1));
+        const int k1 = min(k + nwv, n - 1);
+        TokenLoad<players> v0 = stamp(k), v1 = stamp(k1);
+        asm volatile("" : "+v"(v0.stamp), "+v"(v1.stamp));
+        values(k, v0);
+        values(k1, v1);
         settle(v0);
         token_store(F, f, v0, k, te);
         settle(v1);
