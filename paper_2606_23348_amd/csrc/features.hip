@@ -542,6 +542,83 @@ __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, 
     plane_out<SHIFT, G, R, N>(F, f, grp * N * (kWave / G), k - grp * kFeatC, ro, d);
 }
 
+// The planes by a lane per cell, which writes every channel of its cell in
+// dwords: about 20 vector instructions a plane and 64 cells, against 60 to
+// 100 for each round of a plane task, which boards of few cells (or a second
+// round of few) and batches that do not fill the chip pay in full.  The lines
+// are written in parts, so large outputs are for the planes (see by_cells).
+// A wave's task is 64 cells and some of the players; a channel 21 value that
+// comes from HBM is loaded before the stores of the player before it (loads
+// and stores count together, so a later wait would be one for those stores).
+__device__ __forceinline__ void cells_out(const FeatLds &F, const FrameCtx &f, float *fe, int wv, int nwv)
+{
+    const Geom &g = f.g;
+    const int HW = g.HW, S = g.S, P = g.P;
+    const int words = g.NW, groups = min(P, max(1, nwv / words));
+    const Rsrc ro = buffer_rsrc(fe, 4u * (uint32_t)(P * kFeatC * HW));
+    for (int k = wv; k < words * groups; k += nwv) {
+        const int grp = k / words, c = (k - grp * words) * kWave + lane_id();
+        if (c >= HW) continue;
+        // the frames of turns t, t - 1, ..., t - 7
+        int32_t army[kHist + 1];
+        uint32_t own[kHist + 1], foe[kHist + 1];
+#pragma unroll
+        for (int j = 0; j <= kHist; ++j) {
+            const int at = ((f.t - j) & 7) * S + c;
+            army[j] = F.farmy[at];
+            own[j] = F.own[at];
+            foe[j] = F.foe[at];
+        }
+        const int row = div_w(c, g);
+        const float cx = F.cx[c - row * g.W], cy = F.cy[row];
+        auto age = [&](int p) {                        // channel 21
+            const uint32_t b = F.bits[p * S + c];
+            const uint32_t dt = (uint32_t)(f.t - F.lturn[p * S + c]);
+            if (!(~(b >> B_NOW) & (b >> B_ENEMY) & 1u)) return 0.0f;
+            return dt < (uint32_t)kAgeTable ? g_age_table[dt] : (float)(log1p((double)(int32_t)dt) / 5.0);
+        };
+        const int end = (grp + 1) * P / groups;
+        int p = grp * P / groups;
+        float next = age(p);
+#pragma nounroll
+        for (; p < end; ++p) {
+            const float aged = next;
+            next = age(min(p + 1, end - 1));
+            const uint32_t b = F.bits[p * S + c], now = b >> B_NOW, place = b >> B_PLACE;
+            auto put = [&](int ch, float x) {
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), ro, 4 * c, 4 * (p * kFeatC + ch) * HW, kEdge);
+            };
+            auto bit = [](uint32_t m, int at) { return (float)((m >> at) & 1u); };
+            put(0, (float)keep(army[0], b, B_NOW));
+            put(1, (float)keep(army[0], own[0], p));
+            put(2, (float)keep(army[0], foe[0], p));
+            put(3, (float)keep(army[0], b, B_NEUTRAL));
+#pragma unroll
+            for (int j = 0; j < 5; ++j) put(4 + j, bit(b, j));
+            put(9, bit(now & place, 0));
+            put(10, bit(own[0], p));
+            put(11, bit(foe[0], p));
+            put(12, bit(~now, 0));
+            put(13, bit(~now & place, 0));
+#pragma unroll
+            for (int j = 0; j < 6; ++j) put(14 + j, F.flat[p * 6 + j]);
+            put(20, (float)F.last[p * S + c]);
+            put(21, aged);
+            put(22, cx);
+            put(23, cy);
+            int32_t o0 = keep(army[0], own[0], p), f0 = keep(army[0], foe[0], p);
+#pragma unroll
+            for (int j = 0; j < kHist; ++j) {
+                const int32_t o1 = keep(army[j + 1], own[j + 1], p), f1 = keep(army[j + 1], foe[j + 1], p);
+                put(24 + j, (float)(o0 - o1));
+                put(24 + kHist + j, (float)(f0 - f1));
+                o0 = o1;
+                f0 = f1;
+            }
+        }
+    }
+}
+
 // Token windows: 64 of the 512 turns of `players` players' two rows (the
 // enemies' army and land) per task.  Two players share the turns' stamps and
 // halve the tasks, which small boards' 2 or 4 waves and many players feel (one
@@ -724,6 +801,7 @@ __device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx 
 
 }  // namespace
 
+// G, R, N, SHIFT: see plane_out; G = 1: a lane per cell (cells_out).
 template <bool SHIFT, int G, int R, int N>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 {
@@ -799,7 +877,11 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
         if (tokens) token_windows<2>(F, f, fb, rm, te, wv, nwv);
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
-    for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
+    if constexpr (G == 1) {
+        cells_out(F, f, fe, wv, nwv);
+    } else {
+        for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
+    }
 }
 
 // ---------------------------------------------------------------- rollouts
@@ -1006,6 +1088,25 @@ hipError_t feature_tables_ready()
     return e;
 }
 
+// How a board's planes lie in the tensor: the quads of 4 cells of one, shifted
+// where it starts inside 16 bytes, and the rounds of 64 that they take on
+// 128-byte lines.
+struct PlaneLayout {
+    bool shift;
+    int quads, rounds;
+};
+
+static PlaneLayout plane_layout(int HW, const float *feat)
+{
+    const uintptr_t at = reinterpret_cast<uintptr_t>(feat);
+    PlaneLayout l;
+    l.shift = HW % 4 != 0 || (at & 15) != 0;
+    l.quads = l.shift ? (HW + 3) / 4 + 1 : HW / 4;
+    const int before = HW % 32 == 0 && (at & 127) == 0 ? 0 : 7;    // quads of the first line before the plane
+    l.rounds = (l.quads + before + kWave - 1) / kWave;
+    return l;
+}
+
 // The instance for a board: planes on 16-byte boundaries or not, two players
 // to a wave where a plane (shifted or not) takes at most half of one, rounds
 // of 64 quads of a plane.  Up to two rounds a wave takes the planes of
@@ -1013,38 +1114,77 @@ hipError_t feature_tables_ready()
 // as much as a round (features and step with one player to a task and two:
 // 16x16 1v1, 32,000 envs 890, 705 us; 13x15 1v1, 20,000 envs 512, 464; 17x19
 // 2v2, 2,000 envs 120, 115; with three rounds the same either way: 25x25,
-// 3,000 envs of 3 players 232, 234).  Of one round it takes three players'
-// where that leaves no more than one idle, else four's (two and three or
-// four: 13x15 FFA-7 with tokens, 338 envs 48.0, 44.9; 8x20 FFA-3, 5,225 envs
-// 111, 108; 14x14 FFA-8, 2,000 envs 150, 148; 16x16 2v2, 16,000 envs 610, 617;
-// 16 turns of rollout of 12x16 2v2, 400 envs 224, 207).
+// 3,000 envs of 3 players 232, 234).  Of one round it takes two players' of 2,
+// three of 3, 5 or 6, four of 4, 7 or 8: no more than one place is idle (two
+// and three or four: 13x15 FFA-7 with tokens, 338 envs 48.0, 44.9; 8x20 FFA-3,
+// 5,225 envs 111, 108; 14x14 FFA-8, 2,000 envs 150, 148; 16x16 2v2, 16,000 envs
+// 610, 617; 16 turns of rollout of 12x16 2v2, 400 envs 224, 207).
 template <class F>
-static void by_layout(int HW, int P, const float *feat, F &&go)
+static void by_layout(const PlaneLayout &l, int P, F &&go)
 {
-    const bool shift = HW % 4 != 0 || (reinterpret_cast<uintptr_t>(feat) & 15) != 0;
-    const int quads = (HW + (shift ? 3 : 0)) / 4 + (shift ? 1 : 0), lines = HW % 32 == 0 && (reinterpret_cast<uintptr_t>(feat) & 127) == 0 ? 0 : 7;
-    auto pick = [&](auto sh) {
+    auto pick = [&](auto shift) {
         constexpr std::integral_constant<int, 64> wave{};
-        constexpr std::integral_constant<int, 1> one{};    // players to a task
+        constexpr std::integral_constant<int, 1> one{};
         constexpr std::integral_constant<int, 2> two{};
-        if (quads <= 32) go(sh, std::integral_constant<int, 32>{}, std::integral_constant<int, 1>{}, one);
-        else if (quads + lines <= 64) {
-            if (P == 2) go(sh, wave, std::integral_constant<int, 1>{}, two);
-            else if (P == 4 || P > 6) go(sh, wave, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-            else go(sh, wave, std::integral_constant<int, 1>{}, std::integral_constant<int, 3>{});
-        }
-        else if (quads + lines <= 128) go(sh, wave, std::integral_constant<int, 2>{}, two);
-        else if (quads + lines <= 192) go(sh, wave, std::integral_constant<int, 3>{}, one);
-        else if (quads + lines <= 256) go(sh, wave, std::integral_constant<int, 4>{}, one);
-        else go(sh, wave, std::integral_constant<int, 5>{}, one);
+        constexpr std::integral_constant<int, 3> three{};
+        constexpr std::integral_constant<int, 4> four{};
+        constexpr std::integral_constant<int, 5> five{};
+        if (l.quads <= 32) go(shift, std::integral_constant<int, 32>{}, one, one);
+        else if (l.rounds == 1 && P == 2) go(shift, wave, one, two);
+        else if (l.rounds == 1 && (P == 4 || P > 6)) go(shift, wave, one, four);
+        else if (l.rounds == 1) go(shift, wave, one, three);
+        else if (l.rounds == 2) go(shift, wave, two, two);
+        else if (l.rounds == 3) go(shift, wave, three, one);
+        else if (l.rounds == 4) go(shift, wave, four, one);
+        else go(shift, wave, five, one);
     };
-    if (shift) pick(std::true_type{});
+    if (l.shift) pick(std::true_type{});
     else pick(std::false_type{});
 }
 
+// Whether a batch's features go out by cells (cells_out) rather than by plane
+// tasks: outputs that the 256 MB last-level cache holds, whose lines in parts
+// it puts together, of boards on which a plane task works for few cells.
+// Measured on 1,300 boards and batches (features and step, us, by planes and
+// by cells; more than these sizes cost the cells up to 1.3 times the planes):
+// - planes that start inside 16 bytes, up to 256 cells: 15x15 FFA-8, 300 envs
+//   49.8, 33.2; 13x15 FFA-7 with tokens, 338 envs 45.9, 33.8; 15x15 2v2, 1,500
+//   envs (205 MB) 85.6, 70.2; 410 MB 143, 135 and 1v1 144, 156;
+// - the same with up to 350 cells: 17x17 FFA-8, 300 envs 54.9, 40; 17x17 1v1,
+//   1,500 envs (132 MB) 58.0, 61.3; 23x23, 621 envs 43, 45;
+// - aligned planes where a task leaves more than 40% of its lanes idle (8x8
+//   FFA-3, 1,500 envs 35.4, 25.2; or a second round of few quads:
+//   12x20 FFA-8, 100 envs 27.6, 25.4), or more than 20% and the output is not
+//   a matter of latency (10x10 2v2, 1,500 envs 48.5, 37.7; 300 envs 20.7, 20.5);
+// - others are the same or slower by cells (16x16 2v2, 642 envs 36.5, 43.2;
+//   24x24 1v1, 1,140 envs 63, 75).
+static bool by_cells(const Geom &g, const PlaneLayout &l, int n_envs)
+{
+    const uint64_t bytes = 4ull * kFeatC * (uint64_t)n_envs * (uint64_t)(g.P * g.HW);
+    if (l.shift && g.HW <= 256) return bytes <= 200000000ull;
+    if (bytes > 110000000ull) return false;
+    if (l.shift) return g.HW <= 350;
+    if (l.quads > 32) return l.rounds == 2 && g.HW <= 272;
+    const int used = g.P * l.quads, lanes = kWave * ((g.P + 1) / 2);
+    return 5 * used < 3 * lanes || (5 * used < 4 * lanes && bytes > 50000000ull);
+}
+
+// Workgroups that one round over the chip holds, one to a CU.
+constexpr int kCUs = 256;
+
 hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 {
+    const PlaneLayout layout = plane_layout(a.g.HW, a.feat);
     const uint32_t lds = feat_lds_bytes(a.g.S, a.g.P);
+    if (by_cells(a.g, layout, n_envs)) {
+        // A wave's tasks are 64 cells of some players: 8 waves while a CU holds
+        // one or two envs, then 4, or 2 on boards of few tasks (8, 4 and 2
+        // waves: 15x15 1v1, 800 envs 32.0, 25.1, 26.9; 300 envs 20.1, 20.0,
+        // 22; 9x9 1v1, 6,000 envs 152, 92, 77; 13x15 1v1, 5,058 envs 160, 157, 178).
+        const int nwv = n_envs <= 2 * kCUs ? 8 : a.g.NW <= 2 && a.g.P <= 4 && n_envs > 8 * kCUs ? 2 : 4;
+        hipLaunchKernelGGL((k_features<true, 1, 1, 1>), dim3((unsigned)n_envs), dim3(kWave * nwv), lds, stream, a);
+        return hipGetLastError();
+    }
     // Waves per env: as many as fill a CU's 32 with the envs that fit its
     // LDS, so that a small board's phases overlap other envs' (10x10 1v1,
     // 30,000 envs: 8 waves 545 us, 4 waves 426, 2 waves 365; 16x16 2v2,
@@ -1058,13 +1198,13 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     // with tokens, 2,385 envs 630, 548; 31x31 2v2, 1,500 envs 252, 224; 25x25
     // FFA-8, 1,024 envs 209, 196; but 31x30 1v1, 6,000 envs 490, 552).
     const uint32_t fit = 160u * 1024u / lds;
-    const bool most = n_envs <= 256 || fit == 1 || (fit == 2 && a.g.P > 4);
+    const bool most = n_envs <= kCUs || fit == 1 || (fit == 2 && a.g.P > 4);
     // 12 below 512 envs, where some CUs hold one env and some two (8, 12 and 16
     // waves: 9x14 2v2, 286 envs 29.7, 28.1; 9x19 FFA-5, 325 envs 33.9, 32.8,
     // 39; 24x24 1v1, 320 envs 29.5, 28.8; 13x15 FFA-7, 338 envs 44.9, 45.6, 53).
-    const int nwv = most ? kFeatMostWaves : n_envs < 512 ? 12 : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
-    by_layout(a.g.HW, a.g.P, a.feat, [&](auto shift, auto lanes, auto rounds, auto players) {
-        hipLaunchKernelGGL((k_features<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(players)::value>), dim3((unsigned)n_envs),
+    const int nwv = most ? kFeatMostWaves : n_envs < 2 * kCUs ? 12 : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
+    by_layout(layout, a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
+        hipLaunchKernelGGL((k_features<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
     });
     return hipGetLastError();
@@ -1073,9 +1213,9 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
     const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
-    by_layout(a.g.HW, a.g.P, a.feat, [&](auto shift, auto lanes, auto rounds, auto players) {
-        hipLaunchKernelGGL((k_rollout<decltype(shift)::value, decltype(lanes)::value, decltype(rounds)::value, decltype(players)::value>), dim3((unsigned)n_envs),
-                           dim3(kWave * (n_envs <= 256 ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
+    by_layout(plane_layout(a.g.HW, a.feat), a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
+        hipLaunchKernelGGL((k_rollout<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
+                           dim3(kWave * (n_envs <= kCUs ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
     });
     return hipGetLastError();
 }
