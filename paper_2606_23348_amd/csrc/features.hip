@@ -694,7 +694,7 @@ __device__ __forceinline__ void token_store(const FeatLds &F, const FrameCtx &f,
 }
 
 // The windows of one wave where few envs share a CU (boards of three rounds
-// and more, rollouts): the loads of its first two tasks are issued before the
+// and more): the loads of its first two tasks are issued before the
 // turn's memory update and their values stored after it, so the ring's latency
 // is hidden (as a last task of a few waves the windows cost 1.1 ms of the 3.9
 // of 65,536 envs of 24x24); those left are loaded two at a time.  Feature
@@ -731,7 +731,7 @@ struct TokenWave {
 // 16x16 2v2, 2,600 envs 115, 107).  Every load is waited for here: one left
 // pending at the end is waited for in each plane after it, together with that
 // plane's stores (12x12 1v1, 12,000 envs without tokens 182 us, with such a
-// load 235).
+// load 235; 8 turns of rollout of 13x15 2v2, 600 envs 226, 245).
 template <int players>
 __device__ __forceinline__ void token_windows(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv,
                                               int nwv)
@@ -1019,11 +1019,18 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
             if (lane < 12) reinterpret_cast<uint64_t *>(armt0 + 12 * ((step & 1) ^ 1))[lane] = 0ull;
         }
         lds_barrier();
-        TokenWave<2> tw;
-        tw.start(f, fb, rm, a.tokens != nullptr, wv, nwv);
-        frame_update<true>(F, f, rm, fb, tid, nt);
-        lds_barrier();
-        if (a.tokens != nullptr) tw.finish(F, f, fb, rm, a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow, wv, nwv);
+        float *te = a.tokens != nullptr ? a.tokens + ((size_t)step * gridDim.x + (size_t)e) * P * 2 * kTokenWindow : nullptr;
+        if constexpr (R >= 3) {
+            TokenWave<2> tw;
+            tw.start(f, fb, rm, te != nullptr, wv, nwv);
+            frame_update<true>(F, f, rm, fb, tid, nt);
+            lds_barrier();
+            if (te != nullptr) tw.finish(F, f, fb, rm, te, wv, nwv);
+        } else {
+            frame_update<true>(F, f, rm, fb, tid, nt);
+            lds_barrier();
+            if (te != nullptr) token_windows<2>(F, f, fb, rm, te, wv, nwv);
+        }
         // ---- wave 0 plays the turn on the live board, the others write
         if (wv == 0) {
             const Turn r = advance(rl.L, g, RolloutSrc{e}, s, lane < P ? rl.act[lane] : 0, rl.claim);
