@@ -1220,9 +1220,21 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
     const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
+    // Waves per env: 16 where a CU has one env, by the batch or by the LDS;
+    // 4 in larger batches of boards of which many fit, so that more envs'
+    // serial parts run side by side, as long as a turn has little to write
+    // (us of 3 to 16 turns with 4, 8 and 16 waves: 8x8 FFA-3, 5,000 envs 749,
+    // 934, -; 10x10 1v1, 600 envs 108, 128, -; 13x15 1v1, 5,000 envs 705, 845, -;
+    // but 16x16 1v1, 1,000 envs 179, 170; 10x10 2v2, 1,500 envs 327, 302; 13x15
+    // 2v2, 1,500 envs 571, 498; 25x25 FFA-8, 512 envs 607, 369, 320; 31x31 1v1
+    // 215, 146, 136; 23x23 1v1 218, 167, 185).  Waves 0 to 3 have parts of
+    // their own.
+    const uint32_t fit = 160u * 1024u / lds;
+    const bool few = a.g.P == 2 ? fit >= 7 : a.g.P <= 4 && fit >= 12;
+    const int nwv = n_envs <= kCUs || fit == 1 ? kFeatMostWaves : n_envs > 2 * kCUs && few ? 4 : kFeatWaves;
     by_layout(plane_layout(a.g.HW, a.feat), a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
         hipLaunchKernelGGL((k_rollout<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
-                           dim3(kWave * (n_envs <= kCUs ? kFeatMostWaves : kFeatWaves)), lds, stream, a);
+                           dim3(kWave * nwv), lds, stream, a);
     });
     return hipGetLastError();
 }
