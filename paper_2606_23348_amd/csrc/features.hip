@@ -547,18 +547,19 @@ __device__ __forceinline__ void plane_task(const FeatLds &F, const FrameCtx &f, 
 // 100 for each round of a plane task, which boards of few cells (or a second
 // round of few) and batches that do not fill the chip pay in full.  The lines
 // are written in parts, so large outputs are for the planes (see by_cells).
-// A wave's task is 64 cells and some of the players; a channel 21 value that
-// comes from HBM is loaded before the stores of the player before it (loads
-// and stores count together, so a later wait would be one for those stores).
-__device__ __forceinline__ void cells_out(const FeatLds &F, const FrameCtx &f, float *fe, int wv, int nwv)
+// A wave's task is 64 cells and one of `groups` parts of the players; a
+// channel 21 value that comes from HBM is loaded before the stores of the
+// player before it (loads and stores count together, so a later wait would be
+// one for those stores).
+__device__ __forceinline__ int cell_groups(const Geom &g, int nwv) { return min(g.P, max(1, nwv / g.NW)); }
+
+__device__ __forceinline__ void cell_task(const FeatLds &F, const FrameCtx &f, int k, int groups, float *fe)
 {
     const Geom &g = f.g;
     const int HW = g.HW, S = g.S, P = g.P;
-    const int words = g.NW, groups = min(P, max(1, nwv / words));
+    const int grp = k / g.NW, c = (k - grp * g.NW) * kWave + lane_id();
     const Rsrc ro = buffer_rsrc(fe, 4u * (uint32_t)(P * kFeatC * HW));
-    for (int k = wv; k < words * groups; k += nwv) {
-        const int grp = k / words, c = (k - grp * words) * kWave + lane_id();
-        if (c >= HW) continue;
+    if (c < HW) {
         // the frames of turns t, t - 1, ..., t - 7
         int32_t army[kHist + 1];
         uint32_t own[kHist + 1], foe[kHist + 1];
@@ -801,7 +802,7 @@ __device__ __forceinline__ void scoreboard_out(const FeatLds &F, const FrameCtx 
 
 }  // namespace
 
-// G, R, N, SHIFT: see plane_out; G = 1: a lane per cell (cells_out).
+// G, R, N, SHIFT: see plane_out; G = 1: a lane per cell (cell_task).
 template <bool SHIFT, int G, int R, int N>
 __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 {
@@ -878,7 +879,8 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
     }
     float *fe = a.feat + (size_t)e * (size_t)P * kFeatC * g.HW;
     if constexpr (G == 1) {
-        cells_out(F, f, fe, wv, nwv);
+        const int groups = cell_groups(g, nwv);
+        for (int k = wv; k < g.NW * groups; k += nwv) cell_task(F, f, k, groups, fe);
     } else {
         for (int k = wv; k < plane_tasks<G, N>(P); k += nwv) plane_task<SHIFT, G, R, N>(F, f, k, fe);
     }
@@ -892,14 +894,14 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_features(FeatArgs a)
 // only the outputs go to HBM (512 envs of 23x23 with tokens: 48.0 -> 19.5 us
 // a turn against two launches; 24x24 without: 35.0 -> 17.3 us, 17.2 with
 // constant planes, so it is bound by the stores).
-// Wave 0 plays the turn while the others write its planes; the planes are
+// Wave 0 plays the turn while the others write its planes; these tasks are
 // handed out by a counter, so wave 0 joins when it is done.
 struct RollLds {
     Lds L;                   // the live board
     EnvScalars *s;           // its scalars after the last turn
     int32_t *hdr;            // the memory block's header: magic, episode, stamp[8]
     int32_t *act;            // [8] this turn's actions
-    int32_t *next;           // next plane to hand out
+    int32_t *next;           // next task to hand out
     uint8_t *claim;          // [S] for the moves
 };
 
@@ -973,7 +975,7 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
     }
 
     const uint64_t env_id = a.env_base + (uint64_t)e;
-    const int n_planes = plane_tasks<G, N>(P);
+    const int groups = cell_groups(g, nwv), n_tasks = G == 1 ? g.NW * groups : plane_tasks<G, N>(P);
     for (int step = 0; step < a.n_steps; ++step) {
         // what follows from the geometry is computed anew each turn: kept
         // over the loop it costs more scalar registers than there are
@@ -1056,9 +1058,10 @@ __global__ __launch_bounds__(64 * kFeatMostWaves) void k_rollout(RolloutArgs a)
         }
         float *fe = a.feat + ((size_t)step * gridDim.x + (size_t)e) * (size_t)P * kFeatC * g.HW;
         auto hand = [&]() { return lane == 0 ? atomicAdd(rl.next, 1) : 0; };
-        for (int k = readfirst(hand()); k < n_planes;) {
+        for (int k = readfirst(hand()); k < n_tasks;) {
             const int k2 = hand();                         // the next one, while this one is written
-            plane_task<SHIFT, G, R, N>(F, f, k, fe);
+            if constexpr (G == 1) cell_task(F, f, k, groups, fe);
+            else plane_task<SHIFT, G, R, N>(F, f, k, fe);
             k = readfirst(k2);
         }
         lds_barrier();
@@ -1149,7 +1152,7 @@ static void by_layout(const PlaneLayout &l, int P, F &&go)
     else pick(std::false_type{});
 }
 
-// Whether a batch's features go out by cells (cells_out) rather than by plane
+// Whether a batch's features go out by cells (cell_task) rather than by plane
 // tasks: outputs that the 256 MB last-level cache holds, whose lines in parts
 // it puts together, of boards on which a plane task works for few cells.
 // Measured on 1,300 boards and batches (features and step, us, by planes and
@@ -1217,9 +1220,35 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The same for rollouts, whose turns write on and on: less of a turn's output
+// stays in the cache, and more where a board is few cells and players (us of 4
+// to 10 turns by planes and by cells, and the output of a turn: 8x8 FFA-3,
+// 1,500 envs 271, 137, 43 MB; 8,000 envs 921, 525, 233 MB; 9x9 2v2, 8,000 envs
+// 775, 631, 393 MB; 15x15 FFA-8, 300 envs 392, 314, 82 MB; 512 envs 409, 510,
+// 140 MB; 17x17 2v2, 300 envs 218, 140, 52 MB; 17x19 FFA-8, 200 envs 232, 281,
+// 78 MB; aligned planes of more than 32 quads: 12x20 2v2, 512 envs 160, 196).
+static bool turns_by_cells(const Geom &g, const PlaneLayout &l, uint64_t bytes)
+{
+    const uint64_t most = g.NW * g.P <= 8 ? 400000000ull : g.HW <= 256 ? 110000000ull : 60000000ull;
+    if (l.shift) return g.HW <= 350 && bytes <= most;
+    return l.quads <= 32 && 5 * g.P * l.quads < 3 * kWave * ((g.P + 1) / 2) && bytes <= most;
+}
+
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
+    const PlaneLayout layout = plane_layout(a.g.HW, a.feat);
     const uint32_t lds = roll_lds_bytes(a.g.S, a.g.P);
+    const uint64_t bytes = 4ull * kFeatC * (uint64_t)n_envs * (uint64_t)(a.g.P * a.g.HW);
+    if (turns_by_cells(a.g, layout, bytes)) {
+        // (4, 8 and 16 waves: 15x15 2v2, 200 envs 144, 108, 103; 300 envs 134,
+        // 115, 163; 512 envs (70 MB) 251, 236, 170; 8x8 1v1, 1,500 envs 127,
+        // 188, 331; 9x9 FFA-8, 1,500 envs 563, 394, 487; 13x15 2v2, 800 envs
+        // 411, 339, 389)
+        const bool one = n_envs <= kCUs || (n_envs <= 2 * kCUs && bytes > 60000000ull);
+        const int nwv = one ? kFeatMostWaves : n_envs > 2 * kCUs && a.g.NW * a.g.P <= 8 ? 4 : kFeatWaves;
+        hipLaunchKernelGGL((k_rollout<true, 1, 1, 1>), dim3((unsigned)n_envs), dim3(kWave * nwv), lds, stream, a);
+        return hipGetLastError();
+    }
     // Waves per env: 16 where a CU has one env, by the batch or by the LDS;
     // 4 in larger batches of boards of which many fit, so that more envs'
     // serial parts run side by side, as long as a turn has little to write
@@ -1232,7 +1261,7 @@ hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
     const uint32_t fit = 160u * 1024u / lds;
     const bool few = a.g.P == 2 ? fit >= 7 : a.g.P <= 4 && fit >= 12;
     const int nwv = n_envs <= kCUs || fit == 1 ? kFeatMostWaves : n_envs > 2 * kCUs && few ? 4 : kFeatWaves;
-    by_layout(plane_layout(a.g.HW, a.feat), a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
+    by_layout(layout, a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
         hipLaunchKernelGGL((k_rollout<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
     });

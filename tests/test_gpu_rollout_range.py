@@ -99,3 +99,28 @@ def test_feature_tensor_off_16_bytes(H, W, mode, P, E, shift):
     check(out, cfg, ost, mem, 12, 0, T, False)
     edge = raw.cpu().numpy()
     assert (edge[:shift] == 7.0).all() and (edge[shift + n:] == 7.0).all()
+
+
+# bytes of a turn's features: 152 E P H W; the limit of each kind of board between the two batches
+@pytest.mark.parametrize("H,W,mode,P,limit", [(15, 15, 2, 8, 110), (9, 9, 2, 5, 110), (11, 13, 1, 4, 110), (8, 8, 2, 3, 400), (17, 17, 1, 4, 60),
+                                              (13, 23, 2, 6, 60)])
+@pytest.mark.parametrize("above", [0, 1])
+def test_at_the_size_limits(H, W, mode, P, limit, above):
+    """Turns by cells up to the limit, by planes above it."""
+    import torch
+    E = limit * 1000000 // (152 * P * H * W) + above
+    gen, b, cfg, ost, mem = make(H, W, mode, P, E, seed=E)
+    out = b.rollout(2, 31, 0, tokens=True)
+    torch.cuda.synchronize()
+    check(out, cfg, ost, mem, 31, 0, 2, True)
+
+
+@pytest.mark.parametrize("H,W,mode,P,E,T", [(23, 23, 0, 2, 3, 12), (15, 15, 2, 8, 3, 20), (16, 16, 2, 7, 3, 12), (17, 19, 1, 4, 300, 4), (15, 15, 2, 5, 400, 4),
+                                            (9, 9, 1, 4, 513, 8), (8, 8, 0, 2, 600, 8), (3, 3, 0, 2, 40, 30), (5, 13, 2, 6, 270, 10)])
+def test_boards_of_each_task(H, W, mode, P, E, T):
+    import torch
+    gen, b, cfg, ost, mem = make(H, W, mode, P, E, seed=T + P)
+    for rep in range(2):
+        out = b.rollout(T, 13, rep * T, tokens=True)
+        torch.cuda.synchronize()
+        check(out, cfg, ost, mem, 13, rep * T, T, True)
