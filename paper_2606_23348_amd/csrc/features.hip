@@ -1227,11 +1227,24 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
 // 775, 631, 393 MB; 15x15 FFA-8, 300 envs 392, 314, 82 MB; 512 envs 409, 510,
 // 140 MB; 17x17 2v2, 300 envs 218, 140, 52 MB; 17x19 FFA-8, 200 envs 232, 281,
 // 78 MB; aligned planes of more than 32 quads: 12x20 2v2, 512 envs 160, 196).
+// Of larger boards, whose plane tasks take three rounds and more, only outputs
+// of a few turns stay (8 turns by planes and by cells: 19x21 2v2, 144 envs (35
+// MB) 106.5, 82.4; 267 envs (65 MB) 193, 234; 25x25 1v1, 105 envs 87.8, 77.0;
+// 25x25 FFA-8, 46 envs 227, 159; 31x31 1v1, 119 envs 96.9, 86.9; 210 envs of
+// 29x27 (50 MB) 104.5, 113.8), and of the aligned ones only those whose third
+// round is half empty (24x24 FFA-8, 42 envs 176, 151; 24x24 1v1, 114 envs 75.8,
+// 77.2, 171 envs 74.4, 71.0; but 20x20 1v1, 164 envs 65.2, 72.3; 28x28 1v1, 83
+// envs 84.2, 90.2; 32x32 FFA-8, 24 envs 206, 215).
 static bool turns_by_cells(const Geom &g, const PlaneLayout &l, uint64_t bytes)
 {
-    const uint64_t most = g.NW * g.P <= 8 ? 400000000ull : g.HW <= 256 ? 110000000ull : 60000000ull;
-    if (l.shift) return g.HW <= 350 && bytes <= most;
-    return l.quads <= 32 && 5 * g.P * l.quads < 3 * kWave * ((g.P + 1) / 2) && bytes <= most;
+    const uint64_t most = g.HW > 350         ? 45000000ull
+                          : g.NW * g.P <= 8  ? 400000000ull
+                          : g.HW <= 256      ? 110000000ull
+                                             : 60000000ull;
+    if (bytes > most) return false;
+    if (l.shift) return true;
+    if (l.rounds == 3) return 5 * l.quads < 4 * kWave * 3;
+    return l.quads <= 32 && 5 * g.P * l.quads < 3 * kWave * ((g.P + 1) / 2);
 }
 
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)

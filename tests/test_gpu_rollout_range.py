@@ -124,3 +124,15 @@ def test_boards_of_each_task(H, W, mode, P, E, T):
         out = b.rollout(T, 13, rep * T, tokens=True)
         torch.cuda.synchronize()
         check(out, cfg, ost, mem, 13, rep * T, T, True)
+
+
+@pytest.mark.parametrize("H,W,mode,P,E", [(19, 21, 0, 2, 371), (19, 21, 0, 2, 372), (25, 25, 2, 8, 59), (25, 25, 2, 8, 60), (24, 24, 1, 4, 128),
+                                          (24, 24, 1, 4, 129), (31, 31, 0, 2, 5), (19, 19, 2, 3, 7), (18, 31, 2, 5, 9), (23, 23, 2, 8, 260)])
+def test_boards_of_three_rounds_and_more(H, W, mode, P, E):
+    """On both sides of 45 MB of features a turn, and boards of 3 to 16 words."""
+    import torch
+    gen, b, cfg, ost, mem = make(H, W, mode, P, E, seed=E + P)
+    for rep, tokens in enumerate((True, False)):
+        out = b.rollout(4, 7, rep * 4, tokens=tokens)
+        torch.cuda.synchronize()
+        check(out, cfg, ost, mem, 7, rep * 4, 4, tokens)
