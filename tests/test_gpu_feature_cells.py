@@ -98,3 +98,21 @@ def test_sightings_older_than_the_age_table(H, W, P, mode):
         assert np.array_equal(bits(b.feat.cpu().numpy()), bits(want)), f"jump {jump}"
     # log1p(120 + ...)/5 of a table entry is below 2.22; later ones are above
     assert (want[:, :, 21] > 2.22).any()
+
+
+@pytest.mark.parametrize("fill", [0xA5, 0x7F, 0xFF])
+@pytest.mark.parametrize("H,W,P,E,mode", [(23, 23, 2, 5, 0), (9, 15, 3, 4, 2), (16, 16, 4, 3, 1), (28, 32, 7, 2, 2), (10, 10, 2, 600, 0)])
+def test_block_of_no_episode(H, W, P, E, mode, fill):
+    """Memory that holds anything but this episode's header counts as empty."""
+    import torch
+    gen, b, cfg, ost, mem = make(H, W, P, E, seed=fill + P, mode=mode)
+    feat = torch.zeros(E * P * 38 * H * W, dtype=torch.float32, device="cuda")
+    fmem = torch.full((gen.gen_feat_mem_bytes(b.st),), fill, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    b.sample(9, 0)
+    for t in range(10):
+        gen.gen_features(b.st, fmem, feat)
+        want = oracle.features(cfg, ost, mem)
+        assert np.array_equal(bits(feat.cpu().numpy().reshape(want.shape)), bits(want)), f"step {t}"
+        gen.gen_step_sample(b.st, b.actions, 9, t + 1, None, b.rewards, b.dones)
+        oracle.step(cfg, ost, oracle.sample(cfg, ost, 9, t))
