@@ -314,7 +314,8 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
         const uint8_t *mask = ch >= 24 + kHist ? F.foe : F.own;
         const int o0 = ((f.t - k) & 7) * S, o1 = ((f.t - k - 1) & 7) * S;
         each([&](int q, int p) {
-            const int4 u = keep4(ld16<ANY>(F.farmy + o0 + q), ld4<ANY>(mask + o0 + q), p), v = keep4(ld16<ANY>(F.farmy + o1 + q), ld4<ANY>(mask + o1 + q), p);
+            const int4 u = keep4(ld16<ANY>(F.farmy + o0 + q), ld4<ANY>(mask + o0 + q), p);
+            const int4 v = keep4(ld16<ANY>(F.farmy + o1 + q), ld4<ANY>(mask + o1 + q), p);
             return make_float4((float)(u.x - v.x), (float)(u.y - v.y), (float)(u.z - v.z), (float)(u.w - v.w));
         });
         return;
@@ -325,7 +326,8 @@ __device__ __forceinline__ void channel(const FeatLds &F, const FrameCtx &f, int
         const uint8_t *mask = ch == 1 ? F.own + now : ch == 2 ? F.foe + now : F.bits;
         const bool own = ch == 1 || ch == 2;
         each([&](int q, int p) {
-            const int4 v = keep4(ld16<ANY>(F.farmy + now + q), ld4<ANY>(mask + (own ? 0 : p * S) + q), own ? p : ch == 0 ? (int)B_NOW : (int)B_NEUTRAL);
+            const int4 v = keep4(ld16<ANY>(F.farmy + now + q), ld4<ANY>(mask + (own ? 0 : p * S) + q),
+                                 own ? p : ch == 0 ? (int)B_NOW : (int)B_NEUTRAL);
             return make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
         });
         break;
@@ -637,7 +639,10 @@ template <int players>
 __device__ __forceinline__ int token_tasks(int P) { return (P + players - 1) / players * (kTokenWindow / kWave); }
 
 // The turn of this lane in task k (before the episode: negative).
-__device__ __forceinline__ int32_t token_turn(const FrameCtx &f, int k) { return f.t - (kTokenWindow - 1) + (k & 7) * kWave + lane_id(); }
+__device__ __forceinline__ int32_t token_turn(const FrameCtx &f, int k)
+{
+    return f.t - (kTokenWindow - 1) + (k & 7) * kWave + lane_id();
+}
 
 // Whether some turn of task k may be in the ring (wave-uniform).
 __device__ __forceinline__ bool token_some(const FrameCtx &f, int k)
@@ -712,7 +717,8 @@ struct TokenWave {
         if (wv + nwv < n) v1 = token_load<players>(f, fb, rm, wv + nwv);
     }
 
-    __device__ __forceinline__ void finish(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv, int nwv)
+    __device__ __forceinline__ void finish(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm,
+                                           float *te, int wv, int nwv)
     {
         if (wv < n) token_store(F, f, v0, wv, te);
         if (wv + nwv < n) token_store(F, f, v1, wv + nwv, te);
@@ -734,8 +740,8 @@ struct TokenWave {
 // plane's stores (12x12 1v1, 12,000 envs without tokens 182 us, with such a
 // load 235; 8 turns of rollout of 13x15 2v2, 600 envs 226, 245).
 template <int players>
-__device__ __forceinline__ void token_windows(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm, float *te, int wv,
-                                              int nwv)
+__device__ __forceinline__ void token_windows(const FeatLds &F, const FrameCtx &f, const FeatBlock &fb, const Rsrc &rm,
+                                              float *te, int wv, int nwv)
 {
     auto stamp = [&](int k) {
         TokenLoad<players> v{};
@@ -1231,9 +1237,13 @@ hipError_t launch_features(const FeatArgs &a, int n_envs, hipStream_t stream)
     const uint32_t fit = 160u * 1024u / lds;
     const bool most = n_envs <= kCUs || fit == 1 || (fit == 2 && a.g.P > 4);
     // 12 below 512 envs, where some CUs hold one env and some two (8, 12 and 16
-    // waves: 9x14 2v2, 286 envs 29.7, 28.1; 9x19 FFA-5, 325 envs 33.9, 32.8,
-    // 39; 24x24 1v1, 320 envs 29.5, 28.8; 13x15 FFA-7, 338 envs 44.9, 45.6, 53).
-    const int nwv = most ? kFeatMostWaves : n_envs < 2 * kCUs ? 12 : n_envs <= 1024 || fit < 6 ? kFeatWaves : fit < 16 ? 4 : 2;
+    // waves, features alone: 24x24 1v1, 320 envs 20.3, 19.9, 25.3; 25x25 FFA-4
+    // with tokens, 300 envs 44.5, 42.4, 48.0; FFA-8 16x16, 300 envs 29.2, 28.6,
+    // 32.7; 23x23 1v1, 450 envs 25.5, 25.0, 28.3; 12x12 1v1, 400 envs 11.4,
+    // 11.3, 15.1; 28x28 2v2, 260 envs 41.6, 41.8, 46.9).
+    int nwv = fit < 6 || n_envs <= 1024 ? kFeatWaves : fit < 16 ? 4 : 2;
+    if (most) nwv = kFeatMostWaves;
+    else if (n_envs < 2 * kCUs) nwv = 12;
     by_layout(layout, a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
         hipLaunchKernelGGL((k_features<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);
@@ -1268,6 +1278,10 @@ static bool turns_by_cells(const Geom &g, const PlaneLayout &l, uint64_t bytes)
     return l.quads <= 32 && 5 * g.P * l.quads < 3 * kWave * ((g.P + 1) / 2);
 }
 
+// Waves 0 to 3 have parts of a turn of their own.
+constexpr int kRollLeastWaves = 4;
+static_assert(kRollLeastWaves >= 4 && kFeatWaves >= kRollLeastWaves && kFeatMostWaves >= kRollLeastWaves, "a wave per part of a turn");
+
 hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
 {
     const PlaneLayout layout = plane_layout(a.g.HW, a.feat);
@@ -1279,7 +1293,7 @@ hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
         // 188, 331; 9x9 FFA-8, 1,500 envs 563, 394, 487; 13x15 2v2, 800 envs
         // 411, 339, 389)
         const bool one = n_envs <= kCUs || (n_envs <= 2 * kCUs && bytes > 60000000ull);
-        const int nwv = one ? kFeatMostWaves : n_envs > 2 * kCUs && a.g.NW * a.g.P <= 8 ? 4 : kFeatWaves;
+        const int nwv = one ? kFeatMostWaves : n_envs > 2 * kCUs && a.g.NW * a.g.P <= 8 ? kRollLeastWaves : kFeatWaves;
         hipLaunchKernelGGL((k_rollout<true, 1, 1, 1>), dim3((unsigned)n_envs), dim3(kWave * nwv), lds, stream, a);
         return hipGetLastError();
     }
@@ -1290,11 +1304,10 @@ hipError_t launch_rollout(const RolloutArgs &a, int n_envs, hipStream_t stream)
     // 934, -; 10x10 1v1, 600 envs 108, 128, -; 13x15 1v1, 5,000 envs 705, 845, -;
     // but 16x16 1v1, 1,000 envs 179, 170; 10x10 2v2, 1,500 envs 327, 302; 13x15
     // 2v2, 1,500 envs 571, 498; 25x25 FFA-8, 512 envs 607, 369, 320; 31x31 1v1
-    // 215, 146, 136; 23x23 1v1 218, 167, 185).  Waves 0 to 3 have parts of
-    // their own.
+    // 215, 146, 136; 23x23 1v1 218, 167, 185).
     const uint32_t fit = 160u * 1024u / lds;
     const bool few = a.g.P == 2 ? fit >= 7 : a.g.P <= 4 && fit >= 12;
-    const int nwv = n_envs <= kCUs || fit == 1 ? kFeatMostWaves : n_envs > 2 * kCUs && few ? 4 : kFeatWaves;
+    const int nwv = n_envs <= kCUs || fit == 1 ? kFeatMostWaves : n_envs > 2 * kCUs && few ? kRollLeastWaves : kFeatWaves;
     by_layout(layout, a.g.P, [&](auto shift, auto lanes, auto rounds, auto players) {
         hipLaunchKernelGGL((k_rollout<shift.value, lanes.value, rounds.value, players.value>), dim3((unsigned)n_envs),
                            dim3(kWave * nwv), lds, stream, a);

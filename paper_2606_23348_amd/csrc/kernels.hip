@@ -84,10 +84,10 @@ __device__ __forceinline__ void quad_planes(const Lds &L, const QuadCells &c, ui
 // cells past the map in a padded plane's last quad to zero.
 // ro: buffer descriptor of the env's block; the plane offset is a scalar
 // operand and 4q the one vector offset of all eight stores.
-// AUX: the stores' cache policy (nontemporal by default: every plane these
-// stores write starts on a 32-byte sector, so no sector is shared by two
-// planes written at different times).
-template <int AUX = kAuxNT>
+// Nontemporal also for dense planes, whose first and last sectors belong to
+// two planes (us per step, plain and nontemporal: 2v2 14x14, 50,000 envs 119,
+// 70; FFA-8 12x13, 32,768 envs 115, 77; 1v1 10x10, 65,536 envs 81.5, 80.3; of
+// whole sectors, 2v2 16x16, 65,536 envs 161, 94).
 __device__ __forceinline__ void quad_store(const Lds &L, const Geom &g, const Rsrc &ro, const QuadCells &qc,
                                            uint32_t ac, int p, int q, int PS, uint32_t keep = ~0u)
 {
@@ -96,7 +96,7 @@ __device__ __forceinline__ void quad_store(const Lds &L, const Geom &g, const Rs
     quad_planes(L, qc, ac, p, ally, q, v);
 #pragma unroll
     for (int ch = 0; ch < 8; ++ch)
-        __builtin_amdgcn_raw_buffer_store_b32(v[ch] & keep, ro, 4 * q, (p * 8 + ch) * PS, AUX);
+        __builtin_amdgcn_raw_buffer_store_b32(v[ch] & keep, ro, 4 * q, (p * 8 + ch) * PS, kAuxNT);
 }
 
 // Two waves per env: wave 0 writes the planes of players 0 .. obs_split(P) - 1
@@ -149,7 +149,8 @@ __device__ __forceinline__ void stage_runs(const Lds &L, const Geom &g, uint8_t 
         ac[k] = reinterpret_cast<const uint32_t *>(L.armyc)[qi];
     }
     if (!WHOLE)
-        for (int i = lane; i < (int)(stage_bytes(g) >> 4); i += kWave) reinterpret_cast<uint4 *>(stage)[i] = make_uint4(0u, 0u, 0u, 0u);
+        for (int i = lane; i < (int)(stage_bytes(g) >> 4); i += kWave)
+            reinterpret_cast<uint4 *>(stage)[i] = make_uint4(0u, 0u, 0u, 0u);
     uint32_t carry = 0u;                               // lane i: dword i of the line the last run left unfinished
     for (int n = runs.begin; n < runs.end; ++n) {
         const int p = HALF ? n : n >> 1;
@@ -560,7 +561,8 @@ struct EnvSrc {
 };
 
 template <int KIND, int OBSV, bool SB, bool ACT, int NWV>
-__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu((SB || (OBSV != OBS_QUAD && OBSV != OBS_STAGED)) ? 1 : 8, 8))) void k_env(EnvArgs a)
+__global__ __launch_bounds__(64 * NWV)
+__attribute__((amdgpu_waves_per_eu((SB || (OBSV != OBS_QUAD && OBSV != OBS_STAGED)) ? 1 : 8, 8))) void k_env(EnvArgs a)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     const Geom g = a.g;
@@ -749,8 +751,10 @@ static int dense_waves(const EnvArgs &a, int n_envs)
 // 102; 1v1 18x18, 8,000 envs 25.6, 21.1; 14x20, 8,192 envs 21.8, 20.2; 16x16,
 // 65,536 envs 80, 98; 28x32, 8,000 envs 31, 36; 2v2 21x21 padded to 448, 28,000
 // envs 87, 78.  A second round of a few cells pays later: 13x20, 8,192 envs
-// 18.6, 20.8; 20,000 envs 44.4, 40.4; 65,536 envs 135, 113.  A reset's maps
-// keep the waves apart, so it gains nothing: 24x24 177, 238.)
+// 18.6, 20.8; 20,000 envs 44.4, 40.4; 65,536 envs 135, 114; held to 18 waves a
+// CU the dword stores take 112 there, 40.2 and, at 17x16, 114 against 112, so
+// two cell counts do not get a rule of their own.  A reset's maps keep the
+// waves apart, so it gains nothing: 24x24 177, 238.)
 static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
 {
     if (kind == K_RESET || a.obs == nullptr || a.g.HW <= kOneRound || a.g.PS % 128 == 0) return false;
@@ -764,9 +768,11 @@ static bool stage_whole(const EnvArgs &a, int n_envs, int kind)
 // step, plane by plane and in pairs: 24x24 1v1, 2,048 envs 9.7, 9.9; 4,096
 // envs 14.0, 13.6; 8,192 envs 24.3, 21.6; FFA-8 24x24, 1,024 envs 15.9, 16.5;
 // 2,048 envs 23.4, 22.0; 2v2 24x24, 28,000 envs 118, 99; FFA-6 16x20, 16,384
-// envs 60, 53; 26x32 1v1, 30,000 envs 147, 129; 16x20 1v1 has too little to
-// store per decoded cell: 32,768 envs 45.5, 48.0; boards of one round: 12x16
-// 1v1, 65,536 envs 77, 82).
+// envs 60, 53; 26x32 1v1, 30,000 envs 147, 129; 14x32 1v1, 8,192 envs 18.5,
+// 17.7; FFA-3 10x32, 8,192 envs 19.3, 17.8; two players' planes of 320 cells
+// have too little to store per decoded cell, in each of four shapes: 9,000
+// envs 17.6, 18.6; 32,768 envs 46.0, 48.3; 65,536 envs 85, 89; 78,000 envs,
+// 400 MB 172, 143; boards of one round: 12x16 1v1, 65,536 envs 77, 82).
 static bool pair_planes(const EnvArgs &a, int n_envs)
 {
     if (a.obs == nullptr || a.g.PS != a.g.HW || a.g.HW <= kOneRound || a.g.HW % 128 != 64 || n_envs < 2048) return false;
@@ -774,14 +780,14 @@ static bool pair_planes(const EnvArgs &a, int n_envs)
     return bytes >= (a.g.P * a.g.HW < 800 ? 400000000ull : 35000000ull);
 }
 
-// LDS of the dword writers by one wave: with more than 4 players and planes
-// of more than one line a batch is held to 16 waves a CU, since the lines that two planes
-// share leave the L2 in parts when the 32 waves that would fit all store
-// (us per step with 32 and 16 waves: FFA-8 12x12, 32,768 envs 92, 75; FFA-8
-// 12x13 108, 86; FFA-8 14x14, 16,384 envs 68, 63; FFA-6 14x14, 32,768 envs 93,
-// 71; FFA-5 14x14 74, 64; FFA-8 12x12 padded, 32,768 envs 94, 77; planes
-// within a line or fewer players need the waves: FFA-8 10x10 62, 74; 2v2 14x14, 50,000 envs 73, 88; below 8,192 envs
-// the same either way).
+// LDS of the dword writers by one wave: with more than 4 players and planes of
+// more than one line a batch is held to 16 waves a CU, since the lines that
+// two planes share leave the L2 in parts when the 32 waves that would fit all
+// store (us per step with 32 and 16 waves: FFA-8 12x12, 32,768 envs 92, 75;
+// FFA-8 12x13 108, 86; FFA-8 14x14, 16,384 envs 68, 63; FFA-6 14x14, 32,768
+// envs 93, 71; FFA-5 14x14 74, 64; FFA-8 12x12 padded, 32,768 envs 94, 77;
+// planes within a line or fewer players need the waves: FFA-8 10x10 62, 74;
+// 2v2 14x14, 50,000 envs 73, 88; below 8,192 envs the same either way).
 constexpr uint32_t kSixteenWavesLds = 10240;
 
 static uint32_t dword_lds(const EnvArgs &a, int n_envs, uint32_t lds)
@@ -814,7 +820,8 @@ static hipError_t launch_kind(const EnvArgs &a, int n_envs, hipStream_t stream)
     const bool staged = a.g.HW % 4 != 0, paired = pair_planes(a, n_envs);
     if (staged && nwv > 1) {
         if constexpr (KIND != K_RESET)
-            hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 8>), grid, dim3(kWave * nwv), lds_dense + (uint32_t)(nwv - 1) * stage_bytes(a.g), stream, a);
+            hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 8>), grid, dim3(kWave * nwv),
+                               lds_dense + (uint32_t)(nwv - 1) * stage_bytes(a.g), stream, a);
     } else if (staged) {
         hipLaunchKernelGGL((k_env<KIND, OBS_STREAM, SB, ACT, 1>), grid, block, lds_dense, stream, a);
     } else if (!paired && stage_whole(a, n_envs, KIND)) {
