@@ -10,12 +10,14 @@
 // then each wave writes whole planes: one (player, channel) at a time, so
 // the channel is wave-uniform, four consecutive cells per lane, 16-byte
 // nontemporal stores in runs on 128-byte boundaries whatever the board's
-// size, the waves of a workgroup side by side.  Before, a lane per cell wrote
-// all channels with 4-byte stores; where planes are no multiple of 128 bytes
-// every line then was written in parts.  Features and step, us: FFA-8 25x25,
-// 1,024 envs, 347 -> 206 (24x24 178 -> 167); 1v1 25x25, 8,192 envs, 665 ->
-// 445; 24x24, 460 -> 385; 10x10, 163 -> 113; 24x24 with tokens, 65,536 envs,
-// 3,400 -> 3,100, where constant planes take 2,600: the stores bound it.
+// size, the waves of a workgroup side by side.  A lane per cell that writes
+// all channels with 4-byte stores leaves every line in parts where planes are
+// no multiple of 128 bytes; it stays for outputs that the last-level cache
+// puts together (cell_task, by_cells).  Features and step, us, all by cells
+// before: FFA-8 25x25, 1,024 envs, 347 -> 195 (24x24 178 -> 167); 1v1 25x25,
+// 8,192 envs, 665 -> 445; 24x24, 460 -> 385; 10x10, 163 -> 113; 24x24 with
+// tokens, 65,536 envs, 3,400 -> 3,100, where constant planes take 2,600: the
+// stores bound it.
 // Measured and not kept: runs of 2 to 4 planes per wave with the values at
 // their seams carried over (10 to 25% slower: the waves write further apart).
 #define GEN_LANE_PER_USE        // see lane_id()
