@@ -195,16 +195,16 @@ def run_step_alone(b, wl, torch, stream, steps: int, first_step: int) -> dict:
             "achieved_gbs": alone * b.n_envs / (float(ms.mean()) / 1e3) / 1e9, "algorithmic_bytes_per_frame": alone}
 
 
-def feature_bytes(wl) -> dict:
+def feature_bytes(wl, held: int = 512) -> dict:
     """Algorithmic HBM bytes per frame of gen_features: it reads the state,
     the memory header, the per-player memory (1 + 4 + 4 bytes per cell) and
     the 7 earlier frames of the ring (6 bytes per cell each); it writes the
     per-player memory, this frame's ring slot, the header and the float32
-    [P][38][H][W] features."""
+    [P][38][H][W] features.  held: the turns that the scoreboard ring holds."""
     HW, P, win = wl.H * wl.W, wl.P, 512
     read = HW * 6 + 32 + 64 + 9 * P * HW + 7 * 6 * HW
     write = 9 * P * HW + 6 * HW + 40 + 38 * 4 * P * HW + 4 + 12 * P
-    tok_read = win * 4 + win * 12 * P            # the scoreboard ring, for the 512-turn windows
+    tok_read = held * 4 + held * 12 * P          # the scoreboard ring, for the 512-turn windows
     tok_write = 2 * win * 4 * P
     return {"read": read, "write": write, "total": read + write,
             "total_with_tokens": read + write + tok_read + tok_write}
@@ -223,7 +223,7 @@ def run_features(b, wl, torch, stream, steps: int, first_step: int) -> dict:
         ev1[t].record(stream)
     torch.cuda.synchronize()
     ms = np.array([ev0[t].elapsed_time(ev1[t]) for t in range(steps)])
-    by = feature_bytes(wl)
+    by = feature_bytes(wl, min(512, (steps + 3) // 2))     # the ring fills from the first call on: its mean
     out = {"kernel": "k_features (gen_features, with the temporal tokens)", "steps": steps,
            "kernel_ms_mean": float(ms.mean()), "kernel_ms_p50": float(np.percentile(ms, 50)),
            "frames_per_s": b.n_envs / (float(ms.mean()) / 1e3),
